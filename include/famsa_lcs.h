@@ -253,10 +253,11 @@ void famsa_slink_destroy(famsa_slink_t* s);
  * the maximum spanning tree of the similarities, so instead of SLINK's
  * pointer representation this consumer keeps that tree on the device: after
  * each device tile (FAMSA_LCS_DEVICE_TILES) it replaces its forest with the
- * maximum spanning forest of the forest plus the tile's pairs (Boruvka
- * rounds on the GPU, one pass over the tile per round).  Device memory is
- * O(k) plus per-round partial results of about k * R / 50 entries for tiles
- * of R rows (R <= 65535); tiles may come in any order.  Similarities are
+ * maximum spanning forest of the forest plus the tile's pairs (one pass over
+ * the tile keeps the pairs better than the worst edge on the forest's path
+ * between their ends, then Boruvka rounds on the GPU).  Device memory is O(k),
+ * about 1.2 KB a sequence, in one allocation made by famsa_mst_create; tiles
+ * hold at most 65535 rows and may come in any order.  Similarities are
  * ordered exactly; equal similarities are ordered by the pair (u, v), u < v,
  * so the tree is unique.
  * ------------------------------------------------------------------------ */

@@ -7,15 +7,27 @@
 // similarities, so keeping that tree is enough: after every tile, the forest
 // F becomes the maximum spanning forest of F plus the tile's pairs (a forest
 // that is optimal for a set of edges stays a valid summary of it, by the
-// cycle property).  Each update is a Boruvka run on the device:
-//   1. every vertex finds its best edge to another component -- a row pass
-//      over the tile's rows, a column pass over its columns, and a pass over
-//      F's edges;
-//   2. every component takes the best of its vertices' edges (a two-phase
-//      atomic maximum on the similarity, then minimum on the edge id);
-//   3. components hook along their edges and are relabelled by pointer
-//      jumping; the hooked edges form the new forest;
-// until no component has an outgoing edge.
+// cycle property).  One update:
+//   1. a pair (i, j) of the tile can enter the forest only if it is better
+//      than the worst edge on F's path between i and j; one pass over the
+//      tile (mst_filter) keeps the pairs that are, the survivors;
+//   2. Boruvka on F plus the survivors gives the new forest: every component
+//      takes the best edge that leaves it, components hook along these edges
+//      and are renumbered, edges inside a component are dropped;
+//   3. the rounds' components are the hierarchy that answers the next pass's
+//      path queries (mst_view).
+// The path query (King's lemma on Boruvka trees): the worst edge on the path
+// between i and j in the forest is the worst of the edges that i's and j's
+// components chose in the rounds before they became one.  So per vertex and
+// round the component's label and the worst edge chosen so far suffice: a
+// pair looks up the lowest round in which its labels agree.
+// The tile is read once (four bytes a pair) instead of once and then in parts
+// in each of five or six rounds, and the rounds work on the forest and a few
+// edges a vertex.  Per 1,024-row tile of 30,000 columns the pass takes 12-50 us
+// (later tiles are narrower) and the update behind it about 130 us, most of it
+// launches and one workgroup's latency, against 560 us for dense rounds; k =
+// 12,000 sequences of 60 residues to their guide tree 9.3 -> 5.2 ms, k =
+// 30,000 of 250 88.8 -> 78.4 ms (the LCS kernels are 70 of them).
 //
 // Similarity (Methods, "Pairwise similarities calculation") is
 // LCS / indel^2 with indel = |A| + |B| - 2 LCS, +infinity when indel = 0.
@@ -28,6 +40,8 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <algorithm>
+#include <new>
 #include <vector>
 
 #include "runtime.h"
@@ -47,45 +61,181 @@ __device__ __forceinline__ bool better(uint64_t ka, uint64_t ia, uint64_t kb, ui
   return ka > kb || (ka == kb && ia < ib);
 }
 
+// A vertex's place in the last hierarchy, the coarsest rounds first: slot s
+// is round D - s of D.  label: the vertex's component after that round (the
+// vertex itself where the hierarchy has no such round: labels of different
+// vertices then never agree).  bound: the worst similarity its components
+// chose up to that round, rounded down.
+constexpr uint32_t kMstSlots = 8;
+struct MstView {
+  uint32_t label[kMstSlots];
+  float bound[kMstSlots];
+};
+struct MstExact {  // the same choice exactly
+  uint64_t key[kMstSlots], id[kMstSlots];
+};
+
+constexpr uint32_t kMstMaxRounds = 40;
+struct MstCtl {
+  uint32_t nf;      // edges in the forest
+  uint32_t pad;
+  uint64_t rounds;  // Boruvka rounds with hooks, over all updates
+};
+struct MstPass {  // one update; the next one's is cleared by this one's last launch
+  uint32_t nsurv;   // the tile's surviving pairs
+  uint32_t nnew;    // edges in the new forest
+  uint32_t ntot;    // component labels given out: vertices first, then each round's components
+  uint32_t levels;  // rounds with hooks
+  uint32_t act[kMstMaxRounds];  // round r runs on the whole GPU
+  uint32_t cnt[kMstMaxRounds];  // edges between components in round r
+  uint32_t hi[kMstMaxRounds];   // labels of round r's components end here
+};
+
+struct MstComp {  // per component label, 2 k of them
+  uint64_t* key;  // best outgoing edge
+  uint64_t* id;
+  uint32_t* par;  // hook target, then the root of the hooked tree
+  uint32_t* nid;  // of a root: its label in the next round
+};
+
 struct MstDev {
   const uint32_t* len;
   uint32_t k;
-  uint32_t* comp;     // component label of each vertex
-  uint32_t* parent;   // hook target of each component root
-  uint64_t* vkey;     // best outgoing edge per vertex: key, id, LCS
-  uint64_t* vid;
-  int32_t* vL;
-  uint64_t* wkey;     // best forest edge per vertex (merged into vkey/vid/vL)
-  uint64_t* wid;
-  int32_t* wL;
-  uint64_t* ckey;     // best outgoing edge per component
-  uint64_t* cid;
-  uint64_t* pkey;     // row partials: best edge of each (tile row, column block)
-  uint64_t* pid;
-  int32_t* pL;
-  uint64_t* qkey;     // column partials: best edge of each (row slice, column)
-  uint64_t* qid;
-  int32_t* qL;
-  const uint32_t* fu;  // current forest edges (ctl->nf of them)
-  const uint32_t* fv;
-  const int32_t* fL;
-  uint32_t* nu;        // new forest edges (ctl->nnew of them)
+  uint32_t room;      // survivors the e* arrays hold after the forest's k - 1 edges
+  uint32_t* eu;       // forest edges (ctl->nf), then the survivors
+  uint32_t* ev;
+  uint64_t* ekey;
+  int32_t* eL;
+  uint32_t* nu;       // the new forest (ps->nnew)
   uint32_t* nv;
+  uint64_t* nkey;
   int32_t* nL;
-  struct Ctl {
-    uint32_t nf;      // edges in the current forest
-    uint32_t nnew;    // edges in the new forest
-    uint32_t hooks;   // hooks in this round
-    uint32_t done;    // no component has an outgoing edge: later rounds do nothing
-    uint64_t rounds;  // rounds that did work, over all tiles
-  }* ctl;
+  uint32_t* lu[2];    // edges between components: labels of the ends, index in e*, key
+  uint32_t* lv[2];
+  uint32_t* le[2];
+  uint64_t* lk[2];
+  MstComp c;          // this update's components
+  MstComp next;       // the next update's
+  MstPass* ps;
+  MstPass* ps_next;
+  MstView* view;
+  MstExact* exact;
+  MstCtl* ctl;
+  uint32_t* host;     // pinned: [0] survivors of this update
 };
 
-// The scan: a block covers 256 columns (four per lane) and a slice of 64
-// tile rows, split over its four waves.
-constexpr uint32_t kScanCols = 256;
-constexpr uint32_t kScanSlice = 64;
-constexpr uint32_t kScanWaves = 4;
+// The last rounds run in one workgroup, components in LDS.
+constexpr uint32_t kFinThreads = 1024;
+constexpr uint32_t kFinComps = 4096;
+constexpr uint32_t kFinEdges = 16384;
+constexpr size_t kFinLds = (size_t)kFinComps * 24;
+
+// An update is left undone when its survivors do not fit (the host repeats it
+// with fewer rows), and has nothing to do when there are none.
+__device__ __forceinline__ bool mst_idle(const MstDev& m) {
+  const uint32_t n = m.ps->nsurv;
+  return n == 0 || n > m.room;
+}
+
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// A slot of *counter for every lane that is `on`: one atomic a wave.  Every
+// lane of the wave calls it.
+__device__ __forceinline__ uint32_t wave_slot(bool on, uint32_t* counter) {
+  const uint64_t mask = __ballot(on);
+  if (mask == 0) return 0;
+  const int lead = __builtin_ctzll(mask);
+  uint32_t base = 0;
+  if ((int)__lane_id() == lead) base = atomicAdd(counter, (uint32_t)__popcll(mask));
+  base = (uint32_t)__shfl((int)base, lead, 64);
+  return base + lanes_below(mask);
+}
+
+__device__ __forceinline__ void offer(uint64_t* slot, uint64_t key) {
+  if (key > *slot) atomicMax((unsigned long long*)slot, (unsigned long long)key);  // a stale read only costs an atomic
+}
+
+// The same for a block, with one global atomic: appends from all eight XCDs to
+// one counter are served one after another, about 60 ns each.  Every thread of
+// the block calls it; `red` is LDS of its own.
+struct BlockSlots {
+  uint32_t wave[16];
+  uint32_t base;
+};
+__device__ __forceinline__ uint32_t block_slot(bool on, uint32_t* counter, BlockSlots* red) {
+  const uint32_t w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const uint64_t mask = __ballot(on);
+  if ((threadIdx.x & 63u) == 0) red->wave[w] = (uint32_t)__popcll(mask);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t sum = 0;
+    for (uint32_t i = 0; i < nw; ++i) {
+      const uint32_t n = red->wave[i];
+      red->wave[i] = sum;
+      sum += n;
+    }
+    red->base = sum ? atomicAdd(counter, sum) : 0u;
+  }
+  __syncthreads();
+  const uint32_t at = red->base + red->wave[w] + lanes_below(mask);
+  __syncthreads();  // the LDS is used again by the next call
+  return at;
+}
+
+// A block's offers, gathered in LDS by component before they go out: where few
+// components are left, thousands of edges offer to the same slot, and those
+// atomics would be served one after another too.  A component whose place in
+// the table is taken by another goes out at once.
+constexpr uint32_t kOffers = 2048;
+struct OfferTable {
+  uint32_t comp[kOffers];
+  uint64_t key[kOffers];
+};
+__device__ __forceinline__ void offers_begin(OfferTable* t) {
+  for (uint32_t x = threadIdx.x; x < kOffers; x += blockDim.x) {
+    t->comp[x] = 0xFFFFFFFFu;
+    t->key[x] = 0;
+  }
+  __syncthreads();
+}
+__device__ __forceinline__ void offers_add(OfferTable* t, uint64_t* slots, uint32_t c, uint64_t key) {
+  const uint32_t x = (c * 2654435761u) >> 21;  // 11 bits
+  uint32_t have = t->comp[x];
+  if (have == 0xFFFFFFFFu) {
+    have = atomicCAS(&t->comp[x], 0xFFFFFFFFu, c);
+    if (have == 0xFFFFFFFFu) have = c;
+  }
+  if (have == c) offer(&t->key[x], key);
+  else offer(&slots[c], key);
+}
+__device__ __forceinline__ void offers_end(OfferTable* t, uint64_t* slots) {
+  __syncthreads();
+  for (uint32_t x = threadIdx.x; x < kOffers; x += blockDim.x)
+    if (t->comp[x] != 0xFFFFFFFFu) offer(&slots[t->comp[x]], t->key[x]);
+}
+
+// Clear the components and counters of an update.
+__device__ __forceinline__ void mst_clear(const MstComp& c, MstPass* ps, uint32_t k) {
+  const uint64_t n = 2ull * k, step = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t x = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += step) {
+    c.key[x] = 0;
+    c.id[x] = ~0ull;
+    c.par[x] = (uint32_t)x;
+  }
+  if (blockIdx.x == 0 && threadIdx.x < kMstMaxRounds) {
+    ps->act[threadIdx.x] = 0;
+    ps->cnt[threadIdx.x] = 0;
+    ps->hi[threadIdx.x] = 0;
+    if (threadIdx.x == 0) {
+      ps->nsurv = 0;
+      ps->nnew = 0;
+      ps->ntot = k;
+      ps->levels = 0;
+    }
+  }
+}
 
 // Values before tile row i (rows r0.. of the upper triangle, k - 1 - t per row t).
 __device__ __forceinline__ uint64_t row_off(uint64_t k, uint32_t r0, uint32_t i) {
@@ -93,366 +243,531 @@ __device__ __forceinline__ uint64_t row_off(uint64_t k, uint32_t r0, uint32_t i)
   return n * (k - 1) - ((uint64_t)r0 + i - 1) * n / 2;
 }
 
-__device__ __forceinline__ void take(uint64_t& bk, uint64_t& bi, int32_t& bL, uint64_t k2, uint64_t i2, int32_t L2) {
-  if (better(k2, i2, bk, bi)) {
-    bk = k2;
-    bi = i2;
-    bL = L2;
-  }
-}
+// The pass over the tile: rows r0 + t stride for t in [t0, t1), without every
+// eighth (t a multiple of 8) when `skip` is set (taken by an earlier pass).
+// A block takes 128 columns and a slice of rows; each of its waves holds the
+// columns' labels and bounds in registers (two columns a lane: four would take
+// twice the registers and hide no more latency) and walks rows four at a time,
+// their labels and bounds wave-uniform and their loads in flight together.  A
+// pair costs four instructions a slot and a float comparison, so the pass is
+// bound by reading the tile.  Pairs the rounded bound does not drop (few) are
+// compared exactly with the edge the bound stands for.  Survivors gather in
+// LDS and leave with one global atomic a block.
+constexpr uint32_t kFiltCols = 2;
+constexpr uint32_t kFiltWaves = 16;
+constexpr uint32_t kFiltChunk = 4;
+constexpr uint32_t kFiltBuf = 3072;
 
-// Wave-wide best of (key, id, L); every lane gets the result.
-__device__ __forceinline__ void wave_best(uint64_t& bk, uint64_t& bi, int32_t& bL) {
+__global__ __launch_bounds__(64 * kFiltWaves) void mst_filter(MstDev m, const MstView* __restrict__ view,
+                                                              const uint32_t* __restrict__ len,
+                                                              const int32_t* __restrict__ tile, uint32_t r0,
+                                                              uint32_t r1, uint32_t t0, uint32_t t1, uint32_t slice,
+                                                              uint32_t stride, uint32_t skip, uint32_t j0) {
+  __shared__ uint32_t bi[kFiltBuf], bj[kFiltBuf];
+  __shared__ int32_t bL[kFiltBuf];
+  __shared__ uint32_t s_n, s_base;
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t k = m.k, nf = m.ctl->nf;
+  const uint32_t jb = j0 + blockIdx.x * (64u * kFiltCols);  // < k
+  const uint32_t tb = t0 + blockIdx.y * slice, te = min(t1, tb + slice);
+  const uint32_t last = min(r1, k - 1u) - 1u;  // the tile's last row with a pair
+  if (r0 + tb * stride >= jb + 64u * kFiltCols - 1u) return;  // no column of the block is after its first row
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
+  uint32_t lj[kFiltCols];
+  MstView vj[kFiltCols];
 #pragma unroll
-  for (int d = 32; d > 0; d >>= 1) {
-    const uint64_t k2 = __shfl_xor(bk, d, 64);
-    const uint64_t i2 = __shfl_xor(bi, d, 64);
-    const int32_t L2 = __shfl_xor(bL, d, 64);
-    take(bk, bi, bL, k2, i2, L2);
+  for (int c = 0; c < (int)kFiltCols; ++c) {
+    const uint32_t j = min(jb + 64u * c + lane, k - 1u);
+    vj[c] = view[j];
+    lj[c] = len[j];
   }
-}
-
-__global__ void mst_tile_begin(MstDev m) {
-  const uint32_t v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v == 0) {
-    m.ctl->done = 0;
-    m.ctl->hooks = 0;
-    m.ctl->nnew = 0;
-  }
-  if (v >= m.k) return;
-  m.comp[v] = v;
-  m.parent[v] = v;
-}
-
-// One pass over the tile per round, in small blocks that fit beside the
-// LCS kernels.  Block (bx, sy) covers columns [256 bx, 256 bx + 256) (four
-// per lane) and the 64 tile rows of slice sy that have a column after them
-// in the block; each element (i, j) whose ends lie in different components is
-// a candidate for both ends.  A row's best over the block's columns is a wave
-// reduction, stored as partial (row, bx); a column's best over the slice's
-// rows is reduced over the four waves in LDS and stored as partial (sy, j).
-//
-// Components only grow during a tile's rounds, so the candidates of a row or
-// a column only shrink: a partial whose edge still joins two components is
-// still the best of its set.  After the tile's first round a block therefore
-// recomputes only the partials whose edge has since fallen inside one
-// component, and reads only the elements those partials need.
-__global__ __launch_bounds__(256) void mst_scan(MstDev m, const int32_t* __restrict__ tile, uint32_t r0, uint32_t r1,
-                                                uint32_t nblk, uint32_t bx0, uint32_t first) {
-  if (m.ctl->done) return;
-  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-  const uint32_t bx = bx0 + blockIdx.x;  // blocks left of column r0 + 1 hold no pair and are not launched
-  const uint32_t jb = bx * kScanCols;
-  const uint64_t k = m.k;
-  uint64_t ck[4], cid[4];
-  int32_t cL[4];
-  uint32_t cc[4], cl[4];
-  bool cnew[4];  // column partial (sy, j) to recompute
-  bool anycol = false;
+  for (uint32_t t = tb + wave * kFiltChunk; t < te; t += kFiltChunk * kFiltWaves) {
+    if (r0 + t * stride >= jb + 64u * kFiltCols - 1u) break;  // nor after this row or later ones
+    int32_t L[kFiltChunk][kFiltCols];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    ck[c] = 0;
-    cid[c] = ~0ull;
-    cL[c] = 0;
-    const uint32_t j = jb + 64u * c + lane;
-    cc[c] = j < m.k ? m.comp[j] : 0u;
-    cl[c] = j < m.k ? m.len[j] : 0u;
-    cnew[c] = j < m.k;
-    if (!first && j < m.k) {
-      const uint64_t q = (uint64_t)blockIdx.y * k + j;
-      // no candidate then means none now; else recompute once its row end joined j's component
-      cnew[c] = m.qkey[q] != 0 && m.comp[(uint32_t)(m.qid[q] / k)] == cc[c];
+    for (int u = 0; u < (int)kFiltChunk; ++u) {  // unconditional loads from clamped pairs of the tile
+      const uint32_t i = min(r0 + min(t + (uint32_t)u, te - 1u) * stride, last);
+      const uint64_t off = row_off(k, r0, i);
+#pragma unroll
+      for (int c = 0; c < (int)kFiltCols; ++c) {
+        const uint32_t j = min(max(jb + 64u * c + lane, i + 1u), k - 1u);
+        L[u][c] = tile[off + (j - i - 1u)];
+      }
     }
-    anycol |= cnew[c];
-  }
-  anycol = __any(anycol);
-  const uint32_t i0 = r0 + blockIdx.y * kScanSlice;
-  const uint32_t iend = min(min(r1, i0 + kScanSlice), jb + kScanCols - 1u);  // rows with a column of the block after them
-  // The wave's rows are i0 + wave + kScanWaves t.  Lane t reads row t's
-  // component, length and partial up front, all rows at once; rows are then
-  // taken kChunk at a time, each group's tile loads issued together.
-  constexpr uint32_t kRows = kScanSlice / kScanWaves;
-  constexpr uint32_t kChunk = 4;  // rows whose tile loads are in flight together (8: slower)
-  const uint32_t myrow = i0 + wave + kScanWaves * lane;
-  const bool myok = lane < kRows && myrow < iend;
-  uint32_t mci = 0, mli = 0;
-  bool mnew = false;
-  if (myok) {
-    mci = m.comp[myrow];
-    mli = m.len[myrow];
-    mnew = true;
-    if (!first) {
-      const uint64_t p = (uint64_t)(myrow - r0) * nblk + bx;
-      mnew = m.pkey[p] != 0 && m.comp[(uint32_t)(m.pid[p] % k)] == mci;
-    }
-  }
-  const uint32_t nrows = (uint32_t)__popcll(__ballot(myok));  // rows 0..nrows-1 of the wave exist
-  const uint64_t newmask = __ballot(mnew);
-  for (uint32_t t0 = 0; t0 < nrows && (anycol || (newmask >> t0) != 0); t0 += kChunk) {
-    int32_t L[kChunk][4];
-    uint32_t ci[kChunk], li[kChunk];
-    bool rnew[kChunk];
+    uint64_t keep[kFiltChunk][kFiltCols];
+    uint32_t total = 0;
 #pragma unroll
-    for (int u = 0; u < (int)kChunk; ++u) {
-      const uint32_t t = t0 + (uint32_t)u;
-      const bool live = t < nrows;
-      const uint32_t i = i0 + wave + kScanWaves * t;
-      ci[u] = (uint32_t)__shfl((int)mci, (int)(t & 63u), 64);
-      li[u] = (uint32_t)__shfl((int)mli, (int)(t & 63u), 64);
-      rnew[u] = live && ((newmask >> t) & 1ull);
-      const uint64_t off = row_off(k, r0, i);  // LCS(i, j) at off + j - i - 1
+    for (int u = 0; u < (int)kFiltChunk; ++u) {
+      const uint32_t tu = t + (uint32_t)u, i = r0 + tu * stride;
+      const bool live = tu < te && i <= last && !(skip && (tu & 7u) == 0);
+      const uint32_t ic = min(i, last);
+      const MstView& vi = view[ic];
+      const uint32_t li = len[ic];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {  // only pairs across components, and only those a partial needs
+      for (int c = 0; c < (int)kFiltCols; ++c) {
         const uint32_t j = jb + 64u * c + lane;
-        L[u][c] = (live && j > i && j < m.k && cc[c] != ci[u] && (rnew[u] || cnew[c])) ? tile[off + (j - i - 1u)] : 0;
-      }
-    }
+        float T = -1.0f;  // no round in which the pair is one component: nothing to beat
+        uint32_t slot = kMstSlots;
 #pragma unroll
-    for (int u = 0; u < (int)kChunk; ++u) {
-      const uint32_t t = t0 + (uint32_t)u;
-      if (t >= nrows) break;
-      const uint32_t i = i0 + wave + kScanWaves * t;
-      uint64_t rk = 0, ri = ~0ull;
-      int32_t rL = 0;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const uint32_t j = jb + 64u * c + lane;
-        if (j > i && j < m.k && cc[c] != ci[u] && (rnew[u] || cnew[c])) {
-          const uint64_t key = sim_key(L[u][c], li[u], cl[c]);
-          const uint64_t id = (uint64_t)i * k + j;
-          if (cnew[c]) take(ck[c], cid[c], cL[c], key, id, L[u][c]);
-          take(rk, ri, rL, key, id, L[u][c]);
+        for (int s = 0; s < (int)kMstSlots; ++s) {
+          const bool eq = vi.label[s] == vj[c].label[s];
+          T = eq ? fminf(vi.bound[s], vj[c].bound[s]) : T;
+          slot = eq ? (uint32_t)s : slot;
         }
-      }
-      if (rnew[u]) {
-        if (__any(rk != 0)) wave_best(rk, ri, rL);  // else no lane has a candidate: (0, ~0, 0) as it is
-        if (lane == 0) {
-          const uint64_t p = (uint64_t)(i - r0) * nblk + bx;
-          m.pkey[p] = rk;
-          m.pid[p] = ri;
-          m.pL[p] = rL;
+        const float d = (float)((int32_t)(li + lj[c]) - 2 * L[u][c]);
+        // not (L < T d^2): an infinite bound and d = 0 compare as unordered and are looked at exactly
+        bool on = live && j > i && j < k && !((float)L[u][c] < T * d * d);
+        if (__any(on)) {
+          if (on && slot < kMstSlots) {
+            const uint64_t key = sim_key(L[u][c], li, lj[c]), id = (uint64_t)i * k + j;
+            const MstExact *xi = m.exact + i, *xj = m.exact + j;
+            const uint64_t ki = xi->key[slot], ii = xi->id[slot], kj = xj->key[slot], ij = xj->id[slot];
+            const bool w = better(ki, ii, kj, ij);  // the worse of the two is j's
+            on = better(key, id, w ? kj : ki, w ? ij : ii);
+          }
         }
+        keep[u][c] = __ballot(on);
+        total += (uint32_t)__popcll(keep[u][c]);
+      }
+    }
+    if (total == 0) continue;
+    uint32_t base = 0;
+    if (lane == 0) base = atomicAdd(&s_n, total);
+    base = __builtin_amdgcn_readfirstlane(base);
+    uint32_t over = 0;  // past the block's buffer: straight to the list
+    if (base + total > kFiltBuf) {
+      const uint32_t out = base + total - max(base, kFiltBuf);
+      if (lane == 0) over = atomicAdd(&m.ps->nsurv, out);
+      over = __builtin_amdgcn_readfirstlane(over) - max(base, kFiltBuf);
+    }
+#pragma unroll
+    for (int u = 0; u < (int)kFiltChunk; ++u) {
+      const uint32_t i = r0 + (t + (uint32_t)u) * stride;
+#pragma unroll
+      for (int c = 0; c < (int)kFiltCols; ++c) {
+        const uint32_t at = base + lanes_below(keep[u][c]);
+        if ((keep[u][c] >> lane) & 1ull) {
+          if (at < kFiltBuf) {
+            bi[at] = i;
+            bj[at] = jb + 64u * c + lane;
+            bL[at] = L[u][c];
+          } else if (over + at < m.room) {
+            const uint32_t e = nf + over + at;
+            m.eu[e] = i;
+            m.ev[e] = jb + 64u * c + lane;
+            m.ekey[e] = sim_key(L[u][c], len[i], lj[c]);
+            m.eL[e] = L[u][c];
+          }
+        }
+        base += (uint32_t)__popcll(keep[u][c]);
       }
     }
   }
-  __shared__ uint64_t sk[kScanWaves / 2][kScanCols], si[kScanWaves / 2][kScanCols];
-  __shared__ int32_t sL[kScanWaves / 2][kScanCols];
-  for (uint32_t h = kScanWaves / 2; h > 0; h >>= 1) {
-    if (wave >= h && wave < 2 * h) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        sk[wave - h][64 * c + lane] = ck[c];
-        si[wave - h][64 * c + lane] = cid[c];
-        sL[wave - h][64 * c + lane] = cL[c];
+  __syncthreads();
+  const uint32_t n = min(s_n, kFiltBuf);
+  if (n == 0) return;
+  if (threadIdx.x == 0) s_base = atomicAdd(&m.ps->nsurv, n);
+  __syncthreads();
+  const uint32_t base = s_base;
+  for (uint32_t x = threadIdx.x; x < n && base + x < m.room; x += 64 * kFiltWaves) {
+    const uint32_t e = nf + base + x, i = bi[x], j = bj[x];
+    m.eu[e] = i;
+    m.ev[e] = j;
+    m.ekey[e] = sim_key(bL[x], len[i], len[j]);
+    m.eL[e] = bL[x];
+  }
+}
+
+// Boruvka round r, in four launches over the whole GPU while there are more
+// components or edges than one workgroup takes.  mst_edges: edges get their
+// ends' labels in this round, those inside a component are dropped, the
+// others offer their key to both ends' components.
+constexpr uint32_t kEdgeThreads = 1024;
+
+struct MstList {  // a round's edges; round 0's are the e* arrays themselves
+  const uint32_t *u, *v, *x;
+  const uint64_t* key;
+};
+__device__ __forceinline__ MstList mst_list(const MstDev& m, uint32_t r) {
+  return r == 0 ? MstList{m.eu, m.ev, nullptr, m.ekey}
+                : MstList{m.lu[r & 1], m.lv[r & 1], m.le[r & 1], m.lk[r & 1]};
+}
+
+__global__ __launch_bounds__(kEdgeThreads) void mst_edges(MstDev m, uint32_t r) {
+  __shared__ BlockSlots red;
+  __shared__ OfferTable table;
+  const bool idle = mst_idle(m);
+  MstPass* ps = m.ps;
+  const uint32_t n = r == 0 ? m.ctl->nf + ps->nsurv : ps->cnt[r - 1];
+  const uint32_t nc = r == 0 ? m.k : ps->ntot - ps->hi[r - 1];
+  const bool go = !idle && (r == 0 || ps->act[r - 1]) && n > 0 && !(nc <= kFinComps && n <= kFinEdges);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ps->act[r] = go ? 1u : 0u;
+    if (r == 0) {
+      ps->cnt[0] = go ? n : 0u;
+      __hip_atomic_store(m.host, ps->nsurv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+  }
+  if (!go) return;
+  const uint32_t step = gridDim.x * kEdgeThreads;
+  if (blockIdx.x * kEdgeThreads >= n) return;
+  offers_begin(&table);
+  if (r == 0) {
+    for (uint64_t e = blockIdx.x * kEdgeThreads + threadIdx.x; e < n; e += step) {
+      const uint64_t key = m.ekey[e];
+      offers_add(&table, m.c.key, m.eu[e], key);
+      offers_add(&table, m.c.key, m.ev[e], key);
+    }
+    offers_end(&table, m.c.key);
+    return;
+  }
+  const MstList l = mst_list(m, r - 1);
+  uint32_t *du = m.lu[r & 1], *dv = m.lv[r & 1], *de = m.le[r & 1];
+  uint64_t* dk = m.lk[r & 1];
+  for (uint64_t e0 = blockIdx.x * kEdgeThreads; e0 < n; e0 += step) {  // uniform: every thread takes part in block_slot
+    const uint64_t e = e0 + threadIdx.x;
+    uint32_t a = 0, b = 0, x = 0;
+    uint64_t key = 0;
+    if (e < n) {
+      a = m.c.nid[m.c.par[l.u[e]]];
+      b = m.c.nid[m.c.par[l.v[e]]];
+      x = l.x ? l.x[e] : (uint32_t)e;
+      key = l.key[e];
+    }
+    const bool on = a != b;
+    const uint32_t at = block_slot(on, &ps->cnt[r], &red);
+    if (on) {
+      du[at] = a;
+      dv[at] = b;
+      de[at] = x;
+      dk[at] = key;
+      offers_add(&table, m.c.key, a, key);
+      offers_add(&table, m.c.key, b, key);
+    }
+  }
+  offers_end(&table, m.c.key);
+}
+
+// Edges with their component's best key offer their id.
+__global__ __launch_bounds__(kEdgeThreads) void mst_ids(MstDev m, uint32_t r) {
+  if (!m.ps->act[r]) return;
+  const uint32_t step = gridDim.x * kEdgeThreads, tid = blockIdx.x * kEdgeThreads + threadIdx.x, n = m.ps->cnt[r];
+  if (tid == 0) m.ps->hi[r] = m.ps->ntot;
+  const MstList l = mst_list(m, r);
+  for (uint64_t e = tid; e < n; e += step) {
+    const uint32_t a = l.u[e], b = l.v[e];
+    const uint64_t key = l.key[e];
+    const bool wa = m.c.key[a] == key, wb = m.c.key[b] == key;
+    if (wa || wb) {
+      const uint32_t x = l.x ? l.x[e] : (uint32_t)e;
+      const uint64_t id = (uint64_t)m.eu[x] * m.k + m.ev[x];
+      if (wa) atomicMin((unsigned long long*)&m.c.id[a], (unsigned long long)id);
+      if (wb) atomicMin((unsigned long long*)&m.c.id[b], (unsigned long long)id);
+    }
+  }
+}
+
+// Chosen edges hook their components (two that chose the same edge hook once,
+// the larger label onto the smaller) and join the new forest.
+__global__ __launch_bounds__(kEdgeThreads) void mst_hook(MstDev m, uint32_t r) {
+  __shared__ BlockSlots red;
+  if (!m.ps->act[r]) return;
+  const uint32_t step = gridDim.x * kEdgeThreads, n = m.ps->cnt[r];
+  const MstList l = mst_list(m, r);
+  for (uint64_t e0 = blockIdx.x * kEdgeThreads; e0 < n; e0 += step) {
+    const uint64_t e = e0 + threadIdx.x;
+    bool wa = false, wb = false;
+    uint32_t a = 0, b = 0, x = 0, u = 0, v = 0;
+    uint64_t key = 0;
+    if (e < n) {
+      a = l.u[e];
+      b = l.v[e];
+      key = l.key[e];
+      wa = m.c.key[a] == key;
+      wb = m.c.key[b] == key;
+      if (wa || wb) {
+        x = l.x ? l.x[e] : (uint32_t)e;
+        u = m.eu[x];
+        v = m.ev[x];
+        const uint64_t id = (uint64_t)u * m.k + v;
+        wa = wa && m.c.id[a] == id;
+        wb = wb && m.c.id[b] == id;
       }
     }
-    __syncthreads();
-    if (wave < h) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-        take(ck[c], cid[c], cL[c], sk[wave][64 * c + lane], si[wave][64 * c + lane], sL[wave][64 * c + lane]);
-    }
-    __syncthreads();
-  }
-  if (wave == 0) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const uint32_t j = jb + 64u * c + lane;
-      if (!cnew[c]) continue;
-      const uint64_t q = (uint64_t)blockIdx.y * k + j;
-      m.qkey[q] = ck[c];
-      m.qid[q] = cid[c];
-      m.qL[q] = cL[c];
+    if (wa && !(wb && a < b)) m.c.par[a] = b;
+    if (wb && !(wa && b < a)) m.c.par[b] = a;
+    const uint32_t at = block_slot(wa || wb, &m.ps->nnew, &red);
+    if (wa || wb) {
+      m.nu[at] = u;
+      m.nv[at] = v;
+      m.nkey[at] = key;
+      m.nL[at] = m.eL[x];
     }
   }
-}
-
-// Column results and per-round reset: vertex j takes the best of its column
-// partials over the row slices; its forest and component slots are cleared.
-__global__ void mst_col_reduce(MstDev m, uint32_t r0, uint32_t nslice) {
-  if (m.ctl->done) return;
-  const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= m.k) return;
-  uint64_t bk = 0, bi = ~0ull;
-  int32_t bL = 0;
-  if (j > r0)  // a column at or before the tile's first row has no pair in it (and no partials)
-    for (uint32_t y = 0; y < nslice; ++y) {
-      const uint64_t q = (uint64_t)y * m.k + j;
-      take(bk, bi, bL, m.qkey[q], m.qid[q], m.qL[q]);
-    }
-  m.vkey[j] = bk;
-  m.vid[j] = bi;
-  m.vL[j] = bL;
-  m.wkey[j] = 0;
-  m.wid[j] = ~0ull;
-  m.wL[j] = 0;
-  m.ckey[j] = 0;
-  m.cid[j] = ~0ull;
-}
-
-// Row results: tile row i reduces its partials over the blocks that hold a
-// column after it, and merges them into its candidate.
-__global__ __launch_bounds__(64) void mst_row_reduce(MstDev m, uint32_t r0, uint32_t nblk) {
-  if (m.ctl->done) return;
-  const uint32_t i = r0 + blockIdx.x;
-  uint64_t bk = 0, bi = ~0ull;
-  int32_t bL = 0;
-  const uint64_t base = (uint64_t)blockIdx.x * nblk;
-  for (uint32_t b = (i + 1u) / kScanCols + threadIdx.x; b < nblk; b += 64u)
-    take(bk, bi, bL, m.pkey[base + b], m.pid[base + b], m.pL[base + b]);
-  wave_best(bk, bi, bL);
-  if (threadIdx.x == 0) {
-    take(bk, bi, bL, m.vkey[i], m.vid[i], m.vL[i]);
-    m.vkey[i] = bk;
-    m.vid[i] = bi;
-    m.vL[i] = bL;
-  }
-}
-
-// Forest edges: candidates for both ends, gathered in the w* slots in three
-// phases (key, id, LCS).
-__global__ void mst_forest_key(MstDev m) {
-  const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m.ctl->done || e >= m.ctl->nf) return;
-  const uint32_t u = m.fu[e], v = m.fv[e];
-  if (m.comp[u] == m.comp[v]) return;
-  const uint64_t key = sim_key(m.fL[e], m.len[u], m.len[v]);
-  if (key > m.wkey[u]) atomicMax((unsigned long long*)&m.wkey[u], (unsigned long long)key);
-  if (key > m.wkey[v]) atomicMax((unsigned long long*)&m.wkey[v], (unsigned long long)key);
-}
-
-__global__ void mst_forest_id(MstDev m) {
-  const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m.ctl->done || e >= m.ctl->nf) return;
-  const uint32_t u = m.fu[e], v = m.fv[e];
-  if (m.comp[u] == m.comp[v]) return;
-  const uint64_t key = sim_key(m.fL[e], m.len[u], m.len[v]);
-  const uint64_t id = (uint64_t)u * m.k + v;
-  if (m.wkey[u] == key) atomicMin((unsigned long long*)&m.wid[u], (unsigned long long)id);
-  if (m.wkey[v] == key) atomicMin((unsigned long long*)&m.wid[v], (unsigned long long)id);
-}
-
-__global__ void mst_forest_L(MstDev m) {
-  const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m.ctl->done || e >= m.ctl->nf) return;
-  const uint32_t u = m.fu[e], v = m.fv[e];
-  if (m.comp[u] == m.comp[v]) return;
-  const uint64_t id = (uint64_t)u * m.k + v;
-  if (m.wid[u] == id) m.wL[u] = m.fL[e];
-  if (m.wid[v] == id) m.wL[v] = m.fL[e];
-}
-
-// Each vertex's candidate (tile pass results already in v*) takes its forest
-// edge, and offers itself to its component's maximum.  A plain read first
-// skips most atomics: once a component holds a large key few vertices beat it.
-__global__ void mst_vertex_merge(MstDev m) {
-  const uint32_t v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m.ctl->done) return;
-  const bool ok = v < m.k;
-  uint64_t bk = 0;
-  uint32_t c = 0;
-  if (ok) {
-    uint64_t bi = m.vid[v];
-    int32_t bL = m.vL[v];
-    bk = m.vkey[v];
-    if (m.wkey[v]) {
-      take(bk, bi, bL, m.wkey[v], m.wid[v], m.wL[v]);
-      m.vkey[v] = bk;
-      m.vid[v] = bi;
-      m.vL[v] = bL;
-    }
-    c = m.comp[v];
-  }
-  // Late in a tile most vertices share one large component, and their
-  // atomics on its slot would queue up: the lanes of a wave in the
-  // component of its first candidate take their maximum first, and one lane
-  // offers it.  Every lane stays in the wave for the shuffles.
-  const bool cand = ok && bk != 0;
-  const uint64_t candmask = __ballot(cand);
-  if (candmask == 0) return;
-  const int first = __ffsll((unsigned long long)candmask) - 1;
-  const uint32_t lead = (uint32_t)__shfl((int)c, first, 64);
-  uint64_t x = cand && c == lead ? bk : 0;
-#pragma unroll
-  for (int d = 32; d > 0; d >>= 1) {
-    const uint64_t y = __shfl_xor(x, d, 64);
-    x = y > x ? y : x;
-  }
-  if ((int)__lane_id() == first) {
-    uint64_t* slot = &m.ckey[lead];
-    if (x > *slot) atomicMax((unsigned long long*)slot, (unsigned long long)x);
-  }
-  if (cand && c != lead) {
-    uint64_t* slot = &m.ckey[c];
-    if (bk > *slot) atomicMax((unsigned long long*)slot, (unsigned long long)bk);
-  }
-}
-
-__global__ void mst_comp_id(MstDev m) {
-  const uint32_t v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m.ctl->done || v >= m.k || m.vkey[v] == 0) return;
-  const uint32_t c = m.comp[v];
-  if (m.vkey[v] == m.ckey[c]) atomicMin((unsigned long long*)&m.cid[c], (unsigned long long)m.vid[v]);
-}
-
-// Hook every component with an outgoing edge onto the component at its other
-// end.  The one vertex of the component that holds its chosen edge (the
-// candidate key and id equal the component's) does it, so the edge's LCS is
-// at hand.  Two components that chose the same edge hook once: the larger
-// onto the smaller.  Each hook adds its edge to the new forest.
-__global__ void mst_hook(MstDev m) {
-  const uint32_t v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m.ctl->done || v >= m.k) return;
-  const uint64_t key = m.vkey[v];
-  if (key == 0) return;
-  const uint32_t c = m.comp[v];
-  if (key != m.ckey[c] || m.vid[v] != m.cid[c]) return;
-  const uint64_t id = m.cid[c];
-  const uint32_t u = (uint32_t)(id / m.k), w = (uint32_t)(id % m.k);
-  const uint32_t d = m.comp[u] == c ? m.comp[w] : m.comp[u];
-  if (m.cid[d] == id && c < d) return;  // mutual choice: d hooks onto c
-  m.parent[c] = d;
-  const uint32_t slot = atomicAdd(&m.ctl->nnew, 1u);
-  m.nu[slot] = u;
-  m.nv[slot] = w;
-  m.nL[slot] = m.vL[v];
-  atomicAdd(&m.ctl->hooks, 1u);
 }
 
 // Every component follows its hook chain to the root (chains are acyclic:
 // with a strict order on edges the only cycles of chosen edges are the mutual
-// pairs, which hook once).  Concurrent shortcuts by other threads only move
-// entries further up the same chain.
-__global__ void mst_jump(MstDev m) {
-  const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m.ctl->done || c >= m.k) return;
-  uint32_t r = m.parent[c];
-  while (m.parent[r] != r) r = m.parent[r];
-  m.parent[c] = r;
-}
-
-// Relabel every vertex; the first thread also ends the round: a round
-// without hooks finishes the tile (its relabelling changes nothing, so blocks
-// that see the flag early lose nothing).
-__global__ void mst_relabel(MstDev m) {
-  const uint32_t v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m.ctl->done || v >= m.k) return;
-  m.comp[v] = m.parent[m.comp[v]];
-  if (v == 0) {
-    if (m.ctl->hooks == 0) {
-      m.ctl->done = 1;
-    } else {
-      m.ctl->rounds += 1;
-      m.ctl->hooks = 0;
+// pairs, which hook once; concurrent shortcuts by other threads only move
+// entries further up the same chain), and roots get the next round's labels.
+// A component without an outgoing edge keeps its label for good.
+__global__ __launch_bounds__(kEdgeThreads) void mst_roots(MstDev m, uint32_t r) {
+  __shared__ BlockSlots red;
+  MstPass* ps = m.ps;
+  if (!ps->act[r] || ps->cnt[r] == 0) return;
+  const uint32_t lo = r == 0 ? 0u : ps->hi[r - 1], hi = ps->hi[r];
+  const uint32_t step = gridDim.x * kEdgeThreads;
+  for (uint64_t c0 = lo + (uint64_t)blockIdx.x * kEdgeThreads; c0 < hi; c0 += step) {
+    const uint64_t c = c0 + threadIdx.x;
+    bool isroot = false;
+    if (c < hi) {
+      if (m.c.key[c] == 0) {
+        m.c.nid[c] = (uint32_t)c;
+      } else {
+        uint32_t x = m.c.par[c];
+        while (m.c.par[x] != x) x = m.c.par[x];
+        m.c.par[c] = x;
+        isroot = x == (uint32_t)c;
+      }
     }
+    const uint32_t at = block_slot(isroot, &ps->ntot, &red);
+    if (isroot) m.c.nid[c] = at;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ps->levels = r + 1;
+    m.ctl->rounds += 1;
   }
 }
 
-// The new forest becomes the current one (the host swaps the arrays).
-__global__ void mst_tile_end(MstDev m) {
-  if (threadIdx.x != 0) return;
-  m.ctl->nf = m.ctl->nnew;
-  m.ctl->nnew = 0;
+// The rounds that are left, in one workgroup: the same steps with the
+// components' slots in LDS (24 bytes each) and barriers between them, so a
+// round costs a few microseconds instead of four launches.  Fewer than half
+// of the components are left after a round, so after ceil(log2(k / kFinComps))
+// rounds on the whole GPU they always fit.
+__global__ __launch_bounds__(kFinThreads) void mst_finish(MstDev m, uint32_t queued) {
+  extern __shared__ uint64_t mst_lds[];
+  uint64_t* skey = mst_lds;
+  uint64_t* sid = skey + kFinComps;
+  uint32_t* spar = reinterpret_cast<uint32_t*>(sid + kFinComps);
+  uint32_t* sup = spar + kFinComps;
+  __shared__ uint32_t s_cnt, s_new, s_forest;
+  MstPass* ps = m.ps;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u;
+  if (tid == 0 && queued == 0) __hip_atomic_store(m.host, ps->nsurv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (mst_idle(m)) return;
+  uint32_t r = 0;
+  while (r < queued && ps->act[r]) ++r;
+  uint32_t n = r == 0 ? m.ctl->nf + ps->nsurv : ps->cnt[r - 1];
+  uint32_t lo = r == 0 ? 0u : ps->hi[r - 1], tot = ps->ntot, nc = tot - lo, levels = ps->levels;
+  if (n == 0 || nc > kFinComps) return;  // (never more: see above)
+  MstList l = mst_list(m, r == 0 ? 0 : r - 1);
+  if (tid == 0) s_forest = ps->nnew;
+  uint32_t to = r & 1;
+  const uint32_t levels0 = levels;
+  for (bool begin = true;; begin = false) {
+    for (uint32_t c = tid; c < nc; c += kFinThreads) {
+      skey[c] = 0;
+      sid[c] = ~0ull;
+      spar[c] = c;
+    }
+    if (tid == 0) s_cnt = 0;
+    __syncthreads();
+    uint32_t *du = m.lu[to], *dv = m.lv[to], *de = m.le[to];
+    uint64_t* dk = m.lk[to];
+    // four edges a thread at a time, their loads in flight together
+    for (uint32_t e0 = tid; e0 - lane < n; e0 += 4 * kFinThreads) {
+      uint32_t a[4], b[4], x[4];
+      uint64_t key[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint32_t e = min(e0 + q * kFinThreads, n - 1u);
+        a[q] = l.u[e];
+        b[q] = l.v[e];
+        x[q] = l.x ? l.x[e] : e;
+        key[q] = l.key[e];
+      }
+      if (!begin) {  // labels within the last round's components
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          a[q] = sup[a[q]];
+          b[q] = sup[b[q]];
+        }
+      } else if (r > 0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          a[q] = m.c.par[a[q]];
+          b[q] = m.c.par[b[q]];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          a[q] = m.c.nid[a[q]] - lo;
+          b[q] = m.c.nid[b[q]] - lo;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const bool on = e0 + q * kFinThreads < n && a[q] != b[q];
+        const uint32_t at = wave_slot(on, &s_cnt);
+        if (on) {
+          du[at] = a[q];
+          dv[at] = b[q];
+          de[at] = x[q];
+          dk[at] = key[q];
+          offer(&skey[a[q]], key[q]);
+          offer(&skey[b[q]], key[q]);
+        }
+      }
+    }
+    __threadfence_block();
+    __syncthreads();
+    n = s_cnt;
+    if (n == 0) break;
+    l = MstList{du, dv, de, dk};
+    to ^= 1u;
+    for (uint32_t e0 = tid; e0 < n; e0 += 4 * kFinThreads) {
+      uint32_t a[4], b[4];
+      uint64_t key[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint32_t e = min(e0 + q * kFinThreads, n - 1u);  // a repeated edge offers the same id again
+        a[q] = l.u[e];
+        b[q] = l.v[e];
+        key[q] = l.key[e];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const bool wa = skey[a[q]] == key[q], wb = skey[b[q]] == key[q];
+        if (wa || wb) {
+          const uint32_t x = l.x[min(e0 + q * kFinThreads, n - 1u)];
+          const uint64_t id = (uint64_t)m.eu[x] * m.k + m.ev[x];
+          if (wa) atomicMin((unsigned long long*)&sid[a[q]], (unsigned long long)id);
+          if (wb) atomicMin((unsigned long long*)&sid[b[q]], (unsigned long long)id);
+        }
+      }
+    }
+    if (tid == 0) s_new = 0;
+    __syncthreads();
+    for (uint32_t e0 = tid; e0 - lane < n; e0 += 4 * kFinThreads) {
+      uint32_t a[4], b[4];
+      uint64_t key[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint32_t e = min(e0 + q * kFinThreads, n - 1u);
+        a[q] = l.u[e];
+        b[q] = l.v[e];
+        key[q] = l.key[e];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint32_t e = e0 + q * kFinThreads;
+        bool wa = e < n && skey[a[q]] == key[q], wb = e < n && skey[b[q]] == key[q];
+        uint32_t x = 0, u = 0, v = 0;
+        if (wa || wb) {
+          x = l.x[e];
+          u = m.eu[x];
+          v = m.ev[x];
+          const uint64_t id = (uint64_t)u * m.k + v;
+          wa = wa && sid[a[q]] == id;
+          wb = wb && sid[b[q]] == id;
+        }
+        if (wa && !(wb && a[q] < b[q])) spar[a[q]] = b[q];
+        if (wb && !(wa && b[q] < a[q])) spar[b[q]] = a[q];
+        const uint32_t at = wave_slot(wa || wb, &s_forest);
+        if (wa || wb) {
+          m.nu[at] = u;
+          m.nv[at] = v;
+          m.nkey[at] = key[q];
+          m.nL[at] = m.eL[x];
+        }
+      }
+    }
+    __syncthreads();
+    for (uint32_t c = tid; c < nc; c += kFinThreads) {
+      uint32_t x = spar[c];
+      while (spar[x] != x) x = spar[x];
+      sup[c] = x;
+      m.c.key[lo + c] = skey[c];
+      m.c.id[lo + c] = sid[c];
+      m.c.par[lo + c] = lo + x;
+    }
+    __syncthreads();
+    for (uint32_t c0 = tid & ~63u; c0 < nc; c0 += kFinThreads) {
+      const uint32_t c = c0 + lane;
+      const bool live = c < nc && skey[c] != 0;
+      const bool isroot = live && sup[c] == c;
+      const uint32_t at = wave_slot(isroot, &s_new);
+      if (c < nc && !live) m.c.nid[lo + c] = lo + c;
+      if (isroot) {
+        m.c.nid[lo + c] = tot + at;
+        spar[c] = at;
+      }
+    }
+    __syncthreads();
+    for (uint32_t c = tid; c < nc; c += kFinThreads)
+      if (skey[c] != 0) sup[c] = spar[sup[c]];  // (a component without an edge has no edges to relabel)
+    lo = tot;
+    nc = s_new;
+    tot += nc;
+    ++levels;
+    __syncthreads();  // s_new and the slots are reused by the next round
+  }
+  if (tid == 0) {
+    ps->levels = levels;
+    ps->ntot = tot;
+    ps->nnew = s_forest;
+    m.ctl->rounds += levels - levels0;
+  }
+}
+
+// The hierarchy of this update, per vertex, for the next pass; the new forest
+// becomes the current one, and the next update's components and counters are
+// cleared.  `init`: no forest yet, every vertex by itself.
+__global__ __launch_bounds__(256) void mst_view(MstDev m, uint32_t init) {
+  mst_clear(m.next, m.ps_next, m.k);
+  const uint32_t step = gridDim.x * blockDim.x, tid = blockIdx.x * blockDim.x + threadIdx.x;
+  if (init && tid == 0) {
+    m.ctl->nf = 0;
+    m.ctl->rounds = 0;
+  }
+  if (!init && mst_idle(m)) return;
+  const uint32_t D = init ? 0u : m.ps->levels, nnew = init ? 0u : m.ps->nnew;
+  for (uint64_t v = tid; v < m.k; v += step) {
+    MstView& w = m.view[v];
+    MstExact& x = m.exact[v];
+    uint32_t c = (uint32_t)v;
+    uint64_t key = ~0ull, id = 0;  // nothing chosen yet
+    for (uint32_t s = D; s < kMstSlots; ++s) {  // round 0 and the slots past it
+      w.label[s] = (uint32_t)v;
+      w.bound[s] = -1.0f;
+    }
+    for (uint32_t l = 1; l <= D; ++l) {
+      const uint64_t ck = m.c.key[c];
+      if (ck != 0) {
+        const uint64_t ci = m.c.id[c];
+        if (better(key, id, ck, ci)) {
+          key = ck;
+          id = ci;
+        }
+        c = m.c.nid[m.c.par[c]];
+      }
+      const uint32_t s = D - l;
+      if (s < kMstSlots) {
+        w.label[s] = c;
+        w.bound[s] = (float)(__longlong_as_double((long long)(key - 1ull)) * (1.0 - 0x1p-20));
+        x.key[s] = key;
+        x.id[s] = id;
+      }
+    }
+  }
+  for (uint64_t e = tid; e < nnew; e += step) {
+    m.eu[e] = m.nu[e];
+    m.ev[e] = m.nv[e];
+    m.ekey[e] = m.nkey[e];
+    m.eL[e] = m.nL[e];
+  }
+  if (!init && tid == 0) m.ctl->nf = nnew;
 }
 
 }  // namespace famsa
@@ -462,132 +777,190 @@ using namespace famsa;
 struct famsa_mst_s {
   uint32_t k = 0;
   int device = 0;
-  DevMem len, comp, parent, vkey, vid, vL, wkey, wid, wL, ckey, cid, pkey, pid, pL, qkey, qid, qL;
-  DevMem fu, fv, fL, nu, nv, nL, ctl;
-  uint64_t part_cap = 0;   // row partials the p* arrays hold
-  uint32_t slice_cap = 0;  // row slices the q* arrays hold
-  PinMem hctl;
+  uint32_t surv_cap = 0;       // survivors an update holds: at least eight rows' pairs
+  uint32_t cover = 0xFFFFFFFFu;  // the forest joins all vertices from this one on
+  DevMem mem;                  // every array below, in one allocation
+  MstDev dev{};
+  PinMem hflag;
   uint64_t tiles = 0;
   // Tiles arrive on whatever stream their producer used (a plan alternates
   // two); this event marks the end of the last tile's work, and the next
   // tile's work waits for it, so merges never overlap whatever the streams.
   hipEvent_t last = nullptr;
+  hipEvent_t read = nullptr;  // a pass over the tile and its survivors' count are done
   bool has_last = false;
   ~famsa_mst_s() {
     if (last) {
       if (has_last) (void)hipEventSynchronize(last);
       (void)hipEventDestroy(last);
     }
+    if (read) (void)hipEventDestroy(read);
   }
   int wait_last() const {
     if (has_last) FAMSA_HIP(hipEventSynchronize(last));
     return 0;
   }
-  MstDev view() {
-    MstDev m;
-    m.len = len.as<uint32_t>();
-    m.k = k;
-    m.comp = comp.as<uint32_t>();
-    m.parent = parent.as<uint32_t>();
-    m.vkey = vkey.as<uint64_t>();
-    m.vid = vid.as<uint64_t>();
-    m.vL = vL.as<int32_t>();
-    m.wkey = wkey.as<uint64_t>();
-    m.wid = wid.as<uint64_t>();
-    m.wL = wL.as<int32_t>();
-    m.ckey = ckey.as<uint64_t>();
-    m.cid = cid.as<uint64_t>();
-    m.pkey = pkey.as<uint64_t>();
-    m.pid = pid.as<uint64_t>();
-    m.pL = pL.as<int32_t>();
-    m.qkey = qkey.as<uint64_t>();
-    m.qid = qid.as<uint64_t>();
-    m.qL = qL.as<int32_t>();
-    m.fu = fu.as<uint32_t>();
-    m.fv = fv.as<uint32_t>();
-    m.fL = fL.as<int32_t>();
-    m.nu = nu.as<uint32_t>();
-    m.nv = nv.as<uint32_t>();
-    m.nL = nL.as<int32_t>();
-    m.ctl = ctl.as<MstDev::Ctl>();
-    return m;
-  }
+  int layout();
+  struct Rows {  // rows t0..t1-1 of stride `stride` in a tile; skip: every eighth left out
+    uint32_t t0, t1, stride, skip;
+  };
+  int update(const famsa_lcs_tile* t, const Rows& rows, bool dense, hipStream_t s, bool* fits);
   int merge_tile(const famsa_lcs_tile* t, hipStream_t s);
-  int read_ctl(MstDev::Ctl* out, hipStream_t s);
 };
 
-static inline dim3 grid_for(uint64_t n, uint32_t b = 256) { return dim3((uint32_t)std::max<uint64_t>(1, (n + b - 1) / b)); }
-
-int famsa_mst_s::read_ctl(MstDev::Ctl* out, hipStream_t s) {
-  FAMSA_HIP(hipMemcpyAsync(hctl.p, ctl.p, sizeof(MstDev::Ctl), hipMemcpyDeviceToHost, s));
-  FAMSA_HIP(hipStreamSynchronize(s));
-  memcpy(out, hctl.p, sizeof(MstDev::Ctl));
+// One allocation: about 1 KB a vertex, most of it room for survivors.
+int famsa_mst_s::layout() {
+  const uint64_t n = std::max<uint32_t>(k, 1);
+  const uint64_t pairs = n * (n - 1) / 2;
+  const uint64_t room = k <= (1u << 20) ? 14 * n + std::min<uint64_t>(16 * n, 1u << 17) : n + (8u << 20);
+  surv_cap = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>({pairs, room, 0xFFFFFFF0ull - n}));
+  const uint64_t E = n + surv_cap;
+  uint64_t off = 0;
+  auto part = [&](uint64_t bytes) {
+    const uint64_t at = off;
+    off += (bytes + 255) & ~255ull;
+    return at;
+  };
+  const uint64_t o_len = part(4 * n), o_ctl = part(sizeof(MstCtl)), o_eu = part(4 * E), o_ev = part(4 * E),
+                 o_ek = part(8 * E), o_eL = part(4 * E), o_nu = part(4 * n), o_nv = part(4 * n), o_nk = part(8 * n),
+                 o_nL = part(4 * n), o_lk = part(16 * E), o_l = part(24 * E), o_ck = part(32 * n),
+                 o_ci = part(32 * n), o_pa = part(16 * n), o_ni = part(16 * n), o_ps = part(2 * sizeof(MstPass)), o_vw = part(sizeof(MstView) * n), o_ex = part(sizeof(MstExact) * n);
+  int rc = mem.alloc(off);
+  if (rc) return rc;
+  if ((rc = hflag.alloc(64))) return rc;
+  uint8_t* b = mem.as<uint8_t>();
+  MstDev& d = dev;
+  d.k = k;
+  d.room = surv_cap;
+  d.len = reinterpret_cast<uint32_t*>(b + o_len);
+  d.ctl = reinterpret_cast<MstCtl*>(b + o_ctl);
+  d.eu = reinterpret_cast<uint32_t*>(b + o_eu);
+  d.ev = reinterpret_cast<uint32_t*>(b + o_ev);
+  d.ekey = reinterpret_cast<uint64_t*>(b + o_ek);
+  d.eL = reinterpret_cast<int32_t*>(b + o_eL);
+  d.nu = reinterpret_cast<uint32_t*>(b + o_nu);
+  d.nv = reinterpret_cast<uint32_t*>(b + o_nv);
+  d.nkey = reinterpret_cast<uint64_t*>(b + o_nk);
+  d.nL = reinterpret_cast<int32_t*>(b + o_nL);
+  for (int i = 0; i < 2; ++i) {
+    uint32_t* l = reinterpret_cast<uint32_t*>(b + o_l) + 3 * E * i;
+    d.lu[i] = l;
+    d.lv[i] = l + E;
+    d.le[i] = l + 2 * E;
+    d.lk[i] = reinterpret_cast<uint64_t*>(b + o_lk) + E * i;
+    (i ? d.next : d.c) = MstComp{reinterpret_cast<uint64_t*>(b + o_ck) + 2 * n * i,
+                                 reinterpret_cast<uint64_t*>(b + o_ci) + 2 * n * i,
+                                 reinterpret_cast<uint32_t*>(b + o_pa) + 2 * n * i,
+                                 reinterpret_cast<uint32_t*>(b + o_ni) + 2 * n * i};
+    (i ? d.ps_next : d.ps) = reinterpret_cast<MstPass*>(b + o_ps) + i;
+  }
+  d.view = reinterpret_cast<MstView*>(b + o_vw);
+  d.exact = reinterpret_cast<MstExact*>(b + o_ex);
+  d.host = hflag.as<uint32_t>();
   return 0;
 }
 
-// Boruvka rounds are queued in batches without waiting: every kernel of a
-// round after the last useful one returns at once (the `done` flag), so the
-// host only checks after each batch.  Borůvka needs at most ceil(log2 k) + 1
-// rounds, and few tiles need more than the first batch.
-int famsa_mst_s::merge_tile(const famsa_lcs_tile* t, hipStream_t s) {
+static inline uint32_t grid_for(uint64_t n, uint32_t threads) {
+  return (uint32_t)std::min<uint64_t>(512, std::max<uint64_t>(1, (n + threads - 1) / threads));
+}
+
+// One update of the forest from some of the tile's rows.  The launches are
+// queued without waiting (kernels of rounds that are not needed return at
+// once); the host waits for the pass over the tile alone.  *fits: the
+// survivors fitted; else the forest is as it was.
+int famsa_mst_s::update(const famsa_lcs_tile* t, const Rows& rows, bool dense, hipStream_t s, bool* fits) {
   const uint32_t r0 = t->row_begin, r1 = t->row_end;
-  const bool has_tile = t->count && r1 > r0;
-  if (r1 - r0 > 65535u) return set_error(FAMSA_LCS_EINVAL, "tiles of more than 65535 rows are not supported");
-  if (has_last) FAMSA_HIP(hipStreamWaitEvent(s, last, 0));  // the previous tile's merge, on any stream
-  const uint32_t nblk = (uint32_t)((k + kScanCols - 1) / kScanCols);
-  const uint32_t nslice = has_tile ? (r1 - r0 + kScanSlice - 1) / kScanSlice : 0;
-  if (has_tile && ((uint64_t)nblk * (r1 - r0) > part_cap || nslice > slice_cap)) {
-    FAMSA_HIP(hipStreamSynchronize(s));  // the old partials may still be in use
-    int rc;
-    if ((uint64_t)nblk * (r1 - r0) > part_cap) {
-      part_cap = (uint64_t)nblk * (r1 - r0);
-      if ((rc = pkey.alloc(part_cap * 8)) || (rc = pid.alloc(part_cap * 8)) || (rc = pL.alloc(part_cap * 4))) return rc;
-    }
-    if (nslice > slice_cap) {
-      slice_cap = nslice;
-      const uint64_t n = (uint64_t)slice_cap * k;
-      if ((rc = qkey.alloc(n * 8)) || (rc = qid.alloc(n * 8)) || (rc = qL.alloc(n * 4))) return rc;
-    }
+  // this update's components and counters were cleared by the one before
+  std::swap(dev.c, dev.next);
+  std::swap(dev.ps, dev.ps_next);
+  const MstDev& m = dev;
+  const uint32_t nrows = rows.t1 - rows.t0;
+  const uint64_t most = std::min<uint64_t>((uint64_t)nrows * (k - 1), surv_cap) + k;  // edges, at most
+  uint32_t rounds = 0;  // on the whole GPU
+  while ((k >> rounds) >= kFinComps && rounds < 32) ++rounds;  // then fewer than kFinComps are left
+  if (k <= kFinComps) rounds = 0;
+  if (dense && most > kFinEdges) rounds += 2;
+  // blocks of 128 columns; a slice of rows so that about 256 blocks share the
+  // tile (the survivors' appends are one atomic a block), 64 rows at least:
+  // four for each wave
+  const uint32_t j0 = (uint32_t)((r0 + (uint64_t)rows.t0 * rows.stride + 1ull) & ~63ull);
+  const uint32_t strips = (k - j0 + 64u * kFiltCols - 1u) / (64u * kFiltCols);
+  const uint32_t per = kFiltWaves * kFiltChunk;
+  const uint32_t want = std::max(1u, 256u / strips);
+  const uint32_t slice = (std::max(1u, (nrows + want - 1) / want) + per - 1) / per * per;
+  const dim3 ge(grid_for(most, kEdgeThreads)), gc(grid_for(k, kEdgeThreads)), b(kEdgeThreads);
+  hipLaunchKernelGGL(mst_filter, dim3(strips, (nrows + slice - 1) / slice), dim3(64 * kFiltWaves), 0, s, m, m.view,
+                     m.len, t->lcs, r0, r1, rows.t0, rows.t1, slice, rows.stride, rows.skip, j0);
+  for (uint32_t r = 0; r < rounds; ++r) {
+    hipLaunchKernelGGL(mst_edges, ge, b, 0, s, m, r);
+    if (r == 0) FAMSA_HIP(hipEventRecord(read, s));
+    hipLaunchKernelGGL(mst_ids, ge, b, 0, s, m, r);
+    hipLaunchKernelGGL(mst_hook, ge, b, 0, s, m, r);
+    hipLaunchKernelGGL(mst_roots, gc, b, 0, s, m, r);
   }
-  const MstDev m = view();
-  const dim3 gk = grid_for(k);
-  // first column block holding a column after row r0 (has_tile: r0 + 1 < k, so bx0 < nblk)
-  const uint32_t bx0 = (uint32_t)((r0 + 1ull) / kScanCols);
-  hipLaunchKernelGGL(mst_tile_begin, gk, dim3(256), 0, s, m);
-  const uint32_t kmax_rounds = 2 + (uint32_t)ceil(log2((double)std::max<uint32_t>(k, 2)));
-  uint32_t queued = 0;
-  for (uint32_t batch = 6;; batch = 2) {
-    for (uint32_t r = 0; r < batch; ++r) {
-      const uint32_t first = queued == 0 && r == 0;  // the tile's first round computes every partial
-      if (has_tile)
-        hipLaunchKernelGGL(mst_scan, dim3(nblk - bx0, nslice), dim3(64 * kScanWaves), 0, s, m, t->lcs, r0, r1, nblk,
-                           bx0, first);
-      hipLaunchKernelGGL(mst_col_reduce, gk, dim3(256), 0, s, m, r0, nslice);
-      if (has_tile) hipLaunchKernelGGL(mst_row_reduce, dim3(r1 - r0), dim3(64), 0, s, m, r0, nblk);
-      hipLaunchKernelGGL(mst_forest_key, gk, dim3(256), 0, s, m);
-      hipLaunchKernelGGL(mst_forest_id, gk, dim3(256), 0, s, m);
-      hipLaunchKernelGGL(mst_forest_L, gk, dim3(256), 0, s, m);
-      hipLaunchKernelGGL(mst_vertex_merge, gk, dim3(256), 0, s, m);
-      hipLaunchKernelGGL(mst_comp_id, gk, dim3(256), 0, s, m);
-      hipLaunchKernelGGL(mst_hook, gk, dim3(256), 0, s, m);
-      hipLaunchKernelGGL(mst_jump, gk, dim3(256), 0, s, m);
-      hipLaunchKernelGGL(mst_relabel, gk, dim3(256), 0, s, m);
-      FAMSA_HIP(hipGetLastError());
-    }
-    queued += batch;
-    MstDev::Ctl c;
-    int rc = read_ctl(&c, s);
-    if (rc) return rc;
-    if (c.done) break;
-    if (queued > kmax_rounds) return set_error(FAMSA_LCS_EDEVICE, "spanning forest did not converge in %u rounds", queued);
-  }
-  hipLaunchKernelGGL(mst_tile_end, dim3(1), dim3(64), 0, s, m);
+  hipLaunchKernelGGL(mst_finish, dim3(1), dim3(kFinThreads), kFinLds, s, m, rounds);
+  if (rounds == 0) FAMSA_HIP(hipEventRecord(read, s));
+  hipLaunchKernelGGL(mst_view, dim3(grid_for(2ull * k, 256)), dim3(256), 0, s, m, 0u);
   FAMSA_HIP(hipGetLastError());
   FAMSA_HIP(hipEventRecord(last, s));
   has_last = true;
-  std::swap(fu.p, nu.p);
-  std::swap(fv.p, nv.p);
-  std::swap(fL.p, nL.p);
+  FAMSA_HIP(hipEventSynchronize(read));
+  *fits = *static_cast<volatile uint32_t*>(hflag.p) <= surv_cap;
+  return 0;
+}
+
+// Most tiles are one update.  Where the forest does not join the tile's
+// vertices yet (the first tile; every tile in descending order), or the
+// survivors of a whole tile do not fit, the rows are taken in passes of
+// growing size spread over the tile, every 8^n-th row first: a pass of eight
+// rows always fits, and each pass's forest then drops most pairs of the next
+// (a row seldom beats eight times as many like it).  A pass whose survivors
+// do not fit is halved.
+int famsa_mst_s::merge_tile(const famsa_lcs_tile* t, hipStream_t s) {
+  const uint32_t r0 = t->row_begin, r1 = t->row_end;
+  if (r1 - r0 > 65535u) return set_error(FAMSA_LCS_EINVAL, "tiles of more than 65535 rows are not supported");
+  if (!t->count) {
+    ++tiles;
+    return 0;
+  }
+  if (has_last) FAMSA_HIP(hipStreamWaitEvent(s, last, 0));  // the previous tile's merge, on any stream
+  const uint32_t R = std::min(r1, k - 1) - r0;  // rows with a pair
+  const bool covered = r0 >= cover;
+  std::vector<Rows> todo;  // last first
+  auto passes = [&]() {
+    uint32_t st = 1;
+    while ((R + st - 1) / st > 8) st *= 8;
+    std::vector<Rows> p;
+    for (uint32_t skip = 0;; skip = 1, st /= 8) {
+      p.push_back(Rows{0, (R + st - 1) / st, st, skip});
+      if (st == 1) break;
+    }
+    todo.insert(todo.end(), p.rbegin(), p.rend());
+  };
+  if (covered || t->count <= surv_cap) todo.push_back(Rows{0, R, 1, 0});
+  else passes();
+  while (!todo.empty()) {
+    const Rows rows = todo.back();
+    todo.pop_back();
+    const uint32_t mid = rows.t0 + (rows.t1 - rows.t0) / 2;
+    if ((uint64_t)(rows.t1 - rows.t0) * k > 0xFFFFFFFFull && mid > rows.t0) {  // survivors are counted in 32 bits
+      todo.push_back(Rows{mid, rows.t1, rows.stride, rows.skip});
+      todo.push_back(Rows{rows.t0, mid, rows.stride, rows.skip});
+      continue;
+    }
+    bool fits = false;
+    const int rc = update(t, rows, !covered, s, &fits);
+    if (rc) return rc;
+    if (fits) continue;
+    if (rows.t1 - rows.t0 <= 1) return set_error(FAMSA_LCS_EDEVICE, "one row's pairs do not fit");
+    if (rows.stride == 1 && rows.skip == 0 && rows.t0 == 0 && rows.t1 == R && R > 8) {
+      passes();
+    } else {
+      todo.push_back(Rows{mid, rows.t1, rows.stride, rows.skip});
+      todo.push_back(Rows{rows.t0, mid, rows.stride, rows.skip});
+    }
+  }
+  cover = std::min(cover, r0);
   ++tiles;
   return 0;
 }
@@ -615,25 +988,31 @@ int famsa_mst_create(const uint32_t* lengths, uint32_t k, int device, famsa_mst_
   if (!m) return set_error(FAMSA_LCS_ENOMEM, "out of host memory");
   m->k = k;
   m->device = device;
-  const size_t n = std::max<uint32_t>(k, 1);
-  int rc;
-  if ((rc = m->len.alloc(n * 4)) || (rc = m->comp.alloc(n * 4)) || (rc = m->parent.alloc(n * 4)) ||
-      (rc = m->vkey.alloc(n * 8)) || (rc = m->vid.alloc(n * 8)) || (rc = m->vL.alloc(n * 4)) ||
-      (rc = m->wkey.alloc(n * 8)) || (rc = m->wid.alloc(n * 8)) || (rc = m->wL.alloc(n * 4)) ||
-      (rc = m->ckey.alloc(n * 8)) || (rc = m->cid.alloc(n * 8)) ||
-      (rc = m->fu.alloc(n * 4)) || (rc = m->fv.alloc(n * 4)) || (rc = m->fL.alloc(n * 4)) ||
-      (rc = m->nu.alloc(n * 4)) || (rc = m->nv.alloc(n * 4)) || (rc = m->nL.alloc(n * 4)) ||
-      (rc = m->ctl.alloc(sizeof(MstDev::Ctl))) || (rc = m->hctl.alloc(sizeof(MstDev::Ctl)))) {
+  int rc = m->layout();
+  if (rc) {
     delete m;
     return rc;
   }
-  if (hipEventCreateWithFlags(&m->last, hipEventDisableTiming) != hipSuccess) {
-    m->last = nullptr;
+  hipStream_t st = nullptr;
+  if ((rc = lib_stream(device, 0, &st))) {
     delete m;
-    return set_error(FAMSA_LCS_EDEVICE, "hipEventCreate failed");
+    return rc;
   }
-  if ((k && hipMemcpy(m->len.p, lengths, (size_t)k * 4, hipMemcpyHostToDevice) != hipSuccess) ||
-      hipMemset(m->ctl.p, 0, sizeof(MstDev::Ctl)) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+  if (hipEventCreateWithFlags(&m->last, hipEventDisableTiming) != hipSuccess ||
+      hipEventCreateWithFlags(&m->read, hipEventDisableTiming) != hipSuccess ||
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&mst_finish), hipFuncAttributeMaxDynamicSharedMemorySize,
+                          (int)kFinLds) != hipSuccess) {
+    delete m;
+    return set_error(FAMSA_LCS_EDEVICE, "setting up the forest failed");
+  }
+  if ((k && hipMemcpyAsync(const_cast<uint32_t*>(m->dev.len), lengths, (size_t)k * 4, hipMemcpyHostToDevice, st) !=
+                hipSuccess)) {
+    delete m;
+    return set_error(FAMSA_LCS_EDEVICE, "initialising the forest failed");
+  }
+  hipLaunchKernelGGL(mst_view, dim3(grid_for(2ull * k, 256)), dim3(256), 0, st, m->dev, 1u);
+  // the lengths are the caller's: wait for their copy
+  if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
     delete m;
     return set_error(FAMSA_LCS_EDEVICE, "initialising the forest failed");
   }
@@ -658,17 +1037,17 @@ int famsa_mst_result(const famsa_mst_t* m, uint32_t* u, uint32_t* v, int64_t* lc
   FAMSA_HIP(hipSetDevice(m->device));
   int rc = m->wait_last();
   if (rc) return rc;
-  MstDev::Ctl c;
-  FAMSA_HIP(hipMemcpy(&c, m->ctl.p, sizeof c, hipMemcpyDeviceToHost));
+  MstCtl c;
+  FAMSA_HIP(hipMemcpy(&c, m->dev.ctl, sizeof c, hipMemcpyDeviceToHost));
   const uint32_t n = c.nf;
   std::vector<uint32_t> hu(n), hv(n), hl(m->k);
   std::vector<int32_t> hL(n);
   if (n) {
-    FAMSA_HIP(hipMemcpy(hu.data(), m->fu.p, n * 4, hipMemcpyDeviceToHost));
-    FAMSA_HIP(hipMemcpy(hv.data(), m->fv.p, n * 4, hipMemcpyDeviceToHost));
-    FAMSA_HIP(hipMemcpy(hL.data(), m->fL.p, n * 4, hipMemcpyDeviceToHost));
+    FAMSA_HIP(hipMemcpy(hu.data(), m->dev.eu, n * 4, hipMemcpyDeviceToHost));
+    FAMSA_HIP(hipMemcpy(hv.data(), m->dev.ev, n * 4, hipMemcpyDeviceToHost));
+    FAMSA_HIP(hipMemcpy(hL.data(), m->dev.eL, n * 4, hipMemcpyDeviceToHost));
   }
-  if (m->k) FAMSA_HIP(hipMemcpy(hl.data(), m->len.p, (size_t)m->k * 4, hipMemcpyDeviceToHost));
+  if (m->k) FAMSA_HIP(hipMemcpy(hl.data(), m->dev.len, (size_t)m->k * 4, hipMemcpyDeviceToHost));
   for (uint32_t e = 0; e < n; ++e) {
     if (u) u[e] = hu[e];
     if (v) v[e] = hv[e];
@@ -699,8 +1078,8 @@ int famsa_mst_get_stats(const famsa_mst_t* m, uint64_t* tiles, uint64_t* rounds)
   FAMSA_HIP(hipSetDevice(m->device));
   int rc = m->wait_last();
   if (rc) return rc;
-  MstDev::Ctl c;
-  FAMSA_HIP(hipMemcpy(&c, m->ctl.p, sizeof c, hipMemcpyDeviceToHost));
+  MstCtl c;
+  FAMSA_HIP(hipMemcpy(&c, m->dev.ctl, sizeof c, hipMemcpyDeviceToHost));
   if (tiles) *tiles = m->tiles;
   if (rounds) *rounds = c.rounds;
   return 0;
