@@ -93,6 +93,45 @@ __device__ __forceinline__ uint32_t lds_byte(uint32_t q, uint32_t c, uint32_t la
   return q * (SIG * 1024u) + c * 1024u + lane * 16u;
 }
 
+// Masks of a row from dword w on, zero from dword `end` (at most the row's
+// W_s) on: one 16-byte load at a 4-byte alignment.  Past the row's last dword
+// it reads up to three dwords of what follows (the next code's masks, or the
+// 16 bytes kept behind the last sequence's).
+typedef uint32_t quad_at_dword __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ uint4 mask_quad(const uint32_t* __restrict__ row, uint32_t w, uint32_t end) {
+  const quad_at_dword v = *reinterpret_cast<const quad_at_dword*>(row + (w < end ? w : 0u));
+  return make_uint4(w < end ? v.x : 0u, w + 1 < end ? v.y : 0u, w + 2 < end ? v.z : 0u, w + 3 < end ? v.w : 0u);
+}
+
+// Quads [0, Q) x codes [0, sigma) of a group's masks into the LDS table, by
+// all waves; a lane's row starts at dword w0 and ends at `end` of a row whose
+// code c begins at src + c Ws.  Every lane has a readable `src`.  Four loads
+// of a wave are in flight together: they are scattered (a row a lane), and
+// one at a time with four guarded dwords each took 10 to 20 us an item.
+template <int PLANES>
+__device__ __forceinline__ void stage_masks(const uint32_t* __restrict__ src, uint32_t Ws, uint32_t w0, uint32_t end,
+                                            uint32_t Q, uint32_t sigma, char* __restrict__ lds) {
+  const uint32_t lane = threadIdx.x & 63u, nwaves = blockDim.x >> 6;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // q and c on the scalar unit
+  const uint32_t n = Q * sigma;
+  for (uint32_t e0 = wave; e0 < n; e0 += 4 * nwaves) {
+    uint4 v[4];
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u) {
+      const uint32_t e = min(e0 + u * nwaves, n - 1u), q = e / sigma, c = e - q * sigma;
+      v[u] = mask_quad(src + (uint64_t)c * Ws, w0 + 4u * q, end);
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u) {
+      const uint32_t e = e0 + u * nwaves;
+      if (e < n) {
+        const uint32_t q = e / sigma, c = e - q * sigma;
+        *reinterpret_cast<uint4*>(lds + q * (PLANES * 1024u) + c * 1024u + lane * 16u) = v[u];
+      }
+    }
+  }
+}
+
 // One column symbol: advance this lane's 32*W-bit vector V.  `p` is the
 // lane's address in the symbol's plane of quad 0.
 template <int W, int SIG>
@@ -217,8 +256,10 @@ __device__ __forceinline__ void dispatch_w(uint32_t w, const DeviceBatch& bt, co
   }
 }
 
+// Classes 0 and 1 in at most 64 registers: two workgroups of sixteen waves
+// then share a CU (eight waves a SIMD).
 template <int CLS, int SIG>
-__global__ __launch_bounds__(1024) void lcs_fast_kernel(
+__global__ __launch_bounds__(1024, CLS < 2 ? 8 : 4) void lcs_fast_kernel(
     DeviceBatch bt, const GroupDesc* __restrict__ groups, const LaneDesc* __restrict__ lanes,
     const ItemDesc* __restrict__ items, const uint32_t* __restrict__ colmap, const uint64_t* __restrict__ rowbase,
     const StepRange* __restrict__ ranges, StepCtl* __restrict__ ctl, int32_t* __restrict__ out, uint32_t sigma) {
@@ -232,8 +273,6 @@ __global__ __launch_bounds__(1024) void lcs_fast_kernel(
   const uint32_t begin = ranges[step].begin[CLS];
   const uint32_t end = ranges[step].end[CLS];
   const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t wave = threadIdx.x >> 6;
-  const uint32_t nwaves = blockDim.x >> 6;
   for (;;) {
     if (threadIdx.x == 0) s_item = begin + atomicAdd(&ctl->cursor[CLS], 1u);
     __syncthreads();
@@ -251,22 +290,12 @@ __global__ __launch_bounds__(1024) void lcs_fast_kernel(
       seq = d.seq;
       lc.len = bt.len[seq];
     }
-    {  // stage the group's masks in LDS (zero past each row's end and in the padding)
-      const uint32_t Q = (g.W + 3u) >> 2;
-      const uint32_t Ws = lane < g.nrows ? (bt.len[seq] + 31u) >> 5 : 0u;
-      const uint64_t mo = lane < g.nrows ? bt.mask_off[seq] : 0ull;
-      const uint32_t n = Q * sigma;
-      for (uint32_t e = wave; e < n; e += nwaves) {
-        const uint32_t q = e / sigma, c = e - q * sigma;
-        uint4 v;
-        const uint32_t w0 = 4u * q;
-        const uint32_t* src = bt.masks + mo + (uint64_t)c * Ws;
-        v.x = w0 + 0 < Ws ? src[w0 + 0] : 0u;
-        v.y = w0 + 1 < Ws ? src[w0 + 1] : 0u;
-        v.z = w0 + 2 < Ws ? src[w0 + 2] : 0u;
-        v.w = w0 + 3 < Ws ? src[w0 + 3] : 0u;
-        *reinterpret_cast<uint4*>(lds + lds_byte<SIG>(q, c, lane)) = v;
-      }
+    {  // the group's masks in LDS (zero past each row's end and in the padding)
+      const uint32_t Ws = lane < g.nrows ? (lc.len + 31u) >> 5 : 0u;
+      uint64_t mo = lane < g.nrows ? bt.mask_off[seq] : 0ull;
+      const uint64_t mo0 = __shfl(mo, 0, 64);  // with every lane in: an empty lane reads row 0's masks and stores zeros
+      if (lane >= g.nrows) mo = mo0;
+      stage_masks<SIG>(bt.masks + mo, Ws, 0u, Ws, (g.W + 3u) >> 2, sigma, lds);
     }
     if (threadIdx.x == 0) s_col = item.c0;
     __syncthreads();
@@ -484,22 +513,12 @@ __device__ __forceinline__ void skew_item(const DeviceBatch& bt, const LaneDesc*
      // zero plane of every quad
     const uint32_t Q = (WL + 3u) >> 2;
     const uint32_t Ws = on ? (lc.len + 31u) >> 5 : 0u;
-    const uint64_t mo = on ? bt.mask_off[seq] : 0ull;
-    const uint32_t np = sigma + 1u;
-    for (uint32_t e = wave; e < Q * np; e += nwaves) {
-      const uint32_t q = e / np, c = e - q * np;
-      uint32_t v[4] = {0u, 0u, 0u, 0u};
-      if (c < sigma) {
-        const uint32_t* src = bt.masks + mo + (uint64_t)c * Ws;
-#pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) {
-          const uint32_t wl = 4u * q + k, wr = s * WL + wl;
-          v[k] = (wl < WL && wr < Ws) ? src[wr] : 0u;
-        }
-      }
-      const uint32_t plane = c < sigma ? c : (uint32_t)SIG;
-      *reinterpret_cast<uint4*>(lds + skew_lds_byte<SIG>(q, plane, lane)) = make_uint4(v[0], v[1], v[2], v[3]);
-    }
+    uint64_t mo = on ? bt.mask_off[seq] : 0ull;
+    const uint64_t mo0 = __shfl(mo, 0, 64);  // with every lane in: one without a segment reads row 0's masks and stores zeros
+    if (!on) mo = mo0;
+    stage_masks<SIG + 1>(bt.masks + mo, Ws, s * WL, min(s * WL + WL, Ws), Q, sigma, lds);
+    for (uint32_t q = wave; q < Q; q += nwaves)
+      *reinterpret_cast<uint4*>(lds + skew_lds_byte<SIG>(q, SIG, lane)) = make_uint4(0u, 0u, 0u, 0u);
   }
   if (threadIdx.x == 0) *s_col = item.c0;
   __syncthreads();
@@ -580,7 +599,9 @@ __global__ __launch_bounds__(1024) void lcs_long_kernel(
       seq = d.seq;
     }
     const uint32_t Ws = lane < g.nrows ? (bt.len[seq] + 31u) >> 5 : 0u;
-    const uint64_t mo = lane < g.nrows ? bt.mask_off[seq] : 0ull;
+    uint64_t mo = lane < g.nrows ? bt.mask_off[seq] : 0ull;
+    const uint64_t mo0 = __shfl(mo, 0, 64);
+    if (lane >= g.nrows) mo = mo0;
     const uint32_t nseg = (g.W + SEGW - 1) / SEGW;
     for (uint32_t cb = item.c0; cb < item.c1; cb += nwaves) {
       const uint32_t col = cb + wave;
@@ -608,17 +629,7 @@ __global__ __launch_bounds__(1024) void lcs_long_kernel(
         const uint32_t wbase = sg * SEGW;
         const uint32_t segw = min(SEGW, g.W - wbase);
         const uint32_t qn = (segw + 3u) >> 2;
-        for (uint32_t e = wave; e < qn * sigma; e += nwaves) {
-          const uint32_t q = e / sigma, c = e - q * sigma;
-          const uint32_t w0 = wbase + 4u * q;
-          const uint32_t* src = bt.masks + mo + (uint64_t)c * Ws;
-          uint4 v;
-          v.x = w0 + 0 < Ws ? src[w0 + 0] : 0u;
-          v.y = w0 + 1 < Ws ? src[w0 + 1] : 0u;
-          v.z = w0 + 2 < Ws ? src[w0 + 2] : 0u;
-          v.w = w0 + 3 < Ws ? src[w0 + 3] : 0u;
-          *reinterpret_cast<uint4*>(lds + lds_byte<SIG>(q, c, lane)) = v;
-        }
+        stage_masks<SIG>(bt.masks + mo, Ws, wbase, Ws, qn, sigma, lds);
         __syncthreads();
         if (valid) {
           const bool has_in = sg > 0, has_out = sg + 1 < nseg;

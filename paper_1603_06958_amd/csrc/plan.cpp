@@ -299,7 +299,7 @@ int famsa_lcs_plan_s::upload_work() {
 int famsa_lcs_plan_s::autotune(const char* path) {
   if (plain() || steps.empty()) return 0;
   static const uint32_t kCols[] = {64, 128, 256, 512};
-  static const uint32_t kWaves[3][3] = {{2, 4, 8}, {4, 8, 16}, {8, 16, 16}};
+  static const uint32_t kWaves[3][3] = {{4, 8, 16}, {4, 8, 16}, {8, 16, 16}};
   hipStream_t st = cs[0];
   hipEvent_t e0 = ev_k[0][0], e1 = ev_k[0][1];
   double best_total = 1e300;
@@ -346,7 +346,7 @@ int famsa_lcs_plan_s::autotune(const char* path) {
           if (launch_step_begin(ctl(0), st)) return set_error(FAMSA_LCS_EDEVICE, "step_begin failed");
           FAMSA_HIP(hipEventRecord(e0, st));
           if (launch_fast(c, batch.view(), w, ctl(0), d_out[0].as<int32_t>(), opt.sigma, w1.qmax[c],
-                          (uint32_t)(bpc * gi.cus), wv, st))
+                          std::min((uint32_t)(bpc * gi.cus), w1.max_items[c]), wv, st))
             return set_error(FAMSA_LCS_EDEVICE, "tuning launch failed");
           FAMSA_HIP(hipEventRecord(e1, st));
           FAMSA_HIP(hipEventSynchronize(e1));

@@ -311,7 +311,6 @@ void build_step(WorkLists& wl, const std::vector<StepFamily>& fams, const std::v
   std::vector<PendingGroup> pend;
   std::vector<std::vector<uint64_t>> colprefs;
   colprefs.reserve(fams.size());
-  uint64_t span = 0;
 
   auto add_plain = [&](const LaneDesc& ld, uint32_t fb, uint32_t ncols, uint32_t cm, uint32_t rb) {
     if (ld.pos + 1 >= ncols) return;  // no pairs
@@ -371,7 +370,6 @@ void build_step(WorkLists& wl, const std::vector<StepFamily>& fams, const std::v
         }
         if (cls == 3 && !lpr) wl.long_col_max = std::max(wl.long_col_max, len[fb + perm[std::min(P + 1, k - 1)]]);
         pend.push_back(PendingGroup{g, P + 1, k, cp.data(), 0});
-        span += k - (P + 1);
       }
     } else {
       // tile mode: the rows of all this family's tiles in the step, pooled
@@ -439,7 +437,6 @@ void build_step(WorkLists& wl, const std::vector<StepFamily>& fams, const std::v
           }
           if (cls == 3 && !lpr) wl.long_col_max = std::max(wl.long_col_max, colmax);
           pend.push_back(PendingGroup{g, P + 1, np, cp.data(), 0});
-          span += np - (P + 1);
         }
         continue;
       }
@@ -477,20 +474,37 @@ void build_step(WorkLists& wl, const std::vector<StepFamily>& fams, const std::v
           for (uint32_t j = mini + 1; j < k; ++j) wl.long_col_max = std::max(wl.long_col_max, len[fb + j]);
         if (cls < 4) {
           pend.push_back(PendingGroup{g, mini + 1, k, nullptr, lenprefix[fb]});
-          span += k - (mini + 1);
         }
       }
     }
   }
 
-  // column chunk: the configured size, smaller when the step is small so
-  // there are enough work items to fill the GPU
-  uint32_t C = lp.cols_per_item ? lp.cols_per_item : 256;
-  const uint64_t want_items = 4096;
-  if (span / C < want_items) C = (uint32_t)std::max<uint64_t>(16, std::min<uint64_t>(C, span / want_items));
+  // Work items: a group's columns in runs.  Large runs share one staging of
+  // the group's masks over many columns, but the workgroups that take a
+  // class's last items finish up to an item apart, and the next launch waits
+  // for them.  So a class is cut from its widest group on into items of
+  // 1 / kSlots of the work that is still left, at most the configured columns
+  // and at least a column for each wave of a large workgroup; a class with
+  // fewer columns than that for every workgroup goes down to four (a column a
+  // SIMD).  Measured (LCS kernels of a pass): k = 20,000 of 250 residues in
+  // uniform runs of 256 columns 28.8 ms, of 64 25.4 ms, these 25.3 ms; 24
+  // families of up to 1,500 sequences of 30 to 2,000 residues 4.77 and 4.85
+  // against 4.4 ms; k = 300 of 250 residues, in runs of 16, 0.17 against 0.08
+  // ms.  Smallest runs of 4 or 8 columns everywhere cost 3 to 12% of the
+  // second (a wave without a column waits for its item).
+  const uint32_t cmax = lp.cols_per_item ? lp.cols_per_item : 128;
+  constexpr uint64_t kSlots = 256;  // workgroups that share a class: a CU each
   StepSig sig;
+  auto wlane = [](const GroupDesc& g) -> uint64_t { return g.lpr ? (g.W + g.lpr - 1) / g.lpr : g.W; };  // dwords per lane
+  auto colsum = [&](const PendingGroup& pg, uint32_t c0, uint32_t c1) {
+    return pg.colpref ? pg.colpref[c1] - pg.colpref[c0] : lenprefix[pg.g.fam_base + c1] - lenprefix[pg.g.fam_base + c0];
+  };
+  std::vector<uint32_t> by(pend.size());  // widest first; the lists keep the groups' own order
+  std::iota(by.begin(), by.end(), 0u);
+  std::stable_sort(by.begin(), by.end(), [&](uint32_t a, uint32_t b) { return wlane(pend[a].g) > wlane(pend[b].g); });
+  uint64_t left[4] = {0, 0, 0, 0}, ncols[4] = {0, 0, 0, 0};
+  const uint32_t g0 = (uint32_t)wl.groups.size();
   for (const PendingGroup& pg : pend) {
-    const uint32_t gi = (uint32_t)wl.groups.size();
     wl.groups.push_back(pg.g);
     const int cls = class_of(pg.g.W, sigma);
     const uint32_t q = (pg.g.W + 3) / 4;
@@ -501,13 +515,24 @@ void build_step(WorkLists& wl, const std::vector<StepFamily>& fams, const std::v
       wl.has_long = true;
       sig.lng = 1;
     }
-    for (uint32_t c = pg.c0; c < pg.c1; c += C) {
-      const uint32_t c1 = std::min<uint32_t>(pg.c1, c + C);
-      uint64_t colsum;
-      if (pg.colpref) colsum = pg.colpref[c1] - pg.colpref[c];
-      else colsum = lenprefix[pg.g.fam_base + c1] - lenprefix[pg.g.fam_base + c];
-      const uint64_t wlane = pg.g.lpr ? (pg.g.W + pg.g.lpr - 1) / pg.g.lpr : pg.g.W;  // dwords per lane
-      ci[cls].push_back(CostItem{wlane * colsum + 64, ItemDesc{gi, c, c1, 0}});
+    left[cls] += wlane(pg.g) * colsum(pg, pg.c0, pg.c1);
+    ncols[cls] += pg.c1 - pg.c0;
+  }
+  for (uint32_t x : by) {
+    const PendingGroup& pg = pend[x];
+    const int cls = class_of(pg.g.W, sigma);
+    const uint64_t w = wlane(pg.g);
+    const uint32_t cmin = std::min<uint32_t>(cmax, (uint32_t)std::min<uint64_t>(16, std::max<uint64_t>(4, ncols[cls] / kSlots)));
+    const uint64_t per = std::max<uint64_t>(1, w * colsum(pg, pg.c0, pg.c1) / (pg.c1 - pg.c0));  // a column's cost
+    for (uint32_t c = pg.c0; c < pg.c1;) {
+      const uint64_t want = left[cls] / kSlots / per;
+      uint32_t n = (uint32_t)std::max<uint64_t>(cmin, std::min<uint64_t>(cmax, want));
+      if (n > 16) n -= n % 16;
+      const uint32_t c1 = pg.c1 - c <= n ? pg.c1 : c + n;
+      const uint64_t cost = w * colsum(pg, c, c1);
+      ci[cls].push_back(CostItem{cost + 64, ItemDesc{g0 + x, c, c1, 0}});
+      left[cls] -= std::min(left[cls], cost);
+      c = c1;
     }
   }
   for (int c = 0; c < 4; ++c) {
@@ -515,6 +540,7 @@ void build_step(WorkLists& wl, const std::vector<StepFamily>& fams, const std::v
     r.begin[c] = (uint32_t)wl.items.size();
     for (const CostItem& x : ci[c]) wl.items.push_back(x.it);
     r.end[c] = (uint32_t)wl.items.size();
+    wl.max_items[c] = std::max(wl.max_items[c], r.end[c] - r.begin[c]);
   }
   r.begin[4] = (uint32_t)wl.prows.size();
   wl.prows.insert(wl.prows.end(), pr.begin(), pr.end());
@@ -563,6 +589,7 @@ int gpu_info(int device, GpuInfo* gi) {
 int StepExec::prepare(int ncu, const LaunchParams& lp, const WorkLists& wl, uint32_t sig) {
   sigma = sig;
   cus = ncu;
+  for (int c = 0; c < 4; ++c) items[c] = wl.max_items[c];
   for (int c = 0; c < 3; ++c) {
     qmax[c] = wl.qmax[c];
     waves[c] = lp.waves[c];
@@ -614,7 +641,8 @@ int StepExec::enqueue(const StepSig& sig, const DeviceBatch& b, const DeviceWork
   if (sig.lng) {
     if (!carry) return set_error(FAMSA_LCS_EDEVICE, "long-row kernel without a carry buffer");
     if (ev) FAMSA_HIP(hipEventRecord(ev[6], s));
-    e = launch_long(b, w, ctl, out, sigma, carry, carry_words, blocks[3], waves[3], s);
+    e = launch_long(b, w, ctl, out, sigma, carry, carry_words, std::min(blocks[3], items[3]), waves[3],
+                    s);
     if (e) return set_error(FAMSA_LCS_EDEVICE, "lcs_long launch failed: %s", hipGetErrorString((hipError_t)e));
     if (ev) FAMSA_HIP(hipEventRecord(ev[7], s));
   }
@@ -623,7 +651,7 @@ int StepExec::enqueue(const StepSig& sig, const DeviceBatch& b, const DeviceWork
     if (!q) continue;
     if (q >= 8 || !bpc[c][q]) return set_error(FAMSA_LCS_EDEVICE, "fast kernel %d was not prepared for %u quads", c, q);
     if (ev) FAMSA_HIP(hipEventRecord(ev[2 * c], s));
-    e = launch_fast(c, b, w, ctl, out, sigma, q, bpc[c][q] * (uint32_t)cus, waves[c], s);
+    e = launch_fast(c, b, w, ctl, out, sigma, q, std::min(bpc[c][q] * (uint32_t)cus, items[c]), waves[c], s);
     if (e) return set_error(FAMSA_LCS_EDEVICE, "lcs_fast<%d> launch failed: %s", c, hipGetErrorString((hipError_t)e));
     if (ev) FAMSA_HIP(hipEventRecord(ev[2 * c + 1], s));
   }

@@ -133,8 +133,12 @@ struct TileWork {
 
 constexpr uint32_t kLongWlAuto = 0xFFFFFFFFu;
 struct LaunchParams {
-  uint32_t waves[4] = {4, 8, 16, 16};  // wavefronts per workgroup per class (3 = long rows)
-  uint32_t cols_per_item = 256;
+  // wavefronts per workgroup per class (3 = long rows): as many as keep every
+  // SIMD at six to eight waves beside the workgroups' LDS.  With 4 and 8 waves
+  // the classes 0 and 1 held three and four waves a SIMD, and k = 20,000 (250
+  // residues) took 8.6 and 13.5 ms in them instead of 7.5 and 12.9 ms.
+  uint32_t waves[4] = {8, 16, 16, 16};
+  uint32_t cols_per_item = 128;
   // Long rows (class 3): the most dwords a lane holds in the lanes-per-row
   // mode (which fixes the lanes per row and so the rows per wave), kLongWlAuto
   // for the largest the LDS allows, 0 for the segmented kernel only.
@@ -175,6 +179,7 @@ struct WorkLists {
   uint32_t w64max_plain = 0;       // largest ceil(len/64) in plain rows
   uint64_t cells[5] = {0, 0, 0, 0, 0};
   uint64_t max_plain_pairs = 0;
+  uint32_t max_items[4] = {0, 0, 0, 0};  // most items of a class in a step
 };
 
 struct FamilyRef {
@@ -234,6 +239,7 @@ struct StepExec {
   uint32_t waves[4] = {4, 8, 16, 16};
   uint32_t bpc[3][8] = {};             // resident workgroups per CU for fast class c at q quads
   uint32_t blocks[4] = {0, 0, 0, 0};   // [3]: long-row kernel grid
+  uint32_t items[4] = {0, 0, 0, 0};    // most items of a class in a step: no more workgroups are launched
   int cus = 256;
   bool has_long = false;
   uint32_t carry_words = 0;            // per lane, for the longest column of a long-row item
