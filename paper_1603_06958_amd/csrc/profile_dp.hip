@@ -838,15 +838,20 @@ extern "C" int famsa_profile_align(uint32_t nprob, const uint8_t* seqs, const ui
                  b_ops = part(o_ops), b_score = part(8ull * nprob), b_nops = part(4ull * nprob);
   FAMSA_HIP(hipSetDevice(device));
   // LDS: a problem whose records, costs and edge rows fit in half a CU's LDS
-  // (so that two problems share a CU) reads them from there; the launch
-  // reserves the largest such share for every workgroup
-  int max_lds = 0;
+  // (so that two problems share a CU) reads them from there; with no more
+  // problems than CUs each has a CU to itself, and the whole of its LDS: six
+  // problems 900 to 1,230 columns wide (84 to 113 KB each) took 2.00 ms from
+  // global memory, whose latency every step then waits for (the whole call 2.40
+  // ms; 1.35 ms from LDS).  The launch
+  // reserves the largest share for every workgroup.
+  int max_lds = 0, cus = 0;
   FAMSA_HIP(hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device));
+  FAMSA_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
+  cus = std::max(cus, 1);
   hipFuncAttributes fa;
   FAMSA_HIP(hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(&pdp_dp_kernel)));
-  const uint64_t lds_cap = (uint64_t)std::min(max_lds, (int)kMaxLds) / 2 > fa.sharedSizeBytes
-                               ? (uint64_t)std::min(max_lds, (int)kMaxLds) / 2 - fa.sharedSizeBytes
-                               : 0;
+  const uint64_t lds_share = (uint64_t)std::min(max_lds, (int)kMaxLds) / (nprob <= (uint32_t)cus ? 1 : 2);
+  const uint64_t lds_cap = lds_share > fa.sharedSizeBytes ? lds_share - fa.sharedSizeBytes : 0;
   uint64_t lds_dyn = 0;
   uint32_t waves = 1;  // the launch's workgroups have as many waves as the widest problem uses
   for (PdpProb& d : pr) {
@@ -863,9 +868,7 @@ extern "C" int famsa_profile_align(uint32_t nprob, const uint8_t* seqs, const ui
   // more waves shorten it (its 512 largest problems: 0.41 ms with up to
   // sixteen, 0.47 ms with four; one problem of 555 x 499: 0.39 ms with eight
   // waves, 0.46 ms with four).
-  int cus = 0;
-  FAMSA_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
-  if (nprob >= 4u * (uint32_t)std::max(cus, 1)) waves = std::min(waves, 4u);
+  if (nprob >= 4u * (uint32_t)cus) waves = std::min(waves, 4u);
   lds_dyn = std::max<uint64_t>(lds_dyn, kTbMinLds);  // the trace-back's ops buffer
   if (lds_dyn > 65536)
     FAMSA_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&pdp_dp_kernel),
