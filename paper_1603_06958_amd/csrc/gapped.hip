@@ -15,9 +15,10 @@
 //
 // A batch (typically every sequence of a profile) lives in HBM as arrays of
 // structures per sequence: symbols (uint8, guard 0xFF), counters (uint32)
-// and tree (uint32), each sequence at its own offset.  Gap insertion runs one
-// thread per sequence over the same list of runs, which is how a profile
-// takes the gap columns of the other profile when two are merged.
+// and tree (uint32), each sequence at its own offset.  Gap insertion applies
+// the same list of runs to every sequence, which is how a profile takes the
+// gap columns of the other profile when two are merged; a group of lanes takes
+// a sequence, a lane a run.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <string.h>
@@ -44,16 +45,20 @@ __device__ __forceinline__ uint32_t span_of(const GappedDev& g, uint64_t po, uin
   return p < npos ? 1u + g.gaps[po + p] : 0u;
 }
 
-// Column counts from the counters: leaves, then one tree level at a time.
-__global__ __launch_bounds__(256) void gapped_rebuild(GappedDev g, uint32_t first) {
-  const uint32_t s = first + blockIdx.x;
+// Counters and column counts of sequences without gaps: node v at depth d
+// covers P >> d positions from (v - 2^d) (P >> d) on, a column each.
+__global__ __launch_bounds__(256) void gapped_init(GappedDev g) {
+  const uint32_t s = blockIdx.x;
   const uint64_t po = g.pos_off[s], to = g.tree_off[s];
   const uint32_t npos = g.npos[s], P = g.ptree[s];
-  for (uint32_t j = threadIdx.x; j < P / 2; j += blockDim.x)
-    g.dps[to + P / 2 + j] = span_of(g, po, npos, 2 * j) + span_of(g, po, npos, 2 * j + 1);
-  for (uint32_t lo = P / 4; lo >= 1; lo /= 2) {
-    __syncthreads();
-    for (uint32_t v = lo + threadIdx.x; v < 2 * lo; v += blockDim.x) g.dps[to + v] = g.dps[to + 2 * v] + g.dps[to + 2 * v + 1];
+  for (uint32_t p = threadIdx.x; p < npos; p += blockDim.x) g.gaps[po + p] = 0;
+  for (uint32_t v = threadIdx.x; v < P; v += blockDim.x) {
+    uint32_t n = 0;
+    if (v) {
+      const uint32_t d = 31u - (uint32_t)__builtin_clz(v), each = P >> d, lo = (v - (1u << d)) * each;
+      n = lo < npos ? min(each, npos - lo) : 0u;
+    }
+    g.dps[to + v] = n;
   }
 }
 
@@ -75,24 +80,53 @@ __device__ __forceinline__ uint32_t find_position(const GappedDev& g, uint64_t p
   return x < span_of(g, po, npos, p) ? p : p + 1;
 }
 
-// One thread per sequence applies every run, the rightmost first, so each
-// run's column keeps the meaning it had before the call.
+// G neighbouring lanes take a sequence, a lane a run, G runs at a time from
+// the right end of the list.  Every run's position is looked up in the tree as
+// it was: gaps put in further right, or into the same position's run, do not
+// move the column before it out of its position's span.  The runs are sorted,
+// so the lanes that meet in a counter or a tree node are neighbours: the last
+// of them adds the sum of all (a difference of two prefix sums) with a plain
+// add.  A walk of one run after another, and its adds, are a chain of some 20
+// dependent accesses a run (64 runs into 20,000 sequences of 250: 340 us);
+// here the chain is one walk and one add for G runs (26 us).
+template <int G>
 __global__ __launch_bounds__(256) void gapped_insert(GappedDev g, uint32_t first, uint32_t nseq,
                                                      const uint32_t* __restrict__ col,
                                                      const uint32_t* __restrict__ len, uint32_t nruns) {
-  const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= nseq) return;
-  const uint32_t s = first + t;
+  const uint32_t tid = threadIdx.x, l = tid & (G - 1u);
+  const uint32_t t = blockIdx.x * (256u / G) + tid / G;
+  const bool on = t < nseq;
+  const uint32_t s = first + (on ? t : 0u);
   const uint64_t po = g.pos_off[s], to = g.tree_off[s];
   const uint32_t npos = g.npos[s], P = g.ptree[s];
-  for (uint32_t r = nruns; r-- > 0;) {
-    const uint32_t n = len[r];
-    if (n == 0) continue;
+  for (uint32_t top = nruns; top > 0; top = top > (uint32_t)G ? top - G : 0u) {
+    const uint32_t base = top > (uint32_t)G ? top - G : 0u, nr = top - base;  // runs [base, top)
+    const uint32_t r = base + min(l, nr - 1u);  // lanes without a run repeat the last one and add nothing
+    const uint32_t n = l < nr ? len[r] : 0u;
     uint32_t leaf;
-    // gaps before column c go right after whatever column c-1 belongs to
+    // gaps before column c go right after whatever column c - 1 belongs to
     const uint32_t p = find_position(g, po, to, npos, P, col[r] - 1u, &leaf);
-    g.gaps[po + p] += n;
-    for (uint32_t v = leaf; v >= 1; v /= 2) g.dps[to + v] += n;
+    uint32_t sum = n;  // of the runs up to this one
+#pragma unroll
+    for (int d = 1; d < G; d <<= 1) {
+      const uint32_t y = __shfl_up(sum, d, G);
+      if (l >= (uint32_t)d) sum += y;
+    }
+    // adds the runs of the lanes that share `key` (neighbours) to *x, by the last of them
+    auto add = [&](bool live, uint32_t key, uint32_t* x) {
+      const uint32_t before = __shfl_up(key, 1, G), after = __shfl_down(key, 1, G);
+      const uint64_t heads = __ballot(l == 0 || before != key);
+      const uint32_t lane = tid & 63u;
+      const uint32_t h = 63u - (uint32_t)__builtin_clzll(heads & (~0ull >> (63u - lane)));  // first lane of the run of lanes
+      const uint32_t upto = __shfl(sum, (int)((h - 1u) & 63u), 64);
+      const uint32_t more = sum - ((h & (G - 1u)) ? upto : 0u);
+      if (live && (l == G - 1u || after != key) && more) *x += more;
+    };
+    add(on, p, &g.gaps[po + p]);
+    for (uint32_t v = leaf; __any(v >= 1); v >>= 1) {  // sequences of a wave may have trees of different depths
+      add(on && v >= 1, v, &g.dps[to + v]);
+    }
+    __threadfence_block();  // the next runs' walks see these adds
   }
 }
 
@@ -219,11 +253,7 @@ int famsa_gapped_create(const uint8_t* codes, const uint64_t* seq_off, uint32_t 
     delete g;
     return rc;
   }
-  if (hipMemsetAsync(g->gaps.p, 0, std::max<uint64_t>(total_pos, 1) * 4, st) != hipSuccess) {
-    delete g;
-    return set_error(FAMSA_LCS_EDEVICE, "clearing gap counters failed");
-  }
-  if (nseq) hipLaunchKernelGGL(gapped_rebuild, dim3(nseq), dim3(256), 0, st, g->view(), 0u);
+  if (nseq) hipLaunchKernelGGL(gapped_init, dim3(nseq), dim3(256), 0, st, g->view());
   if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
     delete g;
     return set_error(FAMSA_LCS_EDEVICE, "building the position trees failed");
@@ -259,8 +289,15 @@ int famsa_gapped_insert(famsa_gapped_t* g, uint32_t first, uint32_t count, const
   if (g->runs.bytes < h.size() * 4 && (rc = g->runs.alloc(h.size() * 4))) return rc;
   FAMSA_HIP(hipMemcpyAsync(g->runs.p, h.data(), h.size() * 4, hipMemcpyHostToDevice, g->s));
   const uint32_t* d = g->runs.as<uint32_t>();
-  hipLaunchKernelGGL(gapped_insert, dim3((count + 255) / 256), dim3(256), 0, g->s, g->view(), first, count, d,
-                     d + nruns, nruns);
+  // lanes a sequence: enough for its runs, so that few runs do not leave most of a wave idle
+  auto insert = [&](auto kernel, uint32_t lanes) {
+    const uint32_t per = 256 / lanes;
+    hipLaunchKernelGGL(kernel, dim3((count + per - 1) / per), dim3(256), 0, g->s, g->view(), first, count, d, d + nruns,
+                       nruns);
+  };
+  if (nruns <= 4) insert(gapped_insert<4>, 4);
+  else if (nruns <= 16) insert(gapped_insert<16>, 16);
+  else insert(gapped_insert<64>, 64);
   FAMSA_HIP(hipGetLastError());
   FAMSA_HIP(hipStreamSynchronize(g->s));
   for (uint32_t i = first; i < first + count; ++i) g->h_width[i] += (uint32_t)add;
