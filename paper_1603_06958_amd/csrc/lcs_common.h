@@ -26,6 +26,7 @@
 //     tile: the rows of a step's tiles are pooled and sorted by length, and
 //     each needs the columns (in the caller's order) after its own index.
 #pragma once
+#include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "../../include/famsa_lcs.h"
@@ -164,6 +165,28 @@ int launch_fast(int cls, const DeviceBatch& b, const DeviceWork& w, StepCtl* ctl
 inline uint32_t sig_cap(uint32_t sigma) { return sigma <= 20 ? 20u : 32u; }
 inline size_t fast_lds_bytes(uint32_t sigma, uint32_t qmax) { return (size_t)qmax * sig_cap(sigma) * 1024u; }
 int fast_prepare(int cls, uint32_t sigma, uint32_t qmax, uint32_t waves, int* blocks_per_cu);
+// Whether an allocation-free call's input was valid, found by its first launch
+// and read by its last.  Calls take the `bad` words in turn: the first launch
+// of call n (its number is `ended`, which only last launches write) marks
+// bad[n & 1] and sets `begun` to n + 1; the last launch reads that word by
+// `begun`, clears the other one for call n + 1 and sets `ended` to n + 1.
+struct InputCheck {
+  uint32_t begun, ended;
+  uint32_t bad[2];  // a code is outside the alphabet
+  uint32_t lengths; // a length or an offset is invalid
+  __device__ uint32_t failed() const { return lengths | bad[(begun - 1) & 1u]; }
+  __device__ void end() {
+    bad[begun & 1u] = 0;
+    ended = begun;
+  }
+};
+// Classes 2, 1 and 0 of a step in one launch (qmax: the widest group's quads).
+// `check` (device) may be NULL; else the launch is the last of an
+// allocation-free call: it writes *status (if not NULL), and sets every one of
+// the nvalues outputs to -1 when the input was invalid.
+int launch_small(const DeviceBatch& b, const DeviceWork& w, StepCtl* ctl, int32_t* out, uint32_t sigma, uint32_t qmax,
+                 uint32_t blocks, uint32_t waves, InputCheck* check, int32_t* status, uint64_t nvalues, void* stream);
+int small_prepare(uint32_t sigma, uint32_t qmax);
 // Plain kernel: one pair per lane over the class-3 row range of the current
 // step; w64_max bounds ceil(len/64) of the rows; d_work is scratch for rows
 // longer than the register variants cover (may be NULL otherwise).

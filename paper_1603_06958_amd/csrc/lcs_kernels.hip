@@ -28,6 +28,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <map>
+#include <mutex>
+#include <tuple>
+
 #include "lcs_common.h"
 
 namespace famsa {
@@ -256,6 +260,37 @@ __device__ __forceinline__ void dispatch_w(uint32_t w, const DeviceBatch& bt, co
   }
 }
 
+// One work item of a one-lane-per-row group: its masks to LDS, then waves take
+// its columns.  Every thread of the workgroup calls it.
+template <int WLO, int WHI, int SIG>
+__device__ __forceinline__ void fast_item(const DeviceBatch& bt, const GroupDesc* __restrict__ groups,
+                                          const LaneDesc* __restrict__ lanes, const ItemDesc item,
+                                          const uint32_t* __restrict__ colmap, const uint64_t* __restrict__ rowbase,
+                                          uint32_t sigma, char* lds, uint32_t* s_col, int32_t* __restrict__ out) {
+  const uint32_t lane = threadIdx.x & 63u;
+  const GroupDesc g = groups[item.group];
+  LaneCtx lc{0ull, 0xFFFFFFFFu, 0u, 0u};  // pos = max: an empty lane never stores
+  uint32_t seq = 0;
+  if (lane < g.nrows) {
+    const LaneDesc d = lanes[g.lane_first + lane];
+    lc.out_off = d.out_off;
+    lc.pos = d.pos;
+    lc.orig = d.orig;
+    seq = d.seq;
+    lc.len = bt.len[seq];
+  }
+  {  // the group's masks in LDS (zero past each row's end and in the padding)
+    const uint32_t Ws = lane < g.nrows ? (lc.len + 31u) >> 5 : 0u;
+    uint64_t mo = lane < g.nrows ? bt.mask_off[seq] : 0ull;
+    const uint64_t mo0 = __shfl(mo, 0, 64);  // with every lane in: an empty lane reads row 0's masks and stores zeros
+    if (lane >= g.nrows) mo = mo0;
+    stage_masks<SIG>(bt.masks + mo, Ws, 0u, Ws, (g.W + 3u) >> 2, sigma, lds);
+  }
+  if (threadIdx.x == 0) *s_col = item.c0;
+  __syncthreads();
+  dispatch_w<WLO, WHI, SIG>(g.W, bt, colmap, rowbase, g, item.c1, lds, s_col, lc, out);
+}
+
 // Classes 0 and 1 in at most 64 registers: two workgroups of sixteen waves
 // then share a CU (eight waves a SIMD).
 template <int CLS, int SIG>
@@ -272,34 +307,50 @@ __global__ __launch_bounds__(1024, CLS < 2 ? 8 : 4) void lcs_fast_kernel(
   const uint32_t step = ctl->step;
   const uint32_t begin = ranges[step].begin[CLS];
   const uint32_t end = ranges[step].end[CLS];
-  const uint32_t lane = threadIdx.x & 63u;
   for (;;) {
     if (threadIdx.x == 0) s_item = begin + atomicAdd(&ctl->cursor[CLS], 1u);
     __syncthreads();
     const uint32_t it = s_item;
     if (it >= end) break;  // same value in every thread
-    const ItemDesc item = items[it];
-    const GroupDesc g = groups[item.group];
-    LaneCtx lc{0ull, 0xFFFFFFFFu, 0u, 0u};  // pos = max: an empty lane never stores
-    uint32_t seq = 0;
-    if (lane < g.nrows) {
-      const LaneDesc d = lanes[g.lane_first + lane];
-      lc.out_off = d.out_off;
-      lc.pos = d.pos;
-      lc.orig = d.orig;
-      seq = d.seq;
-      lc.len = bt.len[seq];
-    }
-    {  // the group's masks in LDS (zero past each row's end and in the padding)
-      const uint32_t Ws = lane < g.nrows ? (lc.len + 31u) >> 5 : 0u;
-      uint64_t mo = lane < g.nrows ? bt.mask_off[seq] : 0ull;
-      const uint64_t mo0 = __shfl(mo, 0, 64);  // with every lane in: an empty lane reads row 0's masks and stores zeros
-      if (lane >= g.nrows) mo = mo0;
-      stage_masks<SIG>(bt.masks + mo, Ws, 0u, Ws, (g.W + 3u) >> 2, sigma, lds);
-    }
-    if (threadIdx.x == 0) s_col = item.c0;
+    fast_item<WLO, WHI, SIG>(bt, groups, lanes, items[it], colmap, rowbase, sigma, lds, &s_col, out);
+    __syncthreads();  // LDS and s_item are reused by the next item
+  }
+}
+
+// Classes 2, 1 and 0 in one launch, for steps with too few items to fill the
+// GPU: one class after another each took the time of a single column (about
+// 0.1 us a residue for a wave by itself) and a launch: 100 sequences of up to
+// 300 residues 56 us in two launches and 37 us in one, 300 of 250 63 and 38 us.
+template <int SIG>
+__global__ __launch_bounds__(1024) void lcs_small_kernel(
+    DeviceBatch bt, const GroupDesc* __restrict__ groups, const LaneDesc* __restrict__ lanes,
+    const ItemDesc* __restrict__ items, const uint32_t* __restrict__ colmap, const uint64_t* __restrict__ rowbase,
+    const StepRange* __restrict__ ranges, StepCtl* __restrict__ ctl, int32_t* __restrict__ out, uint32_t sigma,
+    InputCheck* check, int32_t* status, uint64_t nvalues) {
+  constexpr int WHI = SIG == 20 ? 4 * kClassQMax[2] : 16;
+  extern __shared__ uint4 lds4[];
+  char* lds = reinterpret_cast<char*>(lds4);
+  __shared__ uint32_t s_item;
+  __shared__ uint32_t s_col;
+  const bool fail = check && check->failed();
+  if (check && blockIdx.x == 0 && threadIdx.x == 0) {
+    if (status) *status = fail ? FAMSA_LCS_EINVAL : FAMSA_LCS_OK;
+    check->end();
+  }
+  if (fail) {
+    const uint64_t n = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p < nvalues; p += n) out[p] = -1;
+    return;
+  }
+  const StepRange& r = ranges[ctl->step];
+  const uint32_t n2 = r.end[2] - r.begin[2], n1 = r.end[1] - r.begin[1], n0 = r.end[0] - r.begin[0];
+  for (;;) {
+    if (threadIdx.x == 0) s_item = atomicAdd(&ctl->cursor[0], 1u);
     __syncthreads();
-    dispatch_w<WLO, WHI, SIG>(g.W, bt, colmap, rowbase, g, item.c1, lds, &s_col, lc, out);
+    const uint32_t x = s_item;
+    if (x >= n2 + n1 + n0) break;  // same value in every thread
+    const uint32_t it = x < n2 ? r.begin[2] + x : (x < n2 + n1 ? r.begin[1] + (x - n2) : r.begin[0] + (x - n2 - n1));
+    fast_item<1, WHI, SIG>(bt, groups, lanes, items[it], colmap, rowbase, sigma, lds, &s_col, out);
     __syncthreads();  // LDS and s_item are reused by the next item
   }
 }
@@ -759,13 +810,26 @@ static const void* fast_kernel_ptr(int cls, uint32_t sigma) {
   }
 }
 
-// Allow the class's dynamic LDS and report how many workgroups of `waves`
-// waves fit on one CU.  Call before any launch (and before graph capture).
-int fast_prepare(int cls, uint32_t sigma, uint32_t qmax, uint32_t waves, int* blocks_per_cu) {
-  const size_t lds = fast_lds_bytes(sigma, qmax);
-  const void* fn = fast_kernel_ptr(cls, sigma);
+// Allow a kernel's dynamic LDS and report how many workgroups of `waves` waves
+// fit on one CU of the current device.  Call before any launch (and before
+// graph capture).  The answer depends on nothing else, so it is asked once per
+// device, kernel and shape (three driver calls of some 20 us otherwise, for
+// every class of every plan).
+static int kernel_prepare(const void* fn, uint32_t waves, size_t lds, int* blocks_per_cu) {
+  static std::mutex mu;
+  static std::map<std::tuple<int, const void*, uint32_t, size_t>, int> known;
+  int device = 0;
+  hipError_t e = hipGetDevice(&device);
+  if (e != hipSuccess) return (int)e;
+  std::lock_guard<std::mutex> lock(mu);
+  const auto key = std::make_tuple(device, fn, waves, lds);
+  const auto it = known.find(key);
+  if (it != known.end()) {
+    if (blocks_per_cu) *blocks_per_cu = it->second;
+    return 0;
+  }
   hipFuncAttributes fa;
-  hipError_t e = hipFuncGetAttributes(&fa, fn);
+  e = hipFuncGetAttributes(&fa, fn);
   if (e != hipSuccess) return (int)e;
   if (fa.sharedSizeBytes > kLdsReserve || lds + kLdsReserve > g_max_lds) return (int)hipErrorInvalidValue;
   e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(g_max_lds - fa.sharedSizeBytes));
@@ -773,8 +837,13 @@ int fast_prepare(int cls, uint32_t sigma, uint32_t qmax, uint32_t waves, int* bl
   int nb = 0;
   e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, (int)(waves * 64), lds);
   if (e != hipSuccess) return (int)e;
+  known[key] = nb;
   if (blocks_per_cu) *blocks_per_cu = nb;
   return 0;
+}
+
+int fast_prepare(int cls, uint32_t sigma, uint32_t qmax, uint32_t waves, int* blocks_per_cu) {
+  return kernel_prepare(fast_kernel_ptr(cls, sigma), waves, fast_lds_bytes(sigma, qmax), blocks_per_cu);
 }
 
 int launch_fast(int cls, const DeviceBatch& b, const DeviceWork& w, StepCtl* ctl, int32_t* out, uint32_t sigma,
@@ -794,6 +863,28 @@ int launch_fast(int cls, const DeviceBatch& b, const DeviceWork& w, StepCtl* ctl
   return hip_ok(hipGetLastError());
 }
 
+static const void* small_kernel_ptr(uint32_t sigma) {
+  return sig_cap(sigma) == 20 ? reinterpret_cast<const void*>(&lcs_small_kernel<20>)
+                              : reinterpret_cast<const void*>(&lcs_small_kernel<32>);
+}
+
+int small_prepare(uint32_t sigma, uint32_t qmax) {
+  return kernel_prepare(small_kernel_ptr(sigma), 16, fast_lds_bytes(sigma, qmax), nullptr);
+}
+
+int launch_small(const DeviceBatch& b, const DeviceWork& w, StepCtl* ctl, int32_t* out, uint32_t sigma, uint32_t qmax,
+                 uint32_t blocks, uint32_t waves, InputCheck* check, int32_t* status, uint64_t nvalues, void* stream) {
+  const size_t lds = fast_lds_bytes(sigma, qmax);
+  const dim3 grid(blocks), block(waves * 64);
+  if (sig_cap(sigma) == 20)
+    hipLaunchKernelGGL((lcs_small_kernel<20>), grid, block, lds, (hipStream_t)stream, b, w.groups, w.lanes, w.items,
+                       w.colmap, w.rowbase, w.ranges, ctl, out, sigma, check, status, nvalues);
+  else
+    hipLaunchKernelGGL((lcs_small_kernel<32>), grid, block, lds, (hipStream_t)stream, b, w.groups, w.lanes, w.items,
+                       w.colmap, w.rowbase, w.ranges, ctl, out, sigma, check, status, nvalues);
+  return hip_ok(hipGetLastError());
+}
+
 template <int SQ, int SIG>
 static const void* long_fn() {
   return reinterpret_cast<const void*>(&lcs_long_kernel<SQ, SIG>);
@@ -804,19 +895,7 @@ static const void* long_kernel_ptr(uint32_t sigma) {
 }
 
 int long_prepare(uint32_t sigma, uint32_t waves, int* blocks_per_cu) {
-  const size_t lds = long_lds_bytes(sigma);
-  const void* fn = long_kernel_ptr(sigma);
-  hipFuncAttributes fa;
-  hipError_t e = hipFuncGetAttributes(&fa, fn);
-  if (e != hipSuccess) return (int)e;
-  if (fa.sharedSizeBytes > kLdsReserve || lds + kLdsReserve > g_max_lds) return (int)hipErrorInvalidValue;
-  e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(g_max_lds - fa.sharedSizeBytes));
-  if (e != hipSuccess) return (int)e;
-  int nb = 0;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, (int)(waves * 64), lds);
-  if (e != hipSuccess) return (int)e;
-  if (blocks_per_cu) *blocks_per_cu = nb;
-  return 0;
+  return kernel_prepare(long_kernel_ptr(sigma), waves, long_lds_bytes(sigma), blocks_per_cu);
 }
 
 int launch_long(const DeviceBatch& b, const DeviceWork& w, StepCtl* ctl, int32_t* out, uint32_t sigma,

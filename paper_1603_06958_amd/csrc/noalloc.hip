@@ -5,16 +5,21 @@
 // batch, work lists, queue counters and step buffers, and plans the work on
 // the host.  Here every one of those lives in `scratch`, one file-scope
 // device array of fixed size per GPU, and the planning runs on the device:
-//   na_plan_kernel   -- one workgroup: lengths and offsets checked, rows
-//                       sorted by length (bitonic sort in LDS), the family
-//                       mode work lists of the plan path (64-row groups,
-//                       column items, class ranges) and the queue counters;
-//   na_stage_kernel  -- a workgroup per sequence: codes checked, the
-//                       column stream (code c stored as c * 1024) and the
-//                       match masks PM[c][w] written into the sequence's slot;
-//   lcs_fast_kernel  -- the plan path's own kernels, classes 2, 1, 0;
-//   na_finish_kernel -- status word; every output set to -1 on invalid input.
+//   na_prep_kernel   -- the first workgroup plans: lengths and offsets
+//                       checked, rows sorted by length (counting sort), the
+//                       family mode work lists of the plan path (64-row
+//                       groups, column items); the others stage four
+//                       sequences each: codes checked, the column stream
+//                       (code c stored as c * 1024) and the match masks
+//                       PM[c][w] written into the sequence's slot;
+//   lcs_small_kernel -- families of few items: every class in one launch; or
+//   lcs_fast_kernel  -- the plan path's own kernels, classes 2, 1, 0, and
+//   na_finish_kernel -- the status; every output set to -1 on invalid input
+//                       (the last launch does this, whichever it is).
 // Results are the plan path's bit for bit (same kernels, same recurrence).
+// A call of 48 sequences takes 38 us (90 us when the sort was bitonic, staging
+// waited for the plan, and every class had a launch of a full grid), one of
+// 8,192 sequences of 300 residues 5.75 ms (7.08 ms; the LCS kernel is 5.7).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -27,17 +32,18 @@ namespace {
 
 constexpr uint32_t kNaMaxSeq = FAMSA_LCS_NOALLOC_MAX_SEQ;
 constexpr uint32_t kNaMaxGroups = kNaMaxSeq / kLanes;
-constexpr uint32_t kNaMaxItems = 8192;  // the item count never exceeds 4480 (columns per item >= span / 4096)
+constexpr uint32_t kNaMaxItems = 8192;
 constexpr uint32_t kNaMaxLen20 = FAMSA_LCS_NOALLOC_MAX_LEN;      // 28 dwords: the fast classes for sigma <= 20
 constexpr uint32_t kNaMaxLen32 = FAMSA_LCS_NOALLOC_MAX_LEN_S32;  // 16 dwords: class 2 holds 4 quads of 32 planes
 constexpr uint32_t kNaSymSlot = 2 * kNaMaxLen20 + 16;  // bytes: uint16 per residue and the spare chunk
 constexpr uint32_t kNaMaskSlot = 20 * 28;               // dwords: >= 20 x 28 and >= 32 x 16
 constexpr int kNaMaxDevices = 64;
-constexpr uint32_t kNaPlanThreads = 1024;
+constexpr uint32_t kNaThreads = 1024;
+constexpr uint32_t kNaTeam = 256;  // threads that stage a sequence
 
 constexpr size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 constexpr size_t kOffCtl = 0;    // StepCtl
-constexpr size_t kOffErr = 64;   // uint32: 0 valid, nonzero invalid input
+constexpr size_t kOffCheck = 64;   // InputCheck
 constexpr size_t kOffRange = 128;  // StepRange of the one step
 constexpr size_t kOffGroups = 256;
 constexpr size_t kOffLanes = align256(kOffGroups + sizeof(GroupDesc) * kNaMaxGroups);
@@ -52,7 +58,7 @@ constexpr size_t kOffMasks = align256(kOffSym + (size_t)kNaSymSlot * kNaMaxSeq);
 constexpr size_t kNaBytes = align256(kOffMasks + sizeof(uint32_t) * kNaMaskSlot * kNaMaxSeq);
 static_assert(kNaBytes == FAMSA_LCS_NOALLOC_SCRATCH_BYTES, "header states the scratch size");
 static_assert(kNaSymSlot % 16 == 0, "column streams are read in 16-byte chunks");
-static_assert(sizeof(StepCtl) <= 64 && sizeof(StepRange) <= 128, "control block layout");
+static_assert(sizeof(StepCtl) <= 64 && sizeof(InputCheck) <= 64 && sizeof(StepRange) <= 128, "control block layout");
 
 // Each GPU holds its own copy.  Host code never passes this name to a kernel:
 // it takes the device address from hipGetSymbolAddress.
@@ -64,27 +70,36 @@ struct NaView {  // device addresses inside one GPU's scratch
   StepRange* range() const { return reinterpret_cast<StepRange*>(base + kOffRange); }
 };
 
-__device__ __forceinline__ uint32_t* na_err(uint8_t* base) { return reinterpret_cast<uint32_t*>(base + kOffErr); }
+__host__ __device__ inline InputCheck* na_check(uint8_t* base) { return reinterpret_cast<InputCheck*>(base + kOffCheck); }
 
-__device__ __forceinline__ void na_empty_ranges(uint8_t* base) {
-  StepRange* r = reinterpret_cast<StepRange*>(base + kOffRange);
-  for (int c = 0; c < 5; ++c) {
-    r->begin[c] = 0;
-    r->end[c] = 0;
-  }
-  r->plain_pairs = 0;
+// Columns that the groups from `g` on walk: group h needs the positions after
+// its own first row, [64 h + 1, k).
+__host__ __device__ inline uint32_t na_columns(uint32_t k, uint32_t g) {
+  const uint32_t G = k >= 2 ? (k - 2) / kLanes + 1 : 0;  // groups with a pair: 64 h + 1 < k
+  return g >= G ? 0 : (G - g) * (k - 1) - kLanes * ((G - 1) * G / 2 - (g * g - g) / 2);
+}
+// Columns of group g's items, as the plan path cuts them: 1 / 256 of what is
+// left, 4 to 96 (which keeps 8,192 sequences within the item array).
+__host__ __device__ inline uint32_t na_run(uint32_t k, uint32_t g) {
+  const uint32_t lo = na_columns(k, 0) / 256, want = na_columns(k, g) / 256;
+  const uint32_t least = lo < 4 ? 4 : (lo < 16 ? lo : 16);
+  return want < least ? least : (want > 96 ? 96 : want);
+}
+__host__ __device__ inline uint32_t na_items(uint32_t k, uint32_t g) {
+  const uint32_t n = k - (kLanes * g + 1), c = na_run(k, g);
+  return (n + c - 1) / c;
 }
 
-// One workgroup.  Rows sorted longest first (ties by index, as the plan
-// path's stable sort); groups of 64 consecutive sorted rows; group g's rows
-// need the column positions after their own, [64g + 1, k), cut into items
-// of C columns; column position q is sequence colmap[q], and a pair lands in
-// the upper-triangle row of its smaller index.
-__global__ __launch_bounds__(kNaPlanThreads) void na_plan_kernel(const uint64_t* __restrict__ seq_off, uint32_t k,
-                                                                 uint32_t maxlen, uint8_t* __restrict__ base) {
-  __shared__ uint32_t key[kNaMaxSeq];
+// The plan, by one workgroup.  Rows sorted longest first by a counting sort
+// (rows of one length in any order: their values do not depend on it); groups
+// of 64 consecutive sorted rows; column position q is sequence colmap[q], and
+// a pair lands in the upper-triangle row of its smaller index.
+__device__ void na_plan(const uint64_t* __restrict__ seq_off, uint32_t k, uint32_t maxlen, uint8_t* __restrict__ base) {
+  __shared__ uint32_t s_at[1024];  // rows longer than L, then the next place of a row of length L (at 1023 - L)
+  __shared__ uint32_t s_wave[16];
+  __shared__ uint16_t s_row[kNaMaxSeq], s_len[kNaMaxSeq];
   __shared__ uint32_t s_first[kNaMaxGroups + 1];
-  __shared__ uint32_t s_err, s_C;
+  __shared__ uint32_t s_err, s_cnt[3];
   uint32_t* len = reinterpret_cast<uint32_t*>(base + kOffLen);
   uint64_t* sym_off = reinterpret_cast<uint64_t*>(base + kOffSymOff);
   uint64_t* mask_off = reinterpret_cast<uint64_t*>(base + kOffMaskOff);
@@ -93,42 +108,42 @@ __global__ __launch_bounds__(kNaPlanThreads) void na_plan_kernel(const uint64_t*
   LaneDesc* lanes = reinterpret_cast<LaneDesc*>(base + kOffLanes);
   GroupDesc* groups = reinterpret_cast<GroupDesc*>(base + kOffGroups);
   ItemDesc* items = reinterpret_cast<ItemDesc*>(base + kOffItems);
-  const uint32_t tid = threadIdx.x;
-  if (tid == 0) s_err = 0;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  if (tid < 3) s_cnt[tid] = 0;
+  if (tid == 3) s_err = 0;
+  s_at[tid] = 0;
   __syncthreads();
-  uint32_t N = 1;
-  while (N < k) N <<= 1;
-  for (uint32_t i = tid; i < N; i += kNaPlanThreads) {
-    uint32_t kk = 0xFFFFFFFFu;
-    if (i < k) {
-      const uint64_t a = seq_off[i], b = seq_off[i + 1];
-      uint32_t L = 0;
-      if (b < a || b - a > maxlen) atomicOr(&s_err, 1u);
-      else L = (uint32_t)(b - a);
-      len[i] = L;
-      sym_off[i] = (uint64_t)i * kNaSymSlot;
-      mask_off[i] = (uint64_t)i * kNaMaskSlot;
-      kk = ((1023u - L) << 13) | i;  // L <= 896 < 1024, i < 8192
-    }
-    key[i] = kk;
+  for (uint32_t i = tid; i < k; i += kNaThreads) {
+    const uint64_t a = seq_off[i], b = seq_off[i + 1];
+    uint32_t L = 0;
+    if (b < a || b - a > maxlen) atomicOr(&s_err, 1u);
+    else L = (uint32_t)(b - a);
+    len[i] = L;
+    sym_off[i] = (uint64_t)i * kNaSymSlot;
+    mask_off[i] = (uint64_t)i * kNaMaskSlot;
+    s_len[i] = (uint16_t)L;
+    atomicAdd(&s_at[1023u - L], 1u);  // L <= 896
   }
   __syncthreads();
-  for (uint32_t size = 2; size <= N; size <<= 1) {
-    for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
-      for (uint32_t t = tid; t < N / 2; t += kNaPlanThreads) {
-        const uint32_t i = 2 * t - (t & (stride - 1));  // bit `stride` of i is clear
-        const uint32_t j = i + stride;
-        const uint32_t a = key[i], b = key[j];
-        if ((a > b) == ((i & size) == 0)) {
-          key[i] = b;
-          key[j] = a;
-        }
-      }
-      __syncthreads();
+  {  // exclusive prefix over the lengths, longest first
+    const uint32_t n = s_at[tid];
+    uint32_t sum = n;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t y = __shfl_up(sum, d, 64);
+      if (lane >= (uint32_t)d) sum += y;
     }
+    if (lane == 63) s_wave[wave] = sum;
+    __syncthreads();
+    uint32_t before = 0;
+    for (uint32_t w = 0; w < wave; ++w) before += s_wave[w];
+    s_at[tid] = before + sum - n;
   }
-  for (uint32_t q = tid; q < k; q += kNaPlanThreads) {
-    const uint32_t a = key[q] & 0x1FFFu;
+  __syncthreads();
+  for (uint32_t i = tid; i < k; i += kNaThreads) s_row[atomicAdd(&s_at[1023u - s_len[i]], 1u)] = (uint16_t)i;
+  __syncthreads();
+  for (uint32_t q = tid; q < k; q += kNaThreads) {
+    const uint32_t a = s_row[q];
     const uint64_t ro = (uint64_t)a * k - (uint64_t)a * (a + 1) / 2;  // offset of pair (a, a + 1)
     colmap[q] = a;
     rowbase[q] = ro;
@@ -140,17 +155,21 @@ __global__ __launch_bounds__(kNaPlanThreads) void na_plan_kernel(const uint64_t*
     d.pad = 0;
     lanes[q] = d;
   }
-  const uint32_t G = k >= 2 ? (k - 2) / kLanes + 1 : 0;  // groups with a pair: 64 g + 1 < k
-  if (tid == 0) {
-    uint64_t span = 0;
-    for (uint32_t g = 0; g < G; ++g) span += k - (kLanes * g + 1);
-    uint32_t C = 256;
-    if (span / C < 4096) C = (uint32_t)max<uint64_t>(16, min<uint64_t>(C, span / 4096));
-    uint32_t n = 0, cnt[3] = {0, 0, 0};
-    for (uint32_t g = 0; g < G; ++g) {
+  const uint32_t G = k >= 2 ? (k - 2) / kLanes + 1 : 0;
+  if (wave < 2) {  // a lane a group; items numbered by a prefix sum
+    const uint32_t g = tid;
+    const uint32_t ni = g < G ? na_items(k, g) : 0u;
+    uint32_t sum = ni;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t y = __shfl_up(sum, d, 64);
+      if (lane >= (uint32_t)d) sum += y;
+    }
+    if (lane == 63) s_wave[wave] = sum;
+    s_first[g] = sum - ni;  // within its wave
+    if (g < G) {
       const uint32_t P = kLanes * g;
-      const uint32_t L = 1023u - (key[P] >> 13);
-      const uint32_t W = max(1u, (L + 31u) >> 5);
+      const uint32_t W = max(1u, (s_len[s_row[P]] + 31u) >> 5);
       const uint32_t Q = (W + 3u) >> 2;
       const int cls = Q <= (uint32_t)kClassQMax[0] ? 0 : (Q <= (uint32_t)kClassQMax[1] ? 1 : 2);
       GroupDesc gd;
@@ -165,92 +184,97 @@ __global__ __launch_bounds__(kNaPlanThreads) void na_plan_kernel(const uint64_t*
       gd.lpr = 0;
       gd.pad[0] = gd.pad[1] = gd.pad[2] = 0;
       groups[g] = gd;
-      const uint32_t ni = (k - P - 1 + C - 1) / C;
-      s_first[g] = n;
-      n += ni;
-      cnt[cls] += ni;  // classes do not increase with g: rows are sorted longest first
+      atomicAdd(&s_cnt[cls], ni);  // classes do not increase with g: rows are sorted longest first
     }
-    s_first[G] = n;
-    s_C = C;
-    if (n > kNaMaxItems) s_err |= 4u;
+  }
+  __syncthreads();
+  for (uint32_t g = wave; g < G; g += kNaThreads / 64) {
+    const uint32_t f = s_first[g] + (g >= 64 ? s_wave[0] : 0u), ni = na_items(k, g), C = na_run(k, g);
+    for (uint32_t t = lane; t < ni; t += 64) {
+      ItemDesc it;
+      it.group = g;
+      it.c0 = kLanes * g + 1 + t * C;
+      it.c1 = min(k, it.c0 + C);
+      it.pad = 0;
+      items[f + t] = it;
+    }
+  }
+  if (tid == 0) {
+    const uint32_t n2 = s_cnt[2], n1 = s_cnt[1], n = n2 + n1 + s_cnt[0];
+    const uint32_t ends[5] = {s_err ? 0u : n, s_err ? 0u : n2 + n1, s_err ? 0u : n2, 0u, 0u};  // items: class 2, 1, 0
     StepRange* r = reinterpret_cast<StepRange*>(base + kOffRange);
-    r->begin[2] = 0;
-    r->end[2] = cnt[2];
-    r->begin[1] = cnt[2];
-    r->end[1] = cnt[2] + cnt[1];
-    r->begin[0] = cnt[2] + cnt[1];
-    r->end[0] = n;
-    r->begin[3] = r->end[3] = n;
-    r->begin[4] = r->end[4] = 0;
+    for (int c = 0; c < 5; ++c) {
+      r->begin[c] = c < 2 ? ends[c + 1] : 0u;
+      r->end[c] = ends[c];
+    }
     r->plain_pairs = 0;
-    if (s_err) na_empty_ranges(base);
     StepCtl* ctl = reinterpret_cast<StepCtl*>(base + kOffCtl);
     ctl->step = 0;
     ctl->next_step = 0;
     ctl->stride = 0;
     ctl->pad = 0;
     for (int c = 0; c < 4; ++c) ctl->cursor[c] = 0;
-    *na_err(base) = s_err;
-  }
-  __syncthreads();
-  if (s_err) return;
-  const uint32_t C = s_C;
-  for (uint32_t g = 0; g < G; ++g) {
-    const uint32_t f = s_first[g], ni = s_first[g + 1] - f, c0 = kLanes * g + 1;
-    for (uint32_t t = tid; t < ni; t += kNaPlanThreads) {
-      ItemDesc it;
-      it.group = g;
-      it.c0 = c0 + t * C;
-      it.c1 = min(k, it.c0 + C);
-      it.pad = 0;
-      items[f + t] = it;
-    }
+    na_check(base)->lengths = s_err;
+    na_check(base)->begun = na_check(base)->ended + 1;
   }
 }
 
-// A workgroup per sequence: its column stream and its match masks
-// (bit p of PM[c][w] set iff residue 32 w + p equals c; zero past the end).
-__global__ __launch_bounds__(256) void na_stage_kernel(const uint8_t* __restrict__ codes,
-                                                       const uint64_t* __restrict__ seq_off, uint32_t sigma,
-                                                       uint8_t* __restrict__ base) {
-  if (*na_err(base)) return;  // lengths or offsets were rejected: nothing to stage
-  const uint32_t s = blockIdx.x, tid = threadIdx.x;
-  const uint32_t L = reinterpret_cast<const uint32_t*>(base + kOffLen)[s];
-  const uint8_t* src = codes + seq_off[s];
+// A sequence's column stream and match masks (bit p of PM[c][w] set iff
+// residue 32 w + p equals c; zero past the end), by `kNaTeam` threads: a wave
+// takes 64 residues, and one ballot a code is two mask words.  A thread a word
+// compared its 32 residues with every code: 40 us for 8,192 sequences of 300.
+// A code outside the alphabet is marked and staged as code 0, so that the LCS
+// kernels stay within their tables whatever the input.
+__device__ void na_stage(const uint8_t* __restrict__ codes, const uint64_t* __restrict__ seq_off, uint32_t s,
+                         uint32_t sigma, uint32_t maxlen, uint8_t* __restrict__ base) {
+  const uint64_t a = seq_off[s], b = seq_off[s + 1];
+  if (b < a || b - a > maxlen) return;  // the plan rejects it
+  const uint32_t L = (uint32_t)(b - a), W = (L + 31u) >> 5, lane = threadIdx.x & 63u;
+  const uint32_t w0 = (threadIdx.x & (kNaTeam - 1u)) >> 6;
+  const uint8_t* src = codes + a;
   uint16_t* sym = reinterpret_cast<uint16_t*>(base + kOffSym + (size_t)s * kNaSymSlot);
-  bool bad = false;
-  for (uint32_t p = tid; p < L; p += blockDim.x) {
-    const uint32_t c = src[p];
-    bad |= c >= sigma;
-    sym[p] = (uint16_t)(c * 1024u);
-  }
-  const uint32_t W = (L + 31u) >> 5;
-  if (tid < W) {
-    uint32_t cp[32];
-#pragma unroll
-    for (int p = 0; p < 32; ++p) {
-      const uint32_t pos = 32u * tid + (uint32_t)p;
-      cp[p] = pos < L ? (uint32_t)src[pos] : 0xFFFFFFFFu;
+  uint32_t* m = reinterpret_cast<uint32_t*>(base + kOffMasks) + (size_t)s * kNaMaskSlot;
+  for (uint32_t p0 = 64 * w0; p0 < L; p0 += 64 * (kNaTeam / 64)) {
+    const uint32_t p = p0 + lane;
+    uint32_t c = p < L ? (uint32_t)src[p] : 0xFFu;
+    if (p < L && c >= sigma) {
+      atomicOr(&na_check(base)->bad[na_check(base)->ended & 1u], 1u);
+      c = 0;
     }
-    uint32_t* m = reinterpret_cast<uint32_t*>(base + kOffMasks) + (size_t)s * kNaMaskSlot + tid;
-    for (uint32_t c = 0; c < sigma; ++c) {
-      uint32_t x = 0;
-#pragma unroll
-      for (int p = 0; p < 32; ++p) x |= (cp[p] == c ? 1u : 0u) << p;
-      m[(size_t)c * W] = x;
+    if (p < L) sym[p] = (uint16_t)(c * 1024u);
+    uint64_t mine = 0;  // lane c: the residues that equal code c
+    for (uint32_t x = 0; x < sigma; ++x) {
+      const uint64_t eq = __ballot(c == x);
+      mine = lane == x ? eq : mine;
     }
-  }
-  if (bad) {  // a code outside the alphabet: no LCS kernel may run
-    atomicOr(na_err(base), 2u);
-    na_empty_ranges(base);
+    const uint32_t w = p0 >> 5;
+    if (lane < sigma) {
+      m[(size_t)lane * W + w] = (uint32_t)mine;
+      if (w + 1 < W) m[(size_t)lane * W + w + 1] = (uint32_t)(mine >> 32);
+    }
   }
 }
 
-__global__ __launch_bounds__(256) void na_finish_kernel(const uint8_t* __restrict__ base, int32_t* __restrict__ out,
+__global__ __launch_bounds__(kNaThreads) void na_prep_kernel(const uint8_t* __restrict__ codes,
+                                                             const uint64_t* __restrict__ seq_off, uint32_t k,
+                                                             uint32_t sigma, uint32_t maxlen,
+                                                             uint8_t* __restrict__ base) {
+  if (blockIdx.x == 0) {
+    na_plan(seq_off, k, maxlen, base);
+  } else {
+    const uint32_t s = (blockIdx.x - 1) * (kNaThreads / kNaTeam) + threadIdx.x / kNaTeam;
+    if (s < k) na_stage(codes, seq_off, s, sigma, maxlen, base);
+  }
+}
+
+__global__ __launch_bounds__(256) void na_finish_kernel(uint8_t* __restrict__ base, int32_t* __restrict__ out,
                                                         uint64_t npairs, int32_t* __restrict__ status) {
-  const uint32_t e = *reinterpret_cast<const uint32_t*>(base + kOffErr);
-  if (blockIdx.x == 0 && threadIdx.x == 0 && status) *status = e ? FAMSA_LCS_EINVAL : FAMSA_LCS_OK;
-  if (!e) return;
+  const uint32_t fail = na_check(base)->failed();
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (status) *status = fail ? FAMSA_LCS_EINVAL : FAMSA_LCS_OK;
+    na_check(base)->end();
+  }
+  if (!fail) return;
   const uint64_t n = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p < npairs; p += n) out[p] = -1;
 }
@@ -295,6 +319,8 @@ int na_setup(int device, NaDevice** out) {
         d.blocks[s][c] = (uint32_t)n * (uint32_t)cus;
         d.waves[s][c] = waves;
       }
+      const int e = small_prepare(sigma, na_qcap(s, 2));
+      if (e) return set_error(FAMSA_LCS_EDEVICE, "small-step kernel setup for sigma %u failed", sigma);
     }
     d.ptr = static_cast<uint8_t*>(p);
     d.cus = cus;
@@ -312,12 +338,10 @@ int na_run(const uint8_t* codes, const uint64_t* seq_off, uint32_t nseq, uint32_
   uint8_t* base = d->ptr;
   const int s32 = sig_cap(sigma) == 32 ? 1 : 0;
   const uint32_t maxlen = s32 ? kNaMaxLen32 : kNaMaxLen20;
-  hipLaunchKernelGGL(na_plan_kernel, dim3(1), dim3(kNaPlanThreads), 0, st, seq_off, nseq, maxlen, base);
+  const uint32_t per = kNaThreads / kNaTeam;
+  hipLaunchKernelGGL(na_prep_kernel, dim3(1 + (nseq + per - 1) / per), dim3(kNaThreads), 0, st, codes, seq_off, nseq,
+                     sigma, maxlen, base);
   FAMSA_HIP(hipGetLastError());
-  if (nseq) {
-    hipLaunchKernelGGL(na_stage_kernel, dim3(nseq), dim3(256), 0, st, codes, seq_off, sigma, base);
-    FAMSA_HIP(hipGetLastError());
-  }
   const uint64_t npairs = (uint64_t)nseq * (nseq ? nseq - 1 : 0) / 2;
   if (npairs) {
     DeviceBatch b{};
@@ -335,12 +359,22 @@ int na_run(const uint8_t* codes, const uint64_t* seq_off, uint32_t nseq, uint32_
     w.rowbase = reinterpret_cast<const uint64_t*>(base + kOffRowbase);
     w.ranges = reinterpret_cast<const StepRange*>(base + kOffRange);
     StepCtl* ctl = reinterpret_cast<StepCtl*>(base + kOffCtl);
+    uint32_t n = 0;  // items: their number does not depend on the lengths
+    for (uint32_t g = 0; g * kLanes + 1 < nseq; ++g) n += na_items(nseq, g);
+    if (n > kNaMaxItems) return set_error(FAMSA_LCS_EINVAL, "%u work items", n);  // never: 8,192 sequences give 5,986
+    if (n <= 2u * (uint32_t)d->cus) {  // as the plan path's small steps; the widest group is not known here
+      const int e = launch_small(b, w, ctl, out, sigma, na_qcap(s32, 2), std::min(n, (uint32_t)d->cus),
+                                 std::min(16u, na_run(nseq, 0)), na_check(base), status, npairs, st);
+      if (e) return set_error(FAMSA_LCS_EDEVICE, "lcs_small launch failed: %s", hipGetErrorString((hipError_t)e));
+      return 0;
+    }
     for (int c = 2; c >= 0; --c) {  // heaviest class first; a class with no items returns at once
-      const int e = launch_fast(c, b, w, ctl, out, sigma, na_qcap(s32, c), d->blocks[s32][c], d->waves[s32][c], st);
+      const int e = launch_fast(c, b, w, ctl, out, sigma, na_qcap(s32, c), std::min(n, d->blocks[s32][c]),
+                                d->waves[s32][c], st);
       if (e) return set_error(FAMSA_LCS_EDEVICE, "lcs_fast<%d> launch failed: %s", c, hipGetErrorString((hipError_t)e));
     }
   }
-  hipLaunchKernelGGL(na_finish_kernel, dim3(256), dim3(256), 0, st, base, out, npairs, status);
+  hipLaunchKernelGGL(na_finish_kernel, dim3(npairs ? 256 : 1), dim3(256), 0, st, base, out, npairs, status);
   FAMSA_HIP(hipGetLastError());
   return 0;
 }

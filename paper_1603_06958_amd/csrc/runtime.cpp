@@ -542,6 +542,19 @@ void build_step(WorkLists& wl, const std::vector<StepFamily>& fams, const std::v
     r.end[c] = (uint32_t)wl.items.size();
     wl.max_items[c] = std::max(wl.max_items[c], r.end[c] - r.begin[c]);
   }
+  // A step with at most two items a CU takes about as long as its longest
+  // column in every class it launches, so its classes share one launch (which
+  // holds one workgroup a CU, for its LDS is the widest group's).
+  uint32_t fast_items = 0, classes = 0, widest_run = 4;
+  for (int c = 0; c < 3; ++c) {
+    fast_items += r.end[c] - r.begin[c];
+    classes += r.end[c] > r.begin[c];
+    for (const CostItem& x : ci[c]) widest_run = std::max(widest_run, x.it.c1 - x.it.c0);
+  }
+  if (classes > 1 && fast_items <= 2 * kSlots) {
+    sig.small = (uint8_t)std::min<uint32_t>(16, widest_run);
+    wl.max_small_items = std::max(wl.max_small_items, fast_items);
+  }
   r.begin[4] = (uint32_t)wl.prows.size();
   wl.prows.insert(wl.prows.end(), pr.begin(), pr.end());
   r.end[4] = (uint32_t)wl.prows.size();
@@ -590,6 +603,15 @@ int StepExec::prepare(int ncu, const LaunchParams& lp, const WorkLists& wl, uint
   sigma = sig;
   cus = ncu;
   for (int c = 0; c < 4; ++c) items[c] = wl.max_items[c];
+  small_items = wl.max_small_items;
+  if (small_items) {
+    uint32_t q = 0;
+    for (const StepSig& s : wl.sigs)
+      if (s.small) q = std::max<uint32_t>(q, s.widest());
+    const int e = small_prepare(sigma, q);
+    if (e) return set_error(FAMSA_LCS_EDEVICE, "small-step kernel setup (sigma %u, %u quads) failed: %s", sigma, q,
+                            hipGetErrorString((hipError_t)e));
+  }
   for (int c = 0; c < 3; ++c) {
     qmax[c] = wl.qmax[c];
     waves[c] = lp.waves[c];
@@ -646,7 +668,21 @@ int StepExec::enqueue(const StepSig& sig, const DeviceBatch& b, const DeviceWork
     if (e) return set_error(FAMSA_LCS_EDEVICE, "lcs_long launch failed: %s", hipGetErrorString((hipError_t)e));
     if (ev) FAMSA_HIP(hipEventRecord(ev[7], s));
   }
-  for (int c = 2; c >= 0; --c) {
+  if (sig.small) {  // timed as the widest class
+    bool timed = false;
+    for (int c = 2; c >= 0; --c) {
+      if (!sig.q[c]) continue;
+      if (ev) FAMSA_HIP(hipEventRecord(ev[2 * c], s));
+      if (!timed) {
+        timed = true;
+        e = launch_small(b, w, ctl, out, sigma, sig.widest(), std::min((uint32_t)cus, small_items), sig.small, nullptr,
+                         nullptr, 0, s);
+        if (e) return set_error(FAMSA_LCS_EDEVICE, "lcs_small launch failed: %s", hipGetErrorString((hipError_t)e));
+      }
+      if (ev) FAMSA_HIP(hipEventRecord(ev[2 * c + 1], s));
+    }
+  }
+  for (int c = 2; c >= 0 && !sig.small; --c) {
     const uint32_t q = sig.q[c];
     if (!q) continue;
     if (q >= 8 || !bpc[c][q]) return set_error(FAMSA_LCS_EDEVICE, "fast kernel %d was not prepared for %u quads", c, q);

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -156,9 +157,11 @@ uint32_t skew_lanes(uint32_t W, uint32_t sigma, const LaunchParams& lp);
 struct StepSig {
   uint8_t q[3] = {0, 0, 0};
   uint8_t lng = 0, plain = 0;
+  uint8_t small = 0;  // waves a workgroup of the one launch that takes classes 2, 1 and 0 together, 0: a launch each
+  uint8_t widest() const { return std::max(q[0], std::max(q[1], q[2])); }
   uint64_t key() const {
     return (uint64_t)q[0] | ((uint64_t)q[1] << 8) | ((uint64_t)q[2] << 16) | ((uint64_t)lng << 24) |
-           ((uint64_t)plain << 32);
+           ((uint64_t)plain << 32) | ((uint64_t)small << 40);
   }
   bool has(int c) const { return c < 3 ? q[c] != 0 : (c == 3 ? lng != 0 : plain != 0); }
 };
@@ -180,6 +183,7 @@ struct WorkLists {
   uint64_t cells[5] = {0, 0, 0, 0, 0};
   uint64_t max_plain_pairs = 0;
   uint32_t max_items[4] = {0, 0, 0, 0};  // most items of a class in a step
+  uint32_t max_small_items = 0;          // most items of a step whose classes share a launch
 };
 
 struct FamilyRef {
@@ -240,6 +244,7 @@ struct StepExec {
   uint32_t bpc[3][8] = {};             // resident workgroups per CU for fast class c at q quads
   uint32_t blocks[4] = {0, 0, 0, 0};   // [3]: long-row kernel grid
   uint32_t items[4] = {0, 0, 0, 0};    // most items of a class in a step: no more workgroups are launched
+  uint32_t small_items = 0;            // and of a step whose classes share a launch
   int cus = 256;
   bool has_long = false;
   uint32_t carry_words = 0;            // per lane, for the longest column of a long-row item
