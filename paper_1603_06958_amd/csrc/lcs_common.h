@@ -1,9 +1,8 @@
 // Internal descriptors shared by the HIP kernels and the host runtime.
 //
 // Device layout of a batch (built once per plan or serving job):
-//   codes   : every sequence starts at a 32-byte aligned offset dev_off[s]
-//             and is zero-padded to a multiple of 32 bytes, so whole 16- and
-//             32-byte chunks can be read past the last residue.
+//   codes   : the residues, sequences back to back as the caller gave them;
+//             sequence s starts at byte dev_off[s].
 //   len     : residues per sequence (uint32).
 //   masks   : per-symbol match bit masks of the bit-parallel LCS method
 //             (paper, Methods, "Pairwise similarities calculation": w cells
@@ -36,7 +35,6 @@ namespace famsa {
 constexpr int kLanes = 64;        // wavefront size on gfx950
 constexpr int kNumClasses = 5;    // 0..2 fast kernels by row length, 3 segmented long-row kernel, 4 plain kernel
 constexpr int kClassQMax[3] = {2, 3, 7};   // 128-bit mask quads per lane covered by classes 0..2 (W <= 8, 12, 28)
-constexpr int kSeqAlign = 32;     // device code padding / alignment (bytes)
 constexpr size_t kMaxLds = 163840;  // LDS bytes per workgroup on gfx950 (capped by the device's own limit)
 extern size_t g_max_lds;          // min(kMaxLds, device limit), set when a plan or server opens a device
 constexpr size_t kLdsReserve = 64; // static LDS of the fast kernels (queue slots) fits in this
@@ -154,8 +152,9 @@ struct DeviceWork {         // descriptor arrays of a plan (all steps) or of one
 };
 
 // ---- launch wrappers (lcs_kernels.hip) ----
-int launch_build_masks(const DeviceBatch& b, const uint64_t* d_wprefix, uint32_t nseq, uint64_t total_words,
-                       uint32_t sigma, uint32_t* d_masks, void* stream);
+// Column streams and masks of a batch of nseq sequences, from its codes.
+int launch_stage_batch(const DeviceBatch& b, uint32_t nseq, uint32_t max_len, uint32_t sigma, uint8_t* d_sym,
+                       uint32_t* d_masks, void* stream);
 int launch_step_begin(StepCtl* ctl, void* stream);
 // Fast kernel for length class cls (0..2): persistent, `blocks` workgroups of
 // `waves` wavefronts each.

@@ -13,7 +13,7 @@
 // It is exact: every kernel below returns the DP value bit for bit.
 //
 // Three kernels:
-//  * build_masks   -- PM[c][w] for every sequence (one thread per dword).
+//  * stage_batch   -- column streams and PM[c][w] of every sequence.
 //  * lcs_fast<cls> -- one wavefront handles 64 rows (one per lane) against a
 //    single column sequence, so the column symbol is wave-uniform; each lane
 //    reads its row's mask dwords for that symbol from LDS with 128-bit reads
@@ -36,37 +36,44 @@
 
 namespace famsa {
 
-// ------------------------------------------------------------ mask build
+// ------------------------------------------------------------ batch staging
 
-__global__ __launch_bounds__(256) void build_masks_kernel(
-    const uint8_t* __restrict__ codes, const uint64_t* __restrict__ dev_off, const uint32_t* __restrict__ len,
-    const uint64_t* __restrict__ mask_off, const uint64_t* __restrict__ wprefix, uint32_t nseq,
-    uint64_t total_words, uint32_t sigma, uint32_t* __restrict__ masks) {
-  const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= total_words) return;
-  // last sequence whose first word index is <= g (empty sequences own no words)
-  uint32_t lo = 0, hi = nseq;
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (wprefix[mid] <= g) lo = mid; else hi = mid;
-  }
-  const uint32_t s = lo;
-  const uint32_t w = (uint32_t)(g - wprefix[s]);
-  const uint32_t Ws = (uint32_t)(wprefix[s + 1] - wprefix[s]);
-  const uint32_t L = len[s];
-  const uint32_t nvalid = min(32u, L - 32u * w);
-  const uint4* src = reinterpret_cast<const uint4*>(codes + dev_off[s] + 32ull * w);  // 32-byte aligned, padded
-  const uint4 q0 = src[0], q1 = src[1];
-  const uint32_t d[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
-  uint32_t sym[32];
-#pragma unroll
-  for (int p = 0; p < 32; ++p) sym[p] = (p < (int)nvalid) ? ((d[p >> 2] >> (8 * (p & 3))) & 0xFFu) : 0xFFFFFFFFu;
-  uint32_t* dst = masks + mask_off[s] + w;
-  for (uint32_t c = 0; c < sigma; ++c) {
-    uint32_t m = 0;
-#pragma unroll
-    for (int p = 0; p < 32; ++p) m |= (sym[p] == c ? 1u : 0u) << p;
-    dst[(uint64_t)c * Ws] = m;
+// A batch's column streams and match masks from its codes: four waves take 64
+// residues each of a sequence, in rounds of 256, kStageSpan residues a
+// workgroup (blockIdx.y picks which).  A wave's 64 residues are two mask words
+// of every code, and one ballot a code makes both.  The host built the streams
+// (twice the codes' bytes) and padded copies of the codes before, in seven
+// uploads; a thread a word then compared its 32 residues with every code.
+constexpr uint32_t kStageSpan = 4096;
+
+__global__ __launch_bounds__(256) void stage_batch_kernel(const uint8_t* __restrict__ codes,
+                                                          const uint64_t* __restrict__ dev_off,
+                                                          const uint32_t* __restrict__ len,
+                                                          const uint64_t* __restrict__ sym_off,
+                                                          const uint64_t* __restrict__ mask_off, uint32_t sigma,
+                                                          uint8_t* __restrict__ sym, uint32_t* __restrict__ masks) {
+  const uint32_t s = blockIdx.x, lane = threadIdx.x & 63u;
+  const uint32_t L = len[s], W = (L + 31u) >> 5;
+  const uint32_t padded = 8u * ((L + 7u) / 8u + 1u);  // the stream's last chunk is spare, and zero
+  const uint32_t lo = blockIdx.y * kStageSpan, hi = min(padded, lo + kStageSpan);
+  const uint8_t* src = codes + dev_off[s];
+  uint16_t* dst = reinterpret_cast<uint16_t*>(sym + sym_off[s]);
+  uint32_t* m = masks + mask_off[s];
+  for (uint32_t p0 = lo + 64u * (threadIdx.x >> 6); p0 < hi; p0 += 256) {
+    const uint32_t p = p0 + lane;
+    const uint32_t c = p < L ? (uint32_t)src[p] : 0xFFu;
+    if (p < padded) dst[p] = p < L ? (uint16_t)(c * 1024u) : (uint16_t)0;
+    if (p0 >= L) continue;
+    uint64_t mine = 0;  // lane c: the residues that equal code c
+    for (uint32_t x = 0; x < sigma; ++x) {
+      const uint64_t eq = __ballot(c == x);
+      mine = lane == x ? eq : mine;
+    }
+    const uint32_t w = p0 >> 5;
+    if (lane < sigma) {
+      m[(uint64_t)lane * W + w] = (uint32_t)mine;
+      if (w + 1 < W) m[(uint64_t)lane * W + w + 1] = (uint32_t)(mine >> 32);
+    }
   }
 }
 
@@ -782,12 +789,12 @@ static inline int hip_ok(hipError_t e) { return e == hipSuccess ? 0 : (int)e; }
 
 size_t g_max_lds = kMaxLds;
 
-int launch_build_masks(const DeviceBatch& b, const uint64_t* d_wprefix, uint32_t nseq, uint64_t total_words,
-                       uint32_t sigma, uint32_t* d_masks, void* stream) {
-  if (total_words == 0) return 0;
-  const uint64_t blocks = (total_words + 255) / 256;
-  hipLaunchKernelGGL(build_masks_kernel, dim3((uint32_t)blocks), dim3(256), 0, (hipStream_t)stream, b.codes,
-                     b.dev_off, b.len, b.mask_off, d_wprefix, nseq, total_words, sigma, d_masks);
+int launch_stage_batch(const DeviceBatch& b, uint32_t nseq, uint32_t max_len, uint32_t sigma, uint8_t* d_sym,
+                       uint32_t* d_masks, void* stream) {
+  if (nseq == 0) return 0;
+  const uint32_t spans = (8u * ((max_len + 7u) / 8u + 1u) + kStageSpan - 1) / kStageSpan;
+  hipLaunchKernelGGL(stage_batch_kernel, dim3(nseq, spans), dim3(256), 0, (hipStream_t)stream, b.codes, b.dev_off,
+                     b.len, b.sym_off, b.mask_off, sigma, d_sym, d_masks);
   return hip_ok(hipGetLastError());
 }
 

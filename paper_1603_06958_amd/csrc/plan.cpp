@@ -41,7 +41,8 @@ struct famsa_lcs_plan_s {
   WorkLists wl;
   LaunchParams lp;
   StepExec exec;
-  DevMem d_groups, d_lanes, d_items, d_prows, d_colmap, d_rowbase, d_ranges, d_ctl;
+  PackedWork pw;  // offsets of the descriptor arrays in d_work (its host bytes are not kept)
+  DevMem d_work, d_ctl;
   DevMem d_plainwork[2];  // per buffer slot: with two compute streams the slots' steps run concurrently
   DevMem d_carry[2];      // long-row carry scratch, per compute stream
   DevMem d_out[2];
@@ -57,9 +58,7 @@ struct famsa_lcs_plan_s {
   uint64_t pairs = 0, cells = 0;
 
   DeviceWork work() const {
-    return DeviceWork{d_groups.as<GroupDesc>(), d_lanes.as<LaneDesc>(), d_items.as<ItemDesc>(),
-                      d_prows.as<PlainRow>(), d_colmap.as<uint32_t>(), d_rowbase.as<uint64_t>(),
-                      d_ranges.as<StepRange>()};
+    return pw.view(d_work);
   }
   StepCtl* ctl(int slot) const { return d_ctl.as<StepCtl>() + slot; }
   bool plain() const { return opt.flags & FAMSA_LCS_PLAIN; }
@@ -283,13 +282,11 @@ int famsa_lcs_plan_s::enqueue_step(uint64_t s, int slot, bool timed) {
 }
 
 int famsa_lcs_plan_s::upload_work() {
-  hipStream_t s = cs[0];
-  int rc;
-  if ((rc = upload(d_groups, wl.groups, s)) || (rc = upload(d_lanes, wl.lanes, s)) || (rc = upload(d_items, wl.items, s)) ||
-      (rc = upload(d_prows, wl.prows, s)) || (rc = upload(d_colmap, wl.colmap, s)) ||
-      (rc = upload(d_rowbase, wl.rowbase, s)) || (rc = upload(d_ranges, wl.ranges, s)))
-    return rc;
-  FAMSA_HIP(hipStreamSynchronize(s));
+  pw.pack(wl);
+  const int rc = upload(d_work, pw.p.bytes, cs[0]);
+  if (rc) return rc;
+  FAMSA_HIP(hipStreamSynchronize(cs[0]));
+  std::vector<uint8_t>().swap(pw.p.bytes);
   return 0;
 }
 
@@ -316,19 +313,17 @@ int famsa_lcs_plan_s::autotune(const char* path) {
     }
     fams.back().tiles.push_back(TileWork{fb, k, tl.r0, tl.r1, tl.out_off});
   }
-  DevMem tg, tl_, ti, tp, tc, tr, tra;
+  DevMem tw;
+  PackedWork tp;
   for (uint32_t cols : kCols) {
     LaunchParams cand = lp;
     cand.cols_per_item = cols;
     WorkLists w1;
     build_step(w1, fams, batch.h_len, batch.h_lenprefix, opt.sigma, cand, false);
     int rc;
-    if ((rc = upload(tg, w1.groups, st)) || (rc = upload(tl_, w1.lanes, st)) || (rc = upload(ti, w1.items, st)) ||
-        (rc = upload(tp, w1.prows, st)) || (rc = upload(tc, w1.colmap, st)) || (rc = upload(tr, w1.rowbase, st)) ||
-        (rc = upload(tra, w1.ranges, st)))
-      return rc;
-    const DeviceWork w{tg.as<GroupDesc>(), tl_.as<LaneDesc>(), ti.as<ItemDesc>(), tp.as<PlainRow>(), tc.as<uint32_t>(),
-                       tr.as<uint64_t>(), tra.as<StepRange>()};
+    tp.pack(w1);
+    if ((rc = upload(tw, tp.p.bytes, st))) return rc;
+    const DeviceWork w = tp.view(tw);
     double total = 0;
     for (int c = 0; c < 3; ++c) {
       if (!w1.qmax[c]) continue;
@@ -385,12 +380,9 @@ int famsa_lcs_plan_s::autotune(const char* path) {
       build_step(w1, fams, batch.h_len, batch.h_lenprefix, opt.sigma, cand, false);
       if (!w1.has_long) break;  // the first step has no long rows: nothing to choose
       int rc;
-      if ((rc = upload(tg, w1.groups, st)) || (rc = upload(tl_, w1.lanes, st)) || (rc = upload(ti, w1.items, st)) ||
-          (rc = upload(tp, w1.prows, st)) || (rc = upload(tc, w1.colmap, st)) || (rc = upload(tr, w1.rowbase, st)) ||
-          (rc = upload(tra, w1.ranges, st)))
-        return rc;
-      const DeviceWork w{tg.as<GroupDesc>(), tl_.as<LaneDesc>(), ti.as<ItemDesc>(), tp.as<PlainRow>(),
-                         tc.as<uint32_t>(), tr.as<uint64_t>(), tra.as<StepRange>()};
+      tp.pack(w1);
+      if ((rc = upload(tw, tp.p.bytes, st))) return rc;
+      const DeviceWork w = tp.view(tw);
       for (uint32_t wv : {16u, 8u}) {
         int bpc = 0;
         if (long_prepare(opt.sigma, wv, &bpc) || bpc == 0) continue;
@@ -704,8 +696,7 @@ int famsa_lcs_plan_get_info(const famsa_lcs_plan_t* p, famsa_lcs_plan_info* info
   info->nsteps = p->steps.size();
   info->pairs = p->pairs;
   info->cells = p->cells;
-  info->device_bytes = p->batch.bytes + p->d_groups.bytes + p->d_lanes.bytes + p->d_items.bytes + p->d_prows.bytes +
-                       p->d_colmap.bytes + p->d_rowbase.bytes + p->d_ranges.bytes + p->d_ctl.bytes +
+  info->device_bytes = p->batch.bytes + p->d_work.bytes + p->d_ctl.bytes +
                        p->d_plainwork[0].bytes + p->d_plainwork[1].bytes + p->d_carry[0].bytes + p->d_carry[1].bytes + p->d_out[0].bytes + p->d_out[1].bytes;
   info->pinned_bytes = p->h_out[0].bytes + p->h_out[1].bytes;
   for (const auto& t : p->tiles) info->max_tile_values = std::max(info->max_tile_values, t.count);

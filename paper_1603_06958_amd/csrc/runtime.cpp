@@ -151,16 +151,18 @@ DeviceBatch DeviceBatchOwner::view() const {
 static inline uint64_t round_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 
 namespace {
-// Parts of a batch's device allocation, in bytes, from the code bytes (each
-// sequence padded to 32), the stream bytes and the mask dwords.
+// Parts of a batch's device allocation, in bytes, from the residues, the
+// stream bytes and the mask dwords: what is uploaded first (offsets, lengths,
+// codes), then what the GPU makes of it.
 struct BatchLayout {
-  uint64_t off[8], total;
-  BatchLayout(uint64_t cb, uint64_t sb, uint64_t mw, uint32_t n) {
-    const uint64_t sz[8] = {cb + 32, 8ull * (n + 1), 4ull * std::max<uint32_t>(n, 1), 8ull * (n + 1),
-                            8ull * (n + 1), std::max<uint64_t>(sb, 16), 8ull * (n + 1), mw * 4 + 16};
-    total = 0;
-    for (int i = 0; i < 8; ++i) {
+  uint64_t off[7], upload, total;
+  BatchLayout(uint64_t residues, uint64_t sb, uint64_t mw, uint32_t n) {
+    const uint64_t sz[7] = {8ull * (n + 1), 8ull * (n + 1), 8ull * (n + 1), 4ull * std::max<uint32_t>(n, 1),
+                            residues + 16, std::max<uint64_t>(sb, 16), mw * 4 + 16};
+    total = upload = 0;
+    for (int i = 0; i < 7; ++i) {
       off[i] = total;
+      if (i < 5) upload = total + sz[i];
       total += round_up(sz[i], 256);
     }
   }
@@ -168,14 +170,13 @@ struct BatchLayout {
 }  // namespace
 
 uint64_t DeviceBatchOwner::footprint(const uint64_t* seq_off, uint32_t nseq, uint32_t sigma) {
-  uint64_t cb = 0, words = 0, sb = 0;
+  uint64_t words = 0, sb = 0;
   for (uint32_t i = 0; i < nseq; ++i) {
     const uint64_t L = seq_off[i + 1] - seq_off[i];
-    cb += round_up(L, kSeqAlign);
     words += (L + 31) / 32;
     sb += ((L + 7) / 8 + 1) * 16;
   }
-  return BatchLayout(cb, sb, words * sigma, nseq).total;
+  return BatchLayout(nseq ? seq_off[nseq] - seq_off[0] : 0, sb, words * sigma, nseq).total;
 }
 
 int DeviceBatchOwner::create(const uint8_t* hcodes, const uint64_t* seq_off, uint32_t n, uint32_t sig,
@@ -184,76 +185,51 @@ int DeviceBatchOwner::create(const uint8_t* hcodes, const uint64_t* seq_off, uin
   sigma = sig;
   h_len.resize(n);
   h_lenprefix.assign(n + 1, 0);
-  std::vector<uint64_t> hoff(n + 1), hmo(n + 1), hwp(n + 1);
-  uint64_t cb = 0, mw = 0, words = 0;
+  h_dev_off.resize(n + 1);
+  h_mask_off.resize(n + 1);
+  h_sym_off.resize(n + 1);
+  uint64_t mw = 0, sb = 0;
+  const uint64_t base0 = n ? seq_off[0] : 0, residues = n ? seq_off[n] - base0 : 0;
   max_len = 0;
   for (uint32_t i = 0; i < n; ++i) {
     const uint32_t L = (uint32_t)(seq_off[i + 1] - seq_off[i]);
     h_len[i] = L;
     h_lenprefix[i + 1] = h_lenprefix[i] + L;
     max_len = std::max(max_len, L);
-    hoff[i] = cb;
-    cb += round_up(L, kSeqAlign);
-    const uint64_t W = (L + 31) / 32;
-    hmo[i] = mw;
-    mw += W * sigma;
-    hwp[i] = words;
-    words += W;
+    h_dev_off[i] = seq_off[i] - base0;
+    h_mask_off[i] = mw;
+    mw += (uint64_t)((L + 31) / 32) * sigma;
+    h_sym_off[i] = sb;  // ceil(L/8) 16-byte chunks plus one spare
+    sb += ((uint64_t)(L + 7) / 8 + 1) * 16;
   }
-  hoff[n] = cb;
-  hmo[n] = mw;
-  hwp[n] = words;
-  std::vector<uint8_t> packed(cb + 32, 0);
-  for (uint32_t i = 0; i < n; ++i)
-    if (h_len[i]) memcpy(packed.data() + hoff[i], hcodes + seq_off[i], h_len[i]);
-  // column streams: residue c as uint16 c * 1024, ceil(L/8) 16-byte chunks plus one spare
-  h_sym_off.assign(n + 1, 0);
-  uint64_t sb = 0;
-  for (uint32_t i = 0; i < n; ++i) {
-    h_sym_off[i] = sb;
-    sb += ((uint64_t)(h_len[i] + 7) / 8 + 1) * 16;
-  }
+  h_dev_off[n] = residues;
+  h_mask_off[n] = mw;
   h_sym_off[n] = sb;
-  std::vector<uint16_t> stream(std::max<uint64_t>(sb, 16) / 2, 0);
-  for (uint32_t i = 0; i < n; ++i) {
-    uint16_t* d = stream.data() + h_sym_off[i] / 2;
-    const uint8_t* c = hcodes + seq_off[i];
-    for (uint32_t t = 0; t < h_len[i]; ++t) d[t] = (uint16_t)(c[t] * 1024u);
-  }
-  h_dev_off = hoff;
-  h_mask_off = hmo;
-  const BatchLayout lay(cb, sb, mw, n);
+  const BatchLayout lay(residues, sb, mw, n);
   if (mem.bytes < lay.total) {
     const int rc = mem.alloc(lay.total);
     if (rc) return rc;
   }
+  std::vector<uint8_t> up(lay.upload);
+  memcpy(up.data() + lay.off[0], h_dev_off.data(), 8ull * (n + 1));
+  memcpy(up.data() + lay.off[1], h_mask_off.data(), 8ull * (n + 1));
+  memcpy(up.data() + lay.off[2], h_sym_off.data(), 8ull * (n + 1));
+  if (n) memcpy(up.data() + lay.off[3], h_len.data(), 4ull * n);
+  if (residues) memcpy(up.data() + lay.off[4], hcodes + base0, residues);
   uint8_t* base = mem.as<uint8_t>();
-  codes = base + lay.off[0];
-  dev_off = reinterpret_cast<uint64_t*>(base + lay.off[1]);
-  len = reinterpret_cast<uint32_t*>(base + lay.off[2]);
-  mask_off = reinterpret_cast<uint64_t*>(base + lay.off[3]);
-  wprefix = reinterpret_cast<uint64_t*>(base + lay.off[4]);
+  dev_off = reinterpret_cast<uint64_t*>(base + lay.off[0]);
+  mask_off = reinterpret_cast<uint64_t*>(base + lay.off[1]);
+  sym_off = reinterpret_cast<uint64_t*>(base + lay.off[2]);
+  len = reinterpret_cast<uint32_t*>(base + lay.off[3]);
+  codes = base + lay.off[4];
   sym = base + lay.off[5];
-  sym_off = reinterpret_cast<uint64_t*>(base + lay.off[6]);
-  masks = reinterpret_cast<uint32_t*>(base + lay.off[7]);
-  FAMSA_HIP(hipMemcpyAsync(codes, packed.data(), packed.size(), hipMemcpyHostToDevice, s));
-  FAMSA_HIP(hipMemcpyAsync(dev_off, h_dev_off.data(), 8ull * (n + 1), hipMemcpyHostToDevice, s));
-  if (n) FAMSA_HIP(hipMemcpyAsync(len, h_len.data(), 4ull * n, hipMemcpyHostToDevice, s));
-  FAMSA_HIP(hipMemcpyAsync(mask_off, h_mask_off.data(), 8ull * (n + 1), hipMemcpyHostToDevice, s));
-  FAMSA_HIP(hipMemcpyAsync(wprefix, hwp.data(), 8ull * (n + 1), hipMemcpyHostToDevice, s));
-  FAMSA_HIP(hipMemcpyAsync(sym, stream.data(), stream.size() * 2, hipMemcpyHostToDevice, s));
-  FAMSA_HIP(hipMemcpyAsync(sym_off, h_sym_off.data(), 8ull * (n + 1), hipMemcpyHostToDevice, s));
-  const DeviceBatch v = view();
-  int e = launch_build_masks(v, wprefix, n, words, sigma, masks, s);
-  if (e) return set_error(FAMSA_LCS_EDEVICE, "build_masks launch failed: %s", hipGetErrorString((hipError_t)e));
-  if (wait) {
-    // the host sources above are freed on return: wait for the copies
-    FAMSA_HIP(hipStreamSynchronize(s));
-  } else {
-    st_codes.swap(packed);
-    st_sym.swap(stream);
-    st_wprefix.swap(hwp);
-  }
+  masks = reinterpret_cast<uint32_t*>(base + lay.off[6]);
+  FAMSA_HIP(hipMemcpyAsync(base, up.data(), up.size(), hipMemcpyHostToDevice, s));
+  const int e = launch_stage_batch(view(), n, max_len, sigma, sym, masks, s);
+  if (e) return set_error(FAMSA_LCS_EDEVICE, "stage_batch launch failed: %s", hipGetErrorString((hipError_t)e));
+  // the host source is freed on return: wait for the copy, or keep it
+  if (wait) FAMSA_HIP(hipStreamSynchronize(s));
+  else staged.swap(up);
   bytes = mem.bytes;
   return 0;
 }

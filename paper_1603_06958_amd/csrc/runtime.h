@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <string.h>
 
 #include <algorithm>
 #include <string>
@@ -69,6 +70,17 @@ int upload(DevMem& d, const std::vector<T>& h, hipStream_t s) {
   return 0;
 }
 
+// Host arrays gathered for one upload, each part 16-byte aligned.
+struct Packed {
+  std::vector<uint8_t> bytes;
+  template <class T> uint64_t add(const std::vector<T>& v) {
+    const uint64_t at = (bytes.size() + 15) & ~(uint64_t)15;
+    bytes.resize(at + std::max<size_t>(v.size() * sizeof(T), 16));
+    if (!v.empty()) memcpy(bytes.data() + at, v.data(), v.size() * sizeof(T));
+    return at;
+  }
+};
+
 // Normalised options.
 struct Opts {
   uint32_t sigma = 20;
@@ -93,11 +105,10 @@ int validate_batch(const uint8_t* codes, const uint64_t* seq_off, uint32_t nseq,
 // handed to the next job instead of freed.
 struct DeviceBatchOwner {
   DevMem mem;
-  uint8_t* codes = nullptr;      // 32-byte aligned, zero-padded sequences
+  uint8_t* codes = nullptr;      // sequences back to back
   uint64_t* dev_off = nullptr;
   uint32_t* len = nullptr;
   uint64_t* mask_off = nullptr;
-  uint64_t* wprefix = nullptr;   // prefix sums of mask dwords per sequence
   uint8_t* sym = nullptr;        // column streams
   uint64_t* sym_off = nullptr;
   uint32_t* masks = nullptr;
@@ -106,15 +117,13 @@ struct DeviceBatchOwner {
   std::vector<uint64_t> h_dev_off;   // device byte offset of each sequence in `codes`
   std::vector<uint64_t> h_mask_off;  // dword offset of each sequence's masks in `masks`
   std::vector<uint64_t> h_sym_off;   // byte offset of each sequence's column stream in `sym`
-  // host sources of the uploads, kept while they may be in flight (create with wait = false)
-  std::vector<uint8_t> st_codes;
-  std::vector<uint16_t> st_sym;
-  std::vector<uint64_t> st_wprefix;
+  std::vector<uint8_t> staged;  // host source of the upload, kept while it may be in flight (create with wait = false)
   uint32_t nseq = 0, max_len = 0, sigma = 0;
   uint32_t values = FAMSA_LCS_VALUES_LCS;  // tile contents, from the plan's flags
   uint64_t bytes = 0;                      // device bytes held (mem's size)
   DeviceBatch view() const;
-  // Copies the batch (validated) to the device and builds the masks on `s`,
+  // Copies the batch (validated) to the device in one upload and builds the
+  // column streams and masks there, on `s`,
   // reusing `mem` when it is already large enough.  With wait = false the call
   // does not synchronise: the host sources stay in this object, and work
   // ordered on `s` after the call sees the batch.
@@ -184,6 +193,30 @@ struct WorkLists {
   uint64_t max_plain_pairs = 0;
   uint32_t max_items[4] = {0, 0, 0, 0};  // most items of a class in a step
   uint32_t max_small_items = 0;          // most items of a step whose classes share a launch
+};
+
+// The descriptor arrays of `wl` in one buffer: their device view once the
+// bytes are at `base`.
+struct PackedWork {
+  Packed p;
+  uint64_t groups = 0, lanes = 0, items = 0, prows = 0, colmap = 0, rowbase = 0, ranges = 0;
+  void pack(const WorkLists& wl) {
+    p.bytes.clear();
+    groups = p.add(wl.groups);
+    lanes = p.add(wl.lanes);
+    items = p.add(wl.items);
+    prows = p.add(wl.prows);
+    colmap = p.add(wl.colmap);
+    rowbase = p.add(wl.rowbase);
+    ranges = p.add(wl.ranges);
+  }
+  DeviceWork view(const DevMem& m) const {
+    const uint8_t* b = m.as<uint8_t>();
+    return DeviceWork{reinterpret_cast<const GroupDesc*>(b + groups), reinterpret_cast<const LaneDesc*>(b + lanes),
+                      reinterpret_cast<const ItemDesc*>(b + items), reinterpret_cast<const PlainRow*>(b + prows),
+                      reinterpret_cast<const uint32_t*>(b + colmap), reinterpret_cast<const uint64_t*>(b + rowbase),
+                      reinterpret_cast<const StepRange*>(b + ranges)};
+  }
 };
 
 struct FamilyRef {

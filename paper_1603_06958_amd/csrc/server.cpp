@@ -60,8 +60,7 @@ struct StepTile {
 struct Slot {
   DevMem d_out;
   PinMem h_out;
-  DevMem d_groups, d_lanes, d_items, d_prows, d_colmap, d_rowbase, d_ranges, d_devoff, d_len, d_maskoff, d_ctl;
-  DevMem d_symoff;
+  DevMem d_work;  // a step's descriptors, sequence offsets and control block, one upload
   DevMem d_plainwork, d_carry;
   StepExec exec;
   std::vector<StepTile> tiles;
@@ -69,17 +68,6 @@ struct Slot {
   bool busy = false;
   hipEvent_t done = nullptr;
 };
-
-template <class T>
-int upload_grow(DevMem& d, const std::vector<T>& h, hipStream_t s) {
-  const size_t n = std::max<size_t>(h.size() * sizeof(T), 16);
-  if (d.bytes < n) {
-    int rc = d.alloc(n + n / 2);
-    if (rc) return rc;
-  }
-  if (!h.empty()) FAMSA_HIP(hipMemcpyAsync(d.p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice, s));
-  return 0;
-}
 
 }  // namespace
 
@@ -104,6 +92,7 @@ struct famsa_lcs_server_s {
   // host staging kept alive until the step's uploads complete
   struct Staging {
     WorkLists wl;
+    PackedWork pw;
     std::vector<uint64_t> devoff, maskoff, symoff;
     std::vector<uint32_t> len;
   } stage[2];
@@ -241,18 +230,16 @@ int famsa_lcs_server_s::issue(int si) {
   sl.busy = !sl.tiles.empty();
   if (!sl.busy) return 0;
   hipStream_t s = cs;
-  if ((rc = upload_grow(sl.d_groups, st.wl.groups, s)) || (rc = upload_grow(sl.d_lanes, st.wl.lanes, s)) ||
-      (rc = upload_grow(sl.d_items, st.wl.items, s)) || (rc = upload_grow(sl.d_prows, st.wl.prows, s)) ||
-      (rc = upload_grow(sl.d_colmap, st.wl.colmap, s)) || (rc = upload_grow(sl.d_rowbase, st.wl.rowbase, s)) ||
-      (rc = upload_grow(sl.d_ranges, st.wl.ranges, s)) || (rc = upload_grow(sl.d_devoff, st.devoff, s)) ||
-      (rc = upload_grow(sl.d_len, st.len, s)) || (rc = upload_grow(sl.d_maskoff, st.maskoff, s)) ||
-      (rc = upload_grow(sl.d_symoff, st.symoff, s)))
-    return rc;
-  StepCtl hc{};
-  hc.next_step = 0;
-  hc.stride = 1;
-  if (!sl.d_ctl.p && (rc = sl.d_ctl.alloc(sizeof(StepCtl)))) return rc;
-  FAMSA_HIP(hipMemcpyAsync(sl.d_ctl.p, &hc, sizeof hc, hipMemcpyHostToDevice, s));
+  std::vector<StepCtl> ctl(1);
+  ctl[0] = StepCtl{};
+  ctl[0].stride = 1;  // next_step 0: the one step
+  Packed& p = st.pw.p;
+  st.pw.pack(st.wl);
+  const uint64_t o_dev = p.add(st.devoff), o_mask = p.add(st.maskoff), o_sym = p.add(st.symoff), o_len = p.add(st.len),
+                 o_ctl = p.add(ctl);
+  if (sl.d_work.bytes < p.bytes.size() && (rc = sl.d_work.alloc(p.bytes.size() + p.bytes.size() / 2))) return rc;
+  FAMSA_HIP(hipMemcpyAsync(sl.d_work.p, p.bytes.data(), p.bytes.size(), hipMemcpyHostToDevice, s));
+  const uint8_t* dw = sl.d_work.as<uint8_t>();
   if ((rc = sl.exec.prepare(gi.cus, lp, st.wl, opt.sigma))) return rc;
   if (sl.exec.w64max_plain > plain_register_w64_limit()) {
     sl.exec.plain_blocks = std::min<uint32_t>(sl.exec.plain_blocks, (uint32_t)gi.cus * 8u);
@@ -260,14 +247,13 @@ int famsa_lcs_server_s::issue(int si) {
     if (sl.d_plainwork.bytes < need && (rc = sl.d_plainwork.alloc(need))) return rc;
   }
   // codes, sym and masks are null: the step's offsets are absolute device addresses
-  DeviceBatch b{nullptr, sl.d_devoff.as<uint64_t>(),  nullptr, sl.d_symoff.as<uint64_t>(),
-                sl.d_len.as<uint32_t>(), sl.d_maskoff.as<uint64_t>(), nullptr, FAMSA_LCS_VALUES_LCS};
-  DeviceWork w{sl.d_groups.as<GroupDesc>(), sl.d_lanes.as<LaneDesc>(), sl.d_items.as<ItemDesc>(),
-               sl.d_prows.as<PlainRow>(), sl.d_colmap.as<uint32_t>(), sl.d_rowbase.as<uint64_t>(),
-               sl.d_ranges.as<StepRange>()};
+  DeviceBatch b{nullptr, reinterpret_cast<const uint64_t*>(dw + o_dev), nullptr,
+                reinterpret_cast<const uint64_t*>(dw + o_sym), reinterpret_cast<const uint32_t*>(dw + o_len),
+                reinterpret_cast<const uint64_t*>(dw + o_mask), nullptr, FAMSA_LCS_VALUES_LCS};
+  DeviceWork w = st.pw.view(sl.d_work);
   if (sl.exec.has_long && sl.d_carry.bytes < sl.exec.carry_bytes() && (rc = sl.d_carry.alloc(sl.exec.carry_bytes())))
     return rc;
-  if ((rc = sl.exec.enqueue(st.wl.sigs[0], b, w, sl.d_ctl.as<StepCtl>(), sl.d_out.as<int32_t>(),
+  if ((rc = sl.exec.enqueue(st.wl.sigs[0], b, w, reinterpret_cast<StepCtl*>(sl.d_work.as<uint8_t>() + o_ctl), sl.d_out.as<int32_t>(),
                             sl.d_plainwork.as<uint64_t>(), sl.d_carry.as<uint32_t>(), s, nullptr)))
     return rc;
   FAMSA_HIP(hipEventRecord(sl.done, s));
