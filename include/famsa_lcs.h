@@ -360,7 +360,7 @@ int famsa_gapped_width(const famsa_gapped_t* g, uint32_t* width);
 int famsa_gapped_locate(famsa_gapped_t* g, const uint32_t* seq, const uint32_t* col, uint32_t nq, uint32_t* pos);
 /* The gapped rows of sequences first..first+count-1 into host memory: row t
  * (row_bytes apart) gets columns 1..width of sequence first+t, symbol codes
- * and 0xFF for gaps; bytes past the width are left as they were. */
+ * and 0xFF for gaps; bytes past the width are zero. */
 int famsa_gapped_decode(famsa_gapped_t* g, uint32_t first, uint32_t count, uint8_t* out, uint64_t row_bytes);
 /* Copies of sequence s's gap counters (npos entries) and tree (ptree
  * entries, index 0 unused); NULL outputs are skipped. */

@@ -8,7 +8,9 @@ the library is missing: there is no CPU fallback.
 from __future__ import annotations
 
 import ctypes
+import itertools
 import os
+import threading
 from typing import Callable, Dict, Optional, Tuple
 
 import numpy as np
@@ -202,28 +204,55 @@ PROFILE_GAP = 0xFF
 OP_M, OP_D, OP_I = 0, 1, 2
 
 
+_scratch_of = threading.local()
+SCRATCH_BYTES = 64 << 20  # a thread keeps at most this much between calls
+
+
+def _scratch(n: int) -> np.ndarray:
+    """n bytes of this thread's scratch array.  It is kept between calls: the
+    first touch of fresh pages costs more than the copy into them."""
+    a = getattr(_scratch_of, "bytes", None)
+    if a is None or a.size < n:
+        a = np.empty(n, np.uint8)
+        _scratch_of.bytes = a if n <= SCRATCH_BYTES else None
+    return a[:n]
+
+
+def _plain_bytes(arrays) -> bool:
+    """Whether every one is a numpy array of uint8, which needs no conversion."""
+    return set(map(type, arrays)) <= {np.ndarray} and {a.dtype for a in arrays} <= {np.dtype(np.uint8)}
+
+
 def profile_align(problems, subst, gap_costs, alphabet_size: Optional[int] = None, device: int = 0):
     """famsa_profile_align over a list of (sequence, rows) pairs: sequence
     uint8 codes, rows a K x n uint8 array (PROFILE_GAP for gaps).  Returns
     (scores int64 array, list of op arrays)."""
     S = np.ascontiguousarray(subst, dtype=np.int32)
     sigma = int(S.shape[0]) if alphabet_size is None else alphabet_size
-    seqs = [np.ascontiguousarray(a, dtype=np.uint8).reshape(-1) for a, _ in problems]
-    rows = [np.ascontiguousarray(r, dtype=np.uint8) for _, r in problems]
+    seqs = [a for a, _ in problems]
+    rows = [r for _, r in problems]
     n = len(seqs)
+    if not _plain_bytes(seqs):
+        seqs = [np.ascontiguousarray(a, dtype=np.uint8).reshape(-1) for a in seqs]
+    if not _plain_bytes(rows):
+        rows = [np.ascontiguousarray(r, dtype=np.uint8) for r in rows]
+    m = np.array([a.size for a in seqs], np.uint64)
+    shape = np.fromiter(itertools.chain.from_iterable([(r.shape[0], r.shape[1]) for r in rows]), np.int64, 2 * n)
+    nrows, width = shape[0::2].astype(np.uint32), shape[1::2].astype(np.uint32)
     seq_off = np.zeros(n + 1, np.uint64)
-    np.cumsum([x.size for x in seqs], out=seq_off[1:])
+    np.cumsum(m, out=seq_off[1:])
     rows_off = np.zeros(n + 1, np.uint64)
-    np.cumsum([r.size for r in rows], out=rows_off[1:])
-    nrows = np.array([r.shape[0] for r in rows], np.uint32)
-    width = np.array([r.shape[1] for r in rows], np.uint32)
+    np.cumsum(np.array([r.size for r in rows], np.uint64), out=rows_off[1:])
     ops_off = np.zeros(n + 1, np.uint64)
-    np.cumsum([x.size + r.shape[1] for x, r in zip(seqs, rows)], out=ops_off[1:])
-    cat_s = np.concatenate(seqs) if n and int(seq_off[-1]) else np.zeros(1, np.uint8)
-    cat_r = np.concatenate([r.reshape(-1) for r in rows]) if n and int(rows_off[-1]) else np.zeros(1, np.uint8)
+    np.cumsum(m + width, out=ops_off[1:])
+    cat_s = np.concatenate(seqs, axis=None) if n and int(seq_off[-1]) else np.zeros(1, np.uint8)
+    nr = int(rows_off[-1])
+    cat_r = _scratch(max(nr, 1))
+    if nr:
+        np.concatenate(rows, axis=None, out=cat_r)
     costs = np.ascontiguousarray(gap_costs, dtype=np.int64)
     score = np.zeros(max(n, 1), np.int64)
-    ops = np.zeros(max(int(ops_off[-1]), 1), np.uint8)
+    ops = np.empty(max(int(ops_off[-1]), 1), np.uint8)
     nops = np.zeros(max(n, 1), np.uint32)
     check(lib().famsa_profile_align(n, _ptr(cat_s, ctypes.c_uint8), _ptr(seq_off, ctypes.c_uint64),
                                     _ptr(cat_r, ctypes.c_uint8), _ptr(rows_off, ctypes.c_uint64),
@@ -231,7 +260,7 @@ def profile_align(problems, subst, gap_costs, alphabet_size: Optional[int] = Non
                                     _ptr(S, ctypes.c_int32), _ptr(costs, ctypes.c_int64), device,
                                     _ptr(score, ctypes.c_int64), _ptr(ops, ctypes.c_uint8),
                                     _ptr(ops_off, ctypes.c_uint64), _ptr(nops, ctypes.c_uint32)))
-    return score[:n], [ops[int(ops_off[p]):int(ops_off[p]) + int(nops[p])].copy() for p in range(n)]
+    return score[:n], [ops[a:a + k].copy() for a, k in zip(ops_off[:n].tolist(), nops.tolist())]
 
 
 def profile_last_dp_ms() -> float:
@@ -483,11 +512,11 @@ class Gapped:
         return out[:seq.size]
 
     def decode(self, first: int = 0, count: Optional[int] = None) -> np.ndarray:
-        """Rows of symbol codes, 0xFF for gaps (and for padding past a row's width)."""
+        """Rows of symbol codes, 0xFF for gaps, zero past a row's width."""
         count = self.n - first if count is None else count
         w = self.width()[first:first + count]
         rb = int(w.max()) if w.size and w.max() > 0 else 1
-        out = np.full((max(count, 1), rb), 0xFF, np.uint8)
+        out = np.empty((max(count, 1), rb), np.uint8)  # written whole
         check(lib().famsa_gapped_decode(self.handle, first, count, _ptr(out, ctypes.c_uint8), rb))
         return out[:count]
 

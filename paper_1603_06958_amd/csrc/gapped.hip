@@ -143,7 +143,7 @@ __global__ __launch_bounds__(256) void gapped_locate(GappedDev g, const uint32_t
 // One wave per sequence: positions in chunks of 64, their first columns by a
 // wave prefix sum of the spans; each lane writes its symbol and its gap run.
 // Row t of `out` holds columns 1.. of sequence first + t (the guard's column
-// is left out); gaps are 0xFF, and the rest of the row is left as it is.
+// is left out); gaps are 0xFF, and the rest of the row is zero.
 __global__ __launch_bounds__(64) void gapped_decode(GappedDev g, uint32_t first, uint8_t* __restrict__ out,
                                                     uint64_t row_bytes) {
   const uint32_t s = first + blockIdx.x, lane = threadIdx.x;
@@ -167,6 +167,7 @@ __global__ __launch_bounds__(64) void gapped_decode(GappedDev g, uint32_t first,
     }
     base += __shfl(incl, 63, 64);
   }
+  for (uint64_t c = (uint64_t)base - 1 + lane; c < row_bytes; c += 64) row[c] = 0;  // base counts the guard's column
 }
 
 }  // namespace famsa

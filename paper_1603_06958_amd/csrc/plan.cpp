@@ -596,6 +596,7 @@ int famsa_lcs_plan(const uint8_t* codes, const uint64_t* seq_off, uint32_t nseq,
   // budget: batch + descriptors + 2 step buffers (+ plain scratch)
   size_t freeb = 0, totalb = 0;
   if (hipMemGetInfo(&freeb, &totalb) != hipSuccess) return fail(set_error(FAMSA_LCS_EDEVICE, "hipMemGetInfo failed"));
+  freeb += kept_bytes(o.device);
   const uint64_t budget = o.hbm_budget ? o.hbm_budget : (uint64_t)(freeb * 0.9);
   const uint64_t fixed = DeviceBatchOwner::footprint(seq_off, nseq, o.sigma);
   if (fixed > budget) return fail(set_error(FAMSA_LCS_ENOMEM, "batch needs %llu bytes, budget is %llu",

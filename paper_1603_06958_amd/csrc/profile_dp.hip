@@ -824,18 +824,20 @@ extern "C" int famsa_profile_align(uint32_t nprob, const uint8_t* seqs, const ui
     nmax = std::max(nmax, n);
     kmax = std::max(kmax, K);
   }
-  // one device allocation, 256-byte aligned parts
+  // one device allocation, 256-byte aligned parts: what goes up in one copy
+  // (descriptors, scores, sequences), the rows, the GPU's own, and what comes
+  // down in one copy
   uint64_t off = 0;
   auto part = [&](uint64_t bytes) {
     const uint64_t at = off;
     off += up256(bytes ? bytes : 1);
     return at;
   };
-  const uint64_t b_probs = part(sizeof(PdpProb) * nprob), b_subst = part(4ull * sigma * sigma),
-                 b_seqs = part(o_seq), b_rows = part(o_rows), b_cost = part(4 * o_cost),
-                 b_rec = part(sizeof(PdpRec<int64_t>) * o_col), b_first = part(4 * o_rowx),
-                 b_last = part(4 * o_rowx), b_edge = part(sizeof(PdpRec<int64_t>) * o_edge), b_dir = part(o_dir),
-                 b_ops = part(o_ops), b_score = part(8ull * nprob), b_nops = part(4ull * nprob);
+  const uint64_t b_probs = part(sizeof(PdpProb) * nprob), b_subst = part(4ull * sigma * sigma), b_seqs = part(o_seq),
+                 b_rows = part(o_rows), b_cost = part(4 * o_cost), b_rec = part(sizeof(PdpRec<int64_t>) * o_col),
+                 b_first = part(4 * o_rowx), b_last = part(4 * o_rowx),
+                 b_edge = part(sizeof(PdpRec<int64_t>) * o_edge), b_dir = part(o_dir), b_score = part(8ull * nprob),
+                 b_nops = part(4ull * nprob), b_ops = part(o_ops);
   FAMSA_HIP(hipSetDevice(device));
   // LDS: a problem whose records, costs and edge rows fit in half a CU's LDS
   // (so that two problems share a CU) reads them from there; with no more
@@ -888,23 +890,18 @@ extern "C" int famsa_profile_align(uint32_t nprob, const uint8_t* seqs, const ui
   rc = mem.alloc(off);
   if (rc) return rc;
   uint8_t* D = mem.as<uint8_t>();
-  // sequences and rows go up in one copy each when the caller's arrays
-  // already hold them back to back in problem order, else through a packed
-  // host copy
-  bool seq_packed = true, rows_packed = true;
+  std::vector<uint8_t> up(b_seqs + o_seq);
+  memcpy(up.data() + b_probs, launch.data(), sizeof(PdpProb) * nprob);
+  memcpy(up.data() + b_subst, subst, 4ull * sigma * sigma);
+  bool rows_packed = true;
   for (uint32_t p = 0; p < nprob; ++p) {
-    seq_packed = seq_packed && seq_off[p] - seq_off[0] == pr[p].seq;
+    if (pr[p].m) memcpy(up.data() + b_seqs + pr[p].seq, seqs + seq_off[p], pr[p].m);
     rows_packed = rows_packed && rows_off[p] - rows_off[0] == pr[p].rows;
   }
-  std::vector<uint8_t> hseq, hrows;
-  const uint8_t* up_seq = o_seq ? seqs + seq_off[0] : nullptr;
+  // the rows go up from the caller's array when it holds them back to back in
+  // problem order, else through a packed host copy
+  std::vector<uint8_t> hrows;
   const uint8_t* up_rows = o_rows ? rows + rows_off[0] : nullptr;
-  if (o_seq && !seq_packed) {
-    hseq.resize(o_seq);
-    for (uint32_t p = 0; p < nprob; ++p)
-      if (pr[p].m) memcpy(hseq.data() + pr[p].seq, seqs + seq_off[p], pr[p].m);
-    up_seq = hseq.data();
-  }
   if (o_rows && !rows_packed) {
     hrows.resize(o_rows);
     for (uint32_t p = 0; p < nprob; ++p) {
@@ -913,9 +910,7 @@ extern "C" int famsa_profile_align(uint32_t nprob, const uint8_t* seqs, const ui
     }
     up_rows = hrows.data();
   }
-  FAMSA_HIP(hipMemcpyAsync(D + b_probs, launch.data(), sizeof(PdpProb) * nprob, hipMemcpyHostToDevice, st));
-  FAMSA_HIP(hipMemcpyAsync(D + b_subst, subst, 4ull * sigma * sigma, hipMemcpyHostToDevice, st));
-  if (o_seq) FAMSA_HIP(hipMemcpyAsync(D + b_seqs, up_seq, o_seq, hipMemcpyHostToDevice, st));
+  FAMSA_HIP(hipMemcpyAsync(D, up.data(), up.size(), hipMemcpyHostToDevice, st));
   if (o_rows) FAMSA_HIP(hipMemcpyAsync(D + b_rows, up_rows, o_rows, hipMemcpyHostToDevice, st));
   PdpArrays A;
   A.seqs = D + b_seqs;
@@ -948,21 +943,22 @@ extern "C" int famsa_profile_align(uint32_t nprob, const uint8_t* seqs, const ui
   hipLaunchKernelGGL(pdp_dp_kernel, dim3(nprob), dim3(64 * waves), lds_dyn, st, dprobs, A, sigma);
   FAMSA_HIP(hipGetLastError());
   FAMSA_HIP(hipEventRecord(ev[1], st));
-  std::vector<uint8_t> hops(o_ops ? o_ops : 1);
-  FAMSA_HIP(hipMemcpyAsync(score, D + b_score, 8ull * nprob, hipMemcpyDeviceToHost, st));
-  FAMSA_HIP(hipMemcpyAsync(nops, D + b_nops, 4ull * nprob, hipMemcpyDeviceToHost, st));
-  if (o_ops) FAMSA_HIP(hipMemcpyAsync(hops.data(), D + b_ops, o_ops, hipMemcpyDeviceToHost, st));
+  std::vector<uint8_t> down(off - b_score);
+  FAMSA_HIP(hipMemcpyAsync(down.data(), D + b_score, down.size(), hipMemcpyDeviceToHost, st));
   FAMSA_HIP(hipStreamSynchronize(st));
   float ms = 0;
   FAMSA_HIP(hipEventElapsedTime(&ms, ev[0], ev[1]));
   g_profile_dp_ms = ms;
   (void)hipEventDestroy(ev[0]);
   (void)hipEventDestroy(ev[1]);
+  memcpy(score, down.data(), 8ull * nprob);
+  memcpy(nops, down.data() + (b_nops - b_score), 4ull * nprob);
+  const uint8_t* hops = down.data() + (b_ops - b_score);
   for (uint32_t p = 0; p < nprob; ++p) {
     if (nops[p] == 0xFFFFFFFFu) return set_error(FAMSA_LCS_EDEVICE, "problem %u: trace-back stopped early", p);
     if ((uint64_t)nops[p] > (uint64_t)pr[p].m + pr[p].n)  // an alignment has at most m + n ops
       return set_error(FAMSA_LCS_EDEVICE, "problem %u: %u ops from the device", p, nops[p]);
-    memcpy(ops + ops_off[p], hops.data() + pr[p].ops, nops[p]);
+    memcpy(ops + ops_off[p], hops + pr[p].ops, nops[p]);
   }
   return 0;
 }

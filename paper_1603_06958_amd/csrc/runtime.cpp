@@ -30,23 +30,92 @@ void clear_error() { g_err.clear(); }
 
 const char* last_error_text() { return g_err.c_str(); }
 
+namespace {
+struct Kept {
+  void* p;
+  size_t cap;
+  int device;
+};
+std::mutex g_kept_mu;
+std::vector<Kept> g_kept;  // oldest first
+
+void free_on(int device, void* p) {
+  int cur = 0;
+  const bool move = hipGetDevice(&cur) == hipSuccess && cur != device && hipSetDevice(device) == hipSuccess;
+  (void)hipFree(p);
+  if (move) (void)hipSetDevice(cur);
+}
+
+// Takes blocks out of the store until it holds at most `bytes` in `blocks`.
+void trim_kept(size_t bytes, size_t blocks) {
+  size_t held = 0;
+  for (const Kept& k : g_kept) held += k.cap;
+  while (!g_kept.empty() && (held > bytes || g_kept.size() > blocks)) {
+    held -= g_kept.front().cap;
+    free_on(g_kept.front().device, g_kept.front().p);
+    g_kept.erase(g_kept.begin());
+  }
+}
+}  // namespace
+
+size_t kept_bytes(int device) {
+  std::lock_guard<std::mutex> lock(g_kept_mu);
+  size_t held = 0;
+  for (const Kept& k : g_kept) held += k.device == device ? k.cap : 0;
+  return held;
+}
+
 void DevMem::reset() {
-  if (p) (void)hipFree(p);
+  if (p) {
+    int cur = 0;
+    const bool same = hipGetDevice(&cur) == hipSuccess && cur == device;
+    if (same && cap >= kKeptLeast && cap <= kKeptBlock && hipDeviceSynchronize() == hipSuccess) {
+      std::lock_guard<std::mutex> lock(g_kept_mu);
+      g_kept.push_back(Kept{p, cap, device});
+      trim_kept(kKeptBytes, kKeptBlocks);
+    } else {
+      free_on(device, p);
+    }
+  }
   p = nullptr;
-  bytes = 0;
+  bytes = cap = 0;
 }
 
 int DevMem::alloc(size_t n) {
   reset();
   if (n == 0) n = 16;
+  FAMSA_HIP(hipGetDevice(&device));
+  if (n >= kKeptLeast) {  // the smallest kept block that holds it, if that is not far larger
+    std::lock_guard<std::mutex> lock(g_kept_mu);
+    size_t best = g_kept.size();
+    for (size_t i = 0; i < g_kept.size(); ++i)
+      if (g_kept[i].device == device && g_kept[i].cap >= n && g_kept[i].cap / 2 <= n &&
+          (best == g_kept.size() || g_kept[i].cap < g_kept[best].cap))
+        best = i;
+    if (best < g_kept.size()) {
+      p = g_kept[best].p;
+      cap = g_kept[best].cap;
+      bytes = n;
+      g_kept.erase(g_kept.begin() + (long)best);
+      return 0;
+    }
+  }
   hipError_t e = hipMalloc(&p, n);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    {
+      std::lock_guard<std::mutex> lock(g_kept_mu);
+      trim_kept(0, 0);
+    }
+    e = hipMalloc(&p, n);
+  }
   if (e != hipSuccess) {
     p = nullptr;
     (void)hipGetLastError();
     return set_error(e == hipErrorOutOfMemory ? FAMSA_LCS_ENOMEM : FAMSA_LCS_EDEVICE, "hipMalloc(%zu): %s", n,
                      hipGetErrorString(e));
   }
-  bytes = n;
+  bytes = cap = n;
   return 0;
 }
 

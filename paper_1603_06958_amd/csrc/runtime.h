@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/famsa_lcs.h"
@@ -22,30 +23,39 @@ void clear_error();
     if (e_ != hipSuccess) return ::famsa::set_error(FAMSA_LCS_EDEVICE, "%s: %s", #call, hipGetErrorString(e_)); \
   } while (0)
 
-// RAII device / pinned buffers.
+// RAII device / pinned buffers.  Device blocks of 1 MB and more are kept when
+// they are released and handed to later allocations of about their size:
+// getting and giving back such a block takes the driver 0.1 to 0.4 ms, more
+// than many calls' work.  Releasing one waits for the device, as freeing it
+// does, so a block in the store is in use on no stream.  The store holds at
+// most kKeptBytes in kKeptBlocks blocks (the oldest go first) and is emptied
+// before an allocation fails; a plan's or server's budget counts it as free.
+constexpr size_t kKeptBytes = 512u << 20, kKeptBlock = 256u << 20, kKeptLeast = 1u << 20;
+constexpr size_t kKeptBlocks = 16;
+size_t kept_bytes(int device);  // held in the store for `device`
+
 struct DevMem {
   void* p = nullptr;
-  size_t bytes = 0;
+  size_t bytes = 0;  // as asked for
+  size_t cap = 0;    // the block's size
+  int device = 0;
   DevMem() = default;
   DevMem(const DevMem&) = delete;
   DevMem& operator=(const DevMem&) = delete;
-  DevMem(DevMem&& o) noexcept : p(o.p), bytes(o.bytes) {
-    o.p = nullptr;
-    o.bytes = 0;
-  }
+  DevMem(DevMem&& o) noexcept { *this = std::move(o); }
   DevMem& operator=(DevMem&& o) noexcept {
     if (this != &o) {
       reset();
-      p = o.p;
-      bytes = o.bytes;
-      o.p = nullptr;
-      o.bytes = 0;
+      std::swap(p, o.p);
+      std::swap(bytes, o.bytes);
+      std::swap(cap, o.cap);
+      device = o.device;
     }
     return *this;
   }
   ~DevMem() { reset(); }
   void reset();
-  int alloc(size_t n);  // 0 or FAMSA_LCS_ENOMEM / EDEVICE (error text set)
+  int alloc(size_t n);  // on the current device: 0 or FAMSA_LCS_ENOMEM / EDEVICE (error text set)
   template <class T> T* as() const { return static_cast<T*>(p); }
 };
 

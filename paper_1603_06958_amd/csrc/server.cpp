@@ -135,8 +135,7 @@ int famsa_lcs_server_s::admit() {
     j->dev.reset(new DeviceBatchOwner());
     if (reuse >= 0) {
       spare_bytes -= spare[reuse].bytes;
-      std::swap(j->dev->mem.p, spare[reuse].p);
-      std::swap(j->dev->mem.bytes, spare[reuse].bytes);
+      j->dev->mem = std::move(spare[reuse]);
       spare.erase(spare.begin() + reuse);
     }
     // no wait: the uploads and mask build are ordered on cs before the job's first step
@@ -291,9 +290,7 @@ int famsa_lcs_server_s::deliver(int si, famsa_lcs_tile_fn fn, void* user) {
       in_use -= j->dev->bytes;
       // keep the job's device memory for a later job; the step that read it has
       // completed (its copy event was waited on above), and later steps do not
-      spare.emplace_back();
-      std::swap(spare.back().p, j->dev->mem.p);
-      std::swap(spare.back().bytes, j->dev->mem.bytes);
+      spare.push_back(std::move(j->dev->mem));
       spare_bytes += spare.back().bytes;
       j->dev.reset();
       active.erase(std::find(active.begin(), active.end(), j));
@@ -329,6 +326,7 @@ int famsa_lcs_server_create(const famsa_lcs_options* opt, famsa_lcs_server_t** o
   if (o.flags & FAMSA_LCS_LONG_SEGMENTED) s->lp.long_wl = 0;
   size_t freeb = 0, totalb = 0;
   FAMSA_HIP(hipMemGetInfo(&freeb, &totalb));
+  freeb += kept_bytes(o.device);
   s->budget = o.hbm_budget ? o.hbm_budget : (uint64_t)(freeb * 0.9);
   s->step_values = o.step_values;
   s->step_cells = o.step_cells;

@@ -7,6 +7,7 @@ import ctypes
 
 import numpy as np
 import pytest
+import torch  # before the library is loaded: both then use torch's HIP runtime
 
 from paper_1603_06958_amd import binding as B
 
@@ -36,7 +37,6 @@ def values(kind, k, rng):
     ("flat", 4200, 1024, "up"), ("rising", 4200, 4200, "up"), ("rising", 4200, 1024, "up"), ("chain", 4200, 1024, "up"),
     ("chain", 4200, 900, "down"), ("halves", 4096, 512, "mixed"), ("random", 129, 128, "up"), ("rising", 700, 300, "up")])
 def test_forest_of_made_up_tiles(kind, k, R, order):
-    import torch
     rng = np.random.default_rng(k + R)
     lens, M = values(kind, k, rng)
     iu = np.triu_indices(k, 1)

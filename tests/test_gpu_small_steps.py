@@ -4,6 +4,7 @@ changes, groups with a single row, widths at the ends of every class; values
 are the oracle's (or the plain kernel's where there are many)."""
 import numpy as np
 import pytest
+import torch  # before the library is loaded: both then use torch's HIP runtime
 
 import oracle
 from paper_1603_06958_amd import binding as B
@@ -17,7 +18,6 @@ def triangle(tiles, k):
 
 
 def noalloc(b, sigma):
-    import torch
     k = b.nseq
     codes = torch.from_numpy(np.append(b.codes, np.uint8(0))).cuda()
     off = torch.from_numpy(b.seq_off.astype(np.int64)).cuda()
