@@ -255,7 +255,8 @@ void famsa_slink_destroy(famsa_slink_t* s);
  * each device tile (FAMSA_LCS_DEVICE_TILES) it replaces its forest with the
  * maximum spanning forest of the forest plus the tile's pairs (one pass over
  * the tile keeps the pairs better than the worst edge on the forest's path
- * between their ends, then Boruvka rounds on the GPU).  Device memory is O(k),
+ * between their ends; Boruvka rounds on the GPU take these in, those of
+ * several tiles at a time, the last ones when the forest is read).  Device memory is O(k),
  * about 1.2 KB a sequence, in one allocation made by famsa_mst_create; tiles
  * hold at most 65535 rows and may come in any order.  Similarities are
  * ordered exactly; equal similarities are ordered by the pair (u, v), u < v,
@@ -270,7 +271,8 @@ int famsa_mst_create(const uint32_t* lengths, uint32_t k, int device, famsa_mst_
  * whatever stream that one came on, and returns once that work has finished
  * reading the tile (nonzero on a bad tile or a HIP error); calls on one
  * famsa_mst_t must not overlap.  famsa_mst_result, _guide_tree and
- * _get_stats wait for the last merge, not for the whole device. */
+ * _get_stats may be called by several threads at once, not beside consume;
+ * they wait for the merges, not for the whole device. */
 int famsa_mst_consume(void* mst, const famsa_lcs_tile* tile);
 /* The forest's edges (k-1 of them once every pair has been seen): endpoints
  * u < v (family-local), their LCS and indel^2 (similarity LCS / indel^2).

@@ -7,13 +7,14 @@
 // similarities, so keeping that tree is enough: after every tile, the forest
 // F becomes the maximum spanning forest of F plus the tile's pairs (a forest
 // that is optimal for a set of edges stays a valid summary of it, by the
-// cycle property).  One update:
+// cycle property).  In steps:
 //   1. a pair (i, j) of the tile can enter the forest only if it is better
 //      than the worst edge on F's path between i and j; one pass over the
 //      tile (mst_filter) keeps the pairs that are, the survivors;
-//   2. Boruvka on F plus the survivors gives the new forest: every component
-//      takes the best edge that leaves it, components hook along these edges
-//      and are renumbered, edges inside a component are dropped;
+//   2. an update, Boruvka on F plus the survivors of one or several tiles,
+//      gives the new forest: every component takes the best edge that leaves
+//      it, components hook along these edges and are renumbered, edges inside
+//      a component are dropped;
 //   3. the rounds' components are the hierarchy that answers the next pass's
 //      path queries (mst_view).
 // The path query (King's lemma on Boruvka trees): the worst edge on the path
@@ -24,10 +25,10 @@
 // The tile is read once (four bytes a pair) instead of once and then in parts
 // in each of five or six rounds, and the rounds work on the forest and a few
 // edges a vertex.  Per 1,024-row tile of 30,000 columns the pass takes 12-50 us
-// (later tiles are narrower) and the update behind it about 130 us, most of it
-// launches and one workgroup's latency, against 560 us for dense rounds; k =
-// 12,000 sequences of 60 residues to their guide tree 9.3 -> 5.2 ms, k =
-// 30,000 of 250 88.8 -> 78.4 ms (the LCS kernels are 70 of them).
+// (later tiles are narrower) and an update, once in several tiles, 150-250 us,
+// most of it launches, against 560 us a tile for dense rounds; k = 12,000
+// sequences of 60 residues to their guide tree 9.1 -> 3.7 ms, k = 30,000 of
+// 250 88.9 -> 66.3 ms (the LCS kernels are 60 of them).
 //
 // Similarity (Methods, "Pairwise similarities calculation") is
 // LCS / indel^2 with indel = |A| + |B| - 2 LCS, +infinity when indel = 0.
@@ -41,6 +42,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -76,13 +78,14 @@ struct MstExact {  // the same choice exactly
 };
 
 constexpr uint32_t kMstMaxRounds = 40;
+constexpr uint32_t kAll = 0xFFFFFFFFu;
 struct MstCtl {
   uint32_t nf;      // edges in the forest
   uint32_t pad;
   uint64_t rounds;  // Boruvka rounds with hooks, over all updates
 };
 struct MstPass {  // one update; the next one's is cleared by this one's last launch
-  uint32_t nsurv;   // the tile's surviving pairs
+  uint64_t surv;    // low half: survivors so far; high half: blocks of the passes that are through
   uint32_t nnew;    // edges in the new forest
   uint32_t ntot;    // component labels given out: vertices first, then each round's components
   uint32_t levels;  // rounds with hooks
@@ -102,6 +105,7 @@ struct MstDev {
   const uint32_t* len;
   uint32_t k;
   uint32_t room;      // survivors the e* arrays hold after the forest's k - 1 edges
+  uint32_t n;         // survivors that this update takes in, kAll: as many as there are by then
   uint32_t* eu;       // forest edges (ctl->nf), then the survivors
   uint32_t* ev;
   uint64_t* ekey;
@@ -121,21 +125,14 @@ struct MstDev {
   MstView* view;
   MstExact* exact;
   MstCtl* ctl;
-  uint32_t* host;     // pinned: [0] survivors of this update
+  uint32_t* host;     // pinned: [0] survivors so far
 };
 
 // The last rounds run in one workgroup, components in LDS.
 constexpr uint32_t kFinThreads = 1024;
 constexpr uint32_t kFinComps = 4096;
-constexpr uint32_t kFinEdges = 16384;
+constexpr uint32_t kFinEdges = 8192;
 constexpr size_t kFinLds = (size_t)kFinComps * 24;
-
-// An update is left undone when its survivors do not fit (the host repeats it
-// with fewer rows), and has nothing to do when there are none.
-__device__ __forceinline__ bool mst_idle(const MstDev& m) {
-  const uint32_t n = m.ps->nsurv;
-  return n == 0 || n > m.room;
-}
 
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
@@ -216,6 +213,16 @@ __device__ __forceinline__ void offers_end(OfferTable* t, uint64_t* slots) {
     if (t->comp[x] != 0xFFFFFFFFu) offer(&slots[t->comp[x]], t->key[x]);
 }
 
+__device__ __forceinline__ uint32_t mst_taken(const MstDev& m) { return m.n == kAll ? (uint32_t)m.ps->surv : m.n; }
+
+// An update that was queued behind its pass is left undone when the survivors
+// do not fit (the host repeats it with fewer rows), and has nothing to do when
+// there are none.
+__device__ __forceinline__ bool mst_idle(const MstDev& m) {
+  const uint32_t n = mst_taken(m);
+  return n == 0 || n > m.room;
+}
+
 // Clear the components and counters of an update.
 __device__ __forceinline__ void mst_clear(const MstComp& c, MstPass* ps, uint32_t k) {
   const uint64_t n = 2ull * k, step = (uint64_t)gridDim.x * blockDim.x;
@@ -229,12 +236,21 @@ __device__ __forceinline__ void mst_clear(const MstComp& c, MstPass* ps, uint32_
     ps->cnt[threadIdx.x] = 0;
     ps->hi[threadIdx.x] = 0;
     if (threadIdx.x == 0) {
-      ps->nsurv = 0;
+      ps->surv = 0;
       ps->nnew = 0;
       ps->ntot = k;
       ps->levels = 0;
     }
   }
+}
+
+// A block of the pass is through, with n survivors to append: their place.
+// The last one tells the host how many there are now.
+__device__ __forceinline__ uint32_t mst_leave(const MstDev& m, uint32_t n, uint32_t last) {
+  const uint64_t old = atomicAdd((unsigned long long*)&m.ps->surv, (1ull << 32) | n);
+  if ((uint32_t)(old >> 32) == last)
+    __hip_atomic_store(m.host, (uint32_t)old + n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  return (uint32_t)old;
 }
 
 // Values before tile row i (rows r0.. of the upper triangle, k - 1 - t per row t).
@@ -262,7 +278,8 @@ __global__ __launch_bounds__(64 * kFiltWaves) void mst_filter(MstDev m, const Ms
                                                               const uint32_t* __restrict__ len,
                                                               const int32_t* __restrict__ tile, uint32_t r0,
                                                               uint32_t r1, uint32_t t0, uint32_t t1, uint32_t slice,
-                                                              uint32_t stride, uint32_t skip, uint32_t j0) {
+                                                              uint32_t stride, uint32_t skip, uint32_t j0,
+                                                              uint32_t last_block) {
   __shared__ uint32_t bi[kFiltBuf], bj[kFiltBuf];
   __shared__ int32_t bL[kFiltBuf];
   __shared__ uint32_t s_n, s_base;
@@ -272,7 +289,10 @@ __global__ __launch_bounds__(64 * kFiltWaves) void mst_filter(MstDev m, const Ms
   const uint32_t jb = j0 + blockIdx.x * (64u * kFiltCols);  // < k
   const uint32_t tb = t0 + blockIdx.y * slice, te = min(t1, tb + slice);
   const uint32_t last = min(r1, k - 1u) - 1u;  // the tile's last row with a pair
-  if (r0 + tb * stride >= jb + 64u * kFiltCols - 1u) return;  // no column of the block is after its first row
+  if (r0 + tb * stride >= jb + 64u * kFiltCols - 1u) {  // no column of the block is after its first row
+    if (threadIdx.x == 0) (void)mst_leave(m, 0, last_block);
+    return;
+  }
   if (threadIdx.x == 0) s_n = 0;
   __syncthreads();
   uint32_t lj[kFiltCols];
@@ -339,7 +359,7 @@ __global__ __launch_bounds__(64 * kFiltWaves) void mst_filter(MstDev m, const Ms
     uint32_t over = 0;  // past the block's buffer: straight to the list
     if (base + total > kFiltBuf) {
       const uint32_t out = base + total - max(base, kFiltBuf);
-      if (lane == 0) over = atomicAdd(&m.ps->nsurv, out);
+      if (lane == 0) over = (uint32_t)atomicAdd((unsigned long long*)&m.ps->surv, (unsigned long long)out);
       over = __builtin_amdgcn_readfirstlane(over) - max(base, kFiltBuf);
     }
 #pragma unroll
@@ -367,8 +387,7 @@ __global__ __launch_bounds__(64 * kFiltWaves) void mst_filter(MstDev m, const Ms
   }
   __syncthreads();
   const uint32_t n = min(s_n, kFiltBuf);
-  if (n == 0) return;
-  if (threadIdx.x == 0) s_base = atomicAdd(&m.ps->nsurv, n);
+  if (threadIdx.x == 0) s_base = mst_leave(m, n, last_block);
   __syncthreads();
   const uint32_t base = s_base;
   for (uint32_t x = threadIdx.x; x < n && base + x < m.room; x += 64 * kFiltWaves) {
@@ -398,17 +417,13 @@ __device__ __forceinline__ MstList mst_list(const MstDev& m, uint32_t r) {
 __global__ __launch_bounds__(kEdgeThreads) void mst_edges(MstDev m, uint32_t r) {
   __shared__ BlockSlots red;
   __shared__ OfferTable table;
-  const bool idle = mst_idle(m);
   MstPass* ps = m.ps;
-  const uint32_t n = r == 0 ? m.ctl->nf + ps->nsurv : ps->cnt[r - 1];
+  const uint32_t n = r == 0 ? m.ctl->nf + mst_taken(m) : ps->cnt[r - 1];
   const uint32_t nc = r == 0 ? m.k : ps->ntot - ps->hi[r - 1];
-  const bool go = !idle && (r == 0 || ps->act[r - 1]) && n > 0 && !(nc <= kFinComps && n <= kFinEdges);
+  const bool go = !mst_idle(m) && (r == 0 || ps->act[r - 1]) && n > 0 && !(nc <= kFinComps && n <= kFinEdges);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     ps->act[r] = go ? 1u : 0u;
-    if (r == 0) {
-      ps->cnt[0] = go ? n : 0u;
-      __hip_atomic_store(m.host, ps->nsurv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
+    if (r == 0) ps->cnt[0] = go ? n : 0u;
   }
   if (!go) return;
   const uint32_t step = gridDim.x * kEdgeThreads;
@@ -470,7 +485,8 @@ __global__ __launch_bounds__(kEdgeThreads) void mst_ids(MstDev m, uint32_t r) {
 }
 
 // Chosen edges hook their components (two that chose the same edge hook once,
-// the larger label onto the smaller) and join the new forest.
+// the larger label onto the smaller) and join the new forest: the one that
+// moved the component, where a caller gave the same pair twice.
 __global__ __launch_bounds__(kEdgeThreads) void mst_hook(MstDev m, uint32_t r) {
   __shared__ BlockSlots red;
   if (!m.ps->act[r]) return;
@@ -496,10 +512,11 @@ __global__ __launch_bounds__(kEdgeThreads) void mst_hook(MstDev m, uint32_t r) {
         wb = wb && m.c.id[b] == id;
       }
     }
-    if (wa && !(wb && a < b)) m.c.par[a] = b;
-    if (wb && !(wa && b < a)) m.c.par[b] = a;
-    const uint32_t at = block_slot(wa || wb, &m.ps->nnew, &red);
-    if (wa || wb) {
+    bool in = false;
+    if (wa && !(wb && a < b)) in = atomicCAS(&m.c.par[a], a, b) == a;
+    if (wb && !(wa && b < a)) in = atomicCAS(&m.c.par[b], b, a) == b || in;
+    const uint32_t at = block_slot(in, &m.ps->nnew, &red);
+    if (in) {
       m.nu[at] = u;
       m.nv[at] = v;
       m.nkey[at] = key;
@@ -555,11 +572,10 @@ __global__ __launch_bounds__(kFinThreads) void mst_finish(MstDev m, uint32_t que
   __shared__ uint32_t s_cnt, s_new, s_forest;
   MstPass* ps = m.ps;
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
-  if (tid == 0 && queued == 0) __hip_atomic_store(m.host, ps->nsurv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   if (mst_idle(m)) return;
   uint32_t r = 0;
   while (r < queued && ps->act[r]) ++r;
-  uint32_t n = r == 0 ? m.ctl->nf + ps->nsurv : ps->cnt[r - 1];
+  uint32_t n = r == 0 ? m.ctl->nf + mst_taken(m) : ps->cnt[r - 1];
   uint32_t lo = r == 0 ? 0u : ps->hi[r - 1], tot = ps->ntot, nc = tot - lo, levels = ps->levels;
   if (n == 0 || nc > kFinComps) return;  // (never more: see above)
   MstList l = mst_list(m, r == 0 ? 0 : r - 1);
@@ -672,10 +688,11 @@ __global__ __launch_bounds__(kFinThreads) void mst_finish(MstDev m, uint32_t que
           wa = wa && sid[a[q]] == id;
           wb = wb && sid[b[q]] == id;
         }
-        if (wa && !(wb && a[q] < b[q])) spar[a[q]] = b[q];
-        if (wb && !(wa && b[q] < a[q])) spar[b[q]] = a[q];
-        const uint32_t at = wave_slot(wa || wb, &s_forest);
-        if (wa || wb) {
+        bool in = false;
+        if (wa && !(wb && a[q] < b[q])) in = atomicCAS(&spar[a[q]], a[q], b[q]) == a[q];
+        if (wb && !(wa && b[q] < a[q])) in = atomicCAS(&spar[b[q]], b[q], a[q]) == b[q] || in;
+        const uint32_t at = wave_slot(in, &s_forest);
+        if (in) {
           m.nu[at] = u;
           m.nv[at] = v;
           m.nkey[at] = key[q];
@@ -720,6 +737,9 @@ __global__ __launch_bounds__(kFinThreads) void mst_finish(MstDev m, uint32_t que
     m.ctl->rounds += levels - levels0;
   }
 }
+
+// A pass whose survivors do not fit, on an empty list: the list is empty again.
+__global__ void mst_forget(MstPass* ps) { ps->surv = 0; }
 
 // The hierarchy of this update, per vertex, for the next pass; the new forest
 // becomes the current one, and the next update's components and counters are
@@ -787,8 +807,11 @@ struct famsa_mst_s {
   // two); this event marks the end of the last tile's work, and the next
   // tile's work waits for it, so merges never overlap whatever the streams.
   hipEvent_t last = nullptr;
-  hipEvent_t read = nullptr;  // a pass over the tile and its survivors' count are done
+  hipEvent_t read = nullptr;  // the last pass over a tile is done
   bool has_last = false;
+  uint32_t pending = 0;  // survivors that the forest has not taken in yet
+  uint32_t blocks = 0;   // of the passes they are from
+  std::mutex mu;         // reading the forest takes them in
   ~famsa_mst_s() {
     if (last) {
       if (has_last) (void)hipEventSynchronize(last);
@@ -796,19 +819,17 @@ struct famsa_mst_s {
     }
     if (read) (void)hipEventDestroy(read);
   }
-  int wait_last() const {
-    if (has_last) FAMSA_HIP(hipEventSynchronize(last));
-    return 0;
-  }
   int layout();
   struct Rows {  // rows t0..t1-1 of stride `stride` in a tile; skip: every eighth left out
     uint32_t t0, t1, stride, skip;
   };
-  int update(const famsa_lcs_tile* t, const Rows& rows, bool dense, hipStream_t s, bool* fits);
+  int filter(const famsa_lcs_tile* t, const Rows& rows, bool take, hipStream_t s, bool* fits);
+  int update(uint32_t n, uint64_t most, hipStream_t s);
+  int settle();
   int merge_tile(const famsa_lcs_tile* t, hipStream_t s);
 };
 
-// One allocation: about 1 KB a vertex, most of it room for survivors.
+// One allocation: about 1.2 KB a vertex, most of it room for survivors.
 int famsa_mst_s::layout() {
   const uint64_t n = std::max<uint32_t>(k, 1);
   const uint64_t pairs = n * (n - 1) / 2;
@@ -864,22 +885,14 @@ static inline uint32_t grid_for(uint64_t n, uint32_t threads) {
   return (uint32_t)std::min<uint64_t>(512, std::max<uint64_t>(1, (n + threads - 1) / threads));
 }
 
-// One update of the forest from some of the tile's rows.  The launches are
-// queued without waiting (kernels of rounds that are not needed return at
-// once); the host waits for the pass over the tile alone.  *fits: the
-// survivors fitted; else the forest is as it was.
-int famsa_mst_s::update(const famsa_lcs_tile* t, const Rows& rows, bool dense, hipStream_t s, bool* fits) {
+// The pass over some of the tile's rows; the host waits for it and so knows
+// the survivors so far.  *fits: all of them are in the list; else
+// the list is what it was before.  take (on an empty list): the update that
+// takes them in, if they fit, is queued behind the pass without waiting.
+int famsa_mst_s::filter(const famsa_lcs_tile* t, const Rows& rows, bool take, hipStream_t s, bool* fits) {
   const uint32_t r0 = t->row_begin, r1 = t->row_end;
-  // this update's components and counters were cleared by the one before
-  std::swap(dev.c, dev.next);
-  std::swap(dev.ps, dev.ps_next);
   const MstDev& m = dev;
   const uint32_t nrows = rows.t1 - rows.t0;
-  const uint64_t most = std::min<uint64_t>((uint64_t)nrows * (k - 1), surv_cap) + k;  // edges, at most
-  uint32_t rounds = 0;  // on the whole GPU
-  while ((k >> rounds) >= kFinComps && rounds < 32) ++rounds;  // then fewer than kFinComps are left
-  if (k <= kFinComps) rounds = 0;
-  if (dense && most > kFinEdges) rounds += 2;
   // blocks of 128 columns; a slice of rows so that about 256 blocks share the
   // tile (the survivors' appends are one atomic a block), 64 rows at least:
   // four for each wave
@@ -888,34 +901,101 @@ int famsa_mst_s::update(const famsa_lcs_tile* t, const Rows& rows, bool dense, h
   const uint32_t per = kFiltWaves * kFiltChunk;
   const uint32_t want = std::max(1u, 256u / strips);
   const uint32_t slice = (std::max(1u, (nrows + want - 1) / want) + per - 1) / per * per;
+  const dim3 g(strips, (nrows + slice - 1) / slice);
+  blocks += g.x * g.y;
+  hipLaunchKernelGGL(mst_filter, g, dim3(64 * kFiltWaves), 0, s, m, m.view, m.len, t->lcs, r0, r1, rows.t0, rows.t1,
+                     slice, rows.stride, rows.skip, j0, blocks - 1u);
+  FAMSA_HIP(hipGetLastError());
+  if (take) {
+    FAMSA_HIP(hipEventRecord(read, s));
+    const int rc = update(kAll, (uint64_t)nrows * (k - 1), s);
+    if (rc) return rc;
+    FAMSA_HIP(hipEventSynchronize(read));
+    *fits = *static_cast<volatile uint32_t*>(hflag.p) <= surv_cap;
+    return 0;
+  }
+  FAMSA_HIP(hipEventRecord(last, s));
+  has_last = true;
+  FAMSA_HIP(hipEventSynchronize(last));
+  const uint32_t n = *static_cast<volatile uint32_t*>(hflag.p);
+  *fits = n <= surv_cap;
+  if (*fits) {
+    pending = n;
+  } else if (pending == 0) {
+    hipLaunchKernelGGL(mst_forget, dim3(1), dim3(1), 0, s, m.ps);
+    FAMSA_HIP(hipGetLastError());
+    FAMSA_HIP(hipEventRecord(last, s));
+    blocks = 0;
+  }
+  return 0;
+}
+
+// The forest takes in the survivors so far, n of them (or kAll, at most
+// `most`).  Launches are queued without waiting; kernels of rounds that are
+// not needed return at once.
+int famsa_mst_s::update(uint32_t n, uint64_t most, hipStream_t s) {
+  if (n == 0) return 0;
+  dev.n = n;
+  const MstDev& m = dev;
+  most = std::min<uint64_t>(most, surv_cap);
+  uint32_t rounds = 0;  // on the whole GPU
+  while ((k >> rounds) >= kFinComps && rounds < 32) ++rounds;  // then fewer than kFinComps are left
+  if (k <= kFinComps) rounds = 0;
+  // many survivors: one workgroup takes 82 us and more over what two rounds
+  // leave of 70,000 edges, a round on the whole GPU 30 (k = 12,000 sequences
+  // of 60 residues in all: 3.2 ms with no more rounds, 2.9 with two, 2.6 with
+  // four, 2.6 with five); for few components its rounds are the faster ones
+  if (most > 2 * kFinEdges) rounds += k > kFinComps ? 4 : 2;
+  most += k;  // edges
   const dim3 ge(grid_for(most, kEdgeThreads)), gc(grid_for(k, kEdgeThreads)), b(kEdgeThreads);
-  hipLaunchKernelGGL(mst_filter, dim3(strips, (nrows + slice - 1) / slice), dim3(64 * kFiltWaves), 0, s, m, m.view,
-                     m.len, t->lcs, r0, r1, rows.t0, rows.t1, slice, rows.stride, rows.skip, j0);
   for (uint32_t r = 0; r < rounds; ++r) {
     hipLaunchKernelGGL(mst_edges, ge, b, 0, s, m, r);
-    if (r == 0) FAMSA_HIP(hipEventRecord(read, s));
     hipLaunchKernelGGL(mst_ids, ge, b, 0, s, m, r);
     hipLaunchKernelGGL(mst_hook, ge, b, 0, s, m, r);
     hipLaunchKernelGGL(mst_roots, gc, b, 0, s, m, r);
   }
   hipLaunchKernelGGL(mst_finish, dim3(1), dim3(kFinThreads), kFinLds, s, m, rounds);
-  if (rounds == 0) FAMSA_HIP(hipEventRecord(read, s));
   hipLaunchKernelGGL(mst_view, dim3(grid_for(2ull * k, 256)), dim3(256), 0, s, m, 0u);
   FAMSA_HIP(hipGetLastError());
   FAMSA_HIP(hipEventRecord(last, s));
   has_last = true;
-  FAMSA_HIP(hipEventSynchronize(read));
-  *fits = *static_cast<volatile uint32_t*>(hflag.p) <= surv_cap;
+  // the next update's components and counters are cleared by this one
+  std::swap(dev.c, dev.next);
+  std::swap(dev.ps, dev.ps_next);
+  pending = 0;
+  blocks = 0;
   return 0;
 }
 
-// Most tiles are one update.  Where the forest does not join the tile's
-// vertices yet (the first tile; every tile in descending order), or the
-// survivors of a whole tile do not fit, the rows are taken in passes of
-// growing size spread over the tile, every 8^n-th row first: a pass of eight
-// rows always fits, and each pass's forest then drops most pairs of the next
-// (a row seldom beats eight times as many like it).  A pass whose survivors
-// do not fit is halved.
+// The forest of every tile so far, for a reader.
+int famsa_mst_s::settle() {
+  if (!has_last) return 0;
+  if (pending) {
+    hipStream_t s = nullptr;
+    int rc = lib_stream(device, 0, &s);
+    if (rc) return rc;
+    FAMSA_HIP(hipStreamWaitEvent(s, last, 0));
+    if ((rc = update(pending, pending, s))) return rc;
+  }
+  FAMSA_HIP(hipEventSynchronize(last));
+  return 0;
+}
+
+// Most tiles are one pass.  An update costs 150 us and more, whatever it takes
+// in, so survivors wait in the list until they are six a vertex, or the list
+// has no room for the next pass, or the forest is read.  A pass against an
+// older hierarchy lets more pairs through, but not many: where the rows seen
+// double, about one a vertex.  Twelve tiles of k = 12,000 sequences of 60
+// residues take 4.0 ms with an update each, 3.2 with one every two survivors a
+// vertex, 2.6 every five, 2.5 every eight; k = 30,000 of 250 66.0, 64.9, 64.4
+// and 64.1.
+// Where the forest does not join the tile's vertices yet (the first tile;
+// every tile in descending order), or the survivors of a whole tile do not
+// fit, the rows are taken in passes of growing size spread over the tile,
+// every 8^n-th row first, with an update after each: the first pass always
+// fits, and each pass's forest then drops most pairs of the next (a row seldom
+// beats eight times as many like it).  A pass whose survivors do not fit is
+// halved.
 int famsa_mst_s::merge_tile(const famsa_lcs_tile* t, hipStream_t s) {
   const uint32_t r0 = t->row_begin, r1 = t->row_end;
   if (r1 - r0 > 65535u) return set_error(FAMSA_LCS_EINVAL, "tiles of more than 65535 rows are not supported");
@@ -926,10 +1006,12 @@ int famsa_mst_s::merge_tile(const famsa_lcs_tile* t, hipStream_t s) {
   if (has_last) FAMSA_HIP(hipStreamWaitEvent(s, last, 0));  // the previous tile's merge, on any stream
   const uint32_t R = std::min(r1, k - 1) - r0;  // rows with a pair
   const bool covered = r0 >= cover;
+  const uint32_t first = std::max(8u, surv_cap / k);  // rows whose pairs fit, all of them
+  const uint32_t wait = (uint32_t)std::min(6ull * k, surv_cap / 3ull);
   std::vector<Rows> todo;  // last first
   auto passes = [&]() {
     uint32_t st = 1;
-    while ((R + st - 1) / st > 8) st *= 8;
+    while ((R + st - 1) / st > first) st *= 8;
     std::vector<Rows> p;
     for (uint32_t skip = 0;; skip = 1, st /= 8) {
       p.push_back(Rows{0, (R + st - 1) / st, st, skip});
@@ -943,15 +1025,25 @@ int famsa_mst_s::merge_tile(const famsa_lcs_tile* t, hipStream_t s) {
     const Rows rows = todo.back();
     todo.pop_back();
     const uint32_t mid = rows.t0 + (rows.t1 - rows.t0) / 2;
-    if ((uint64_t)(rows.t1 - rows.t0) * k > 0xFFFFFFFFull && mid > rows.t0) {  // survivors are counted in 32 bits
+    // survivors are counted in 32 bits
+    if ((uint64_t)(rows.t1 - rows.t0) * k + pending > 0xFFFFFFFFull && mid > rows.t0) {
       todo.push_back(Rows{mid, rows.t1, rows.stride, rows.skip});
       todo.push_back(Rows{rows.t0, mid, rows.stride, rows.skip});
       continue;
     }
     bool fits = false;
-    const int rc = update(t, rows, !covered, s, &fits);
-    if (rc) return rc;
-    if (fits) continue;
+    int rc = 0;
+    if (!covered && pending && (rc = update(pending, pending, s))) return rc;
+    if ((rc = filter(t, rows, !covered, s, &fits))) return rc;
+    if (fits) {
+      if (pending > wait && (rc = update(pending, pending, s))) return rc;
+      continue;
+    }
+    if (pending) {  // room first
+      if ((rc = update(pending, pending, s))) return rc;
+      todo.push_back(rows);
+      continue;
+    }
     if (rows.t1 - rows.t0 <= 1) return set_error(FAMSA_LCS_EDEVICE, "one row's pairs do not fit");
     if (rows.stride == 1 && rows.skip == 0 && rows.t0 == 0 && rows.t1 == R && R > 8) {
       passes();
@@ -1016,6 +1108,8 @@ int famsa_mst_create(const uint32_t* lengths, uint32_t k, int device, famsa_mst_
     delete m;
     return set_error(FAMSA_LCS_EDEVICE, "initialising the forest failed");
   }
+  std::swap(m->dev.c, m->dev.next);
+  std::swap(m->dev.ps, m->dev.ps_next);
   *out = m;
   return 0;
 }
@@ -1027,6 +1121,7 @@ int famsa_mst_consume(void* user, const famsa_lcs_tile* t) {
   if (t->values != FAMSA_LCS_VALUES_LCS) return 1;  // the forest is built from LCS values
   if (t->count != tri_rows(m->k, t->row_begin, t->row_end)) return 1;
   if (hipSetDevice(m->device) != hipSuccess) return 1;
+  std::lock_guard<std::mutex> lock(m->mu);
   return m->merge_tile(t, (hipStream_t)t->stream) == 0 ? 0 : 1;
 }
 
@@ -1035,7 +1130,9 @@ int famsa_mst_result(const famsa_mst_t* m, uint32_t* u, uint32_t* v, int64_t* lc
   clear_error();
   if (!m || !nedges) return set_error(FAMSA_LCS_EINVAL, "NULL argument");
   FAMSA_HIP(hipSetDevice(m->device));
-  int rc = m->wait_last();
+  famsa_mst_s* const f = const_cast<famsa_mst_s*>(m);
+  std::lock_guard<std::mutex> lock(f->mu);
+  int rc = f->settle();
   if (rc) return rc;
   MstCtl c;
   FAMSA_HIP(hipMemcpy(&c, m->dev.ctl, sizeof c, hipMemcpyDeviceToHost));
@@ -1076,7 +1173,9 @@ int famsa_mst_get_stats(const famsa_mst_t* m, uint64_t* tiles, uint64_t* rounds)
   clear_error();
   if (!m) return set_error(FAMSA_LCS_EINVAL, "mst is NULL");
   FAMSA_HIP(hipSetDevice(m->device));
-  int rc = m->wait_last();
+  famsa_mst_s* const f = const_cast<famsa_mst_s*>(m);
+  std::lock_guard<std::mutex> lock(f->mu);
+  int rc = f->settle();
   if (rc) return rc;
   MstCtl c;
   FAMSA_HIP(hipMemcpy(&c, m->dev.ctl, sizeof c, hipMemcpyDeviceToHost));
