@@ -92,7 +92,7 @@ typedef struct famsa_lcs_options {
   void* stream;            /* hipStream_t the caller orders its own work on, or NULL (library stream) */
   uint64_t hbm_budget;     /* device bytes the plan may hold; 0 = 90% of free memory at plan time */
   uint32_t flags;          /* FAMSA_LCS_* flags above */
-  uint32_t cols_per_item;  /* columns per work item, 0 = tuned/default */
+  uint32_t cols_per_item;  /* the most columns per work item, 0 = tuned/default */
   uint64_t step_values;    /* int32 values per launch step (several tiles), 0 = default (2^27) */
   uint64_t step_cells;     /* server only: cells |A||B| per scheduler step, which bounds how long a
                               step runs and so how long a new job waits; the server's tiles then
