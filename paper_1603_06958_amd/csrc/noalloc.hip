@@ -8,9 +8,10 @@
 //   na_prep_kernel   -- the first workgroup plans: lengths and offsets
 //                       checked, rows sorted by length (counting sort), the
 //                       family mode work lists of the plan path (64-row
-//                       groups, column items); the others stage four
-//                       sequences each: codes checked, the column stream
-//                       (code c stored as c * 1024) and the match masks
+//                       groups, column items); the others stage sequences,
+//                       four at a time, once they have found every length and
+//                       offset of the family valid: codes checked, the column
+//                       stream (code c stored as c * 1024) and the match masks
 //                       PM[c][w] written into the sequence's slot;
 //   lcs_small_kernel -- families of few items: every class in one launch; or
 //   lcs_fast_kernel  -- the plan path's own kernels, classes 2, 1, 0, and
@@ -25,6 +26,7 @@
 
 #include <mutex>
 
+#include "noalloc_input.h"
 #include "runtime.h"
 
 namespace famsa {
@@ -40,6 +42,7 @@ constexpr uint32_t kNaMaskSlot = 20 * 28;               // dwords: >= 20 x 28 an
 constexpr int kNaMaxDevices = 64;
 constexpr uint32_t kNaThreads = 1024;
 constexpr uint32_t kNaTeam = 256;  // threads that stage a sequence
+constexpr uint32_t kNaStageBlocks = 512;  // at most so many workgroups stage: each reads all offsets first (64 KB at most)
 
 constexpr size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 constexpr size_t kOffCtl = 0;    // StepCtl
@@ -224,11 +227,11 @@ __device__ void na_plan(const uint64_t* __restrict__ seq_off, uint32_t k, uint32
 // takes 64 residues, and one ballot a code is two mask words.  A thread a word
 // compared its 32 residues with every code: 40 us for 8,192 sequences of 300.
 // A code outside the alphabet is marked and staged as code 0, so that the LCS
-// kernels stay within their tables whatever the input.
+// kernels stay within their tables whatever the input.  The caller has found
+// every offset of the family valid.
 __device__ void na_stage(const uint8_t* __restrict__ codes, const uint64_t* __restrict__ seq_off, uint32_t s,
-                         uint32_t sigma, uint32_t maxlen, uint8_t* __restrict__ base) {
+                         uint32_t sigma, uint8_t* __restrict__ base) {
   const uint64_t a = seq_off[s], b = seq_off[s + 1];
-  if (b < a || b - a > maxlen) return;  // the plan rejects it
   const uint32_t L = (uint32_t)(b - a), W = (L + 31u) >> 5, lane = threadIdx.x & 63u;
   const uint32_t w0 = (threadIdx.x & (kNaTeam - 1u)) >> 6;
   const uint8_t* src = codes + a;
@@ -261,10 +264,14 @@ __global__ __launch_bounds__(kNaThreads) void na_prep_kernel(const uint8_t* __re
                                                              uint8_t* __restrict__ base) {
   if (blockIdx.x == 0) {
     na_plan(seq_off, k, maxlen, base);
-  } else {
-    const uint32_t s = (blockIdx.x - 1) * (kNaThreads / kNaTeam) + threadIdx.x / kNaTeam;
-    if (s < k) na_stage(codes, seq_off, s, sigma, maxlen, base);
+    return;
   }
+  // no residue is read before the whole family's offsets are known to be valid: a sequence after an invalid one
+  // may lie outside the caller's codes
+  if (!__syncthreads_and(na_share_valid(seq_off, k, maxlen, threadIdx.x, kNaThreads))) return;
+  constexpr uint32_t per = kNaThreads / kNaTeam;
+  for (uint32_t s = (blockIdx.x - 1) * per + threadIdx.x / kNaTeam; s < k; s += (gridDim.x - 1) * per)
+    na_stage(codes, seq_off, s, sigma, base);
 }
 
 __global__ __launch_bounds__(256) void na_finish_kernel(uint8_t* __restrict__ base, int32_t* __restrict__ out,
@@ -338,9 +345,8 @@ int na_run(const uint8_t* codes, const uint64_t* seq_off, uint32_t nseq, uint32_
   uint8_t* base = d->ptr;
   const int s32 = sig_cap(sigma) == 32 ? 1 : 0;
   const uint32_t maxlen = s32 ? kNaMaxLen32 : kNaMaxLen20;
-  const uint32_t per = kNaThreads / kNaTeam;
-  hipLaunchKernelGGL(na_prep_kernel, dim3(1 + (nseq + per - 1) / per), dim3(kNaThreads), 0, st, codes, seq_off, nseq,
-                     sigma, maxlen, base);
+  const uint32_t per = kNaThreads / kNaTeam, stage = std::min((nseq + per - 1) / per, kNaStageBlocks);
+  hipLaunchKernelGGL(na_prep_kernel, dim3(1 + stage), dim3(kNaThreads), 0, st, codes, seq_off, nseq, sigma, maxlen, base);
   FAMSA_HIP(hipGetLastError());
   const uint64_t npairs = (uint64_t)nseq * (nseq ? nseq - 1 : 0) / 2;
   if (npairs) {
