@@ -29,6 +29,7 @@
 #include <stdint.h>
 
 #include "../../include/famsa_lcs.h"
+#include "staging.h"
 
 namespace famsa {
 
@@ -152,9 +153,10 @@ struct DeviceWork {         // descriptor arrays of a plan (all steps) or of one
 };
 
 // ---- launch wrappers (lcs_kernels.hip) ----
-// Column streams and masks of a batch of nseq sequences, from its codes.
-int launch_stage_batch(const DeviceBatch& b, uint32_t nseq, uint32_t max_len, uint32_t sigma, uint8_t* d_sym,
-                       uint32_t* d_masks, void* stream);
+// Column streams and masks of a batch of nseq sequences, from its codes; d_more
+// (device) lists the nmore spans past the sequences' first ones.
+int launch_stage_batch(const DeviceBatch& b, uint32_t nseq, const StageSpan* d_more, uint64_t nmore, uint32_t sigma,
+                       uint8_t* d_sym, uint32_t* d_masks, void* stream);
 int launch_step_begin(StepCtl* ctl, void* stream);
 // Fast kernel for length class cls (0..2): persistent, `blocks` workgroups of
 // `waves` wavefronts each.

@@ -39,27 +39,24 @@ namespace famsa {
 // ------------------------------------------------------------ batch staging
 
 // A batch's column streams and match masks from its codes: four waves take 64
-// residues each of a sequence, in rounds of 256, kStageSpan residues a
-// workgroup (blockIdx.y picks which).  A wave's 64 residues are two mask words
+// residues each of a span of a sequence, in rounds of 256.  Spans 0 .. nseq - 1
+// are the sequences' first ones, the others are listed in `more`.  A wave's 64
+// residues are two mask words
 // of every code, and one ballot a code makes both.  The host built the streams
 // (twice the codes' bytes) and padded copies of the codes before, in seven
 // uploads; a thread a word then compared its 32 residues with every code.
-constexpr uint32_t kStageSpan = 4096;
-
-__global__ __launch_bounds__(256) void stage_batch_kernel(const uint8_t* __restrict__ codes,
-                                                          const uint64_t* __restrict__ dev_off,
-                                                          const uint32_t* __restrict__ len,
-                                                          const uint64_t* __restrict__ sym_off,
-                                                          const uint64_t* __restrict__ mask_off, uint32_t sigma,
-                                                          uint8_t* __restrict__ sym, uint32_t* __restrict__ masks) {
-  const uint32_t s = blockIdx.x, lane = threadIdx.x & 63u;
+__device__ __forceinline__ void stage_span(const uint8_t* __restrict__ codes, const uint64_t* __restrict__ dev_off,
+                                           const uint32_t* __restrict__ len, const uint64_t* __restrict__ sym_off,
+                                           const uint64_t* __restrict__ mask_off, uint32_t s, uint32_t span,
+                                           uint32_t sigma, uint8_t* __restrict__ sym, uint32_t* __restrict__ masks) {
+  const uint32_t lane = threadIdx.x & 63u;
   const uint32_t L = len[s], W = (L + 31u) >> 5;
-  const uint32_t padded = 8u * ((L + 7u) / 8u + 1u);  // the stream's last chunk is spare, and zero
-  const uint32_t lo = blockIdx.y * kStageSpan, hi = min(padded, lo + kStageSpan);
+  const uint32_t padded = stream_codes(L);  // the stream's last chunk is spare, and zero
+  const uint32_t lo = span * kStageSpan, hi = min(padded, lo + kStageSpan);
   const uint8_t* src = codes + dev_off[s];
   uint16_t* dst = reinterpret_cast<uint16_t*>(sym + sym_off[s]);
   uint32_t* m = masks + mask_off[s];
-  for (uint32_t p0 = lo + 64u * (threadIdx.x >> 6); p0 < hi; p0 += 256) {
+  for (uint32_t p0 = lo + 64u * (threadIdx.x >> 6); p0 < hi; p0 += kStageThreads) {
     const uint32_t p = p0 + lane;
     const uint32_t c = p < L ? (uint32_t)src[p] : 0xFFu;
     if (p < padded) dst[p] = p < L ? (uint16_t)(c * 1024u) : (uint16_t)0;
@@ -74,6 +71,17 @@ __global__ __launch_bounds__(256) void stage_batch_kernel(const uint8_t* __restr
       m[(uint64_t)lane * W + w] = (uint32_t)mine;
       if (w + 1 < W) m[(uint64_t)lane * W + w + 1] = (uint32_t)(mine >> 32);
     }
+  }
+}
+
+__global__ __launch_bounds__(kStageThreads) void stage_batch_kernel(
+    const uint8_t* __restrict__ codes, const uint64_t* __restrict__ dev_off, const uint32_t* __restrict__ len,
+    const uint64_t* __restrict__ sym_off, const uint64_t* __restrict__ mask_off, uint32_t nseq,
+    const StageSpan* __restrict__ more, uint64_t spans, uint32_t sigma, uint8_t* __restrict__ sym,
+    uint32_t* __restrict__ masks) {
+  for (uint64_t u = blockIdx.x; u < spans; u += gridDim.x) {
+    const StageSpan x = u < nseq ? StageSpan{(uint32_t)u, 0u} : more[u - nseq];
+    stage_span(codes, dev_off, len, sym_off, mask_off, x.seq, x.span, sigma, sym, masks);
   }
 }
 
@@ -789,12 +797,12 @@ static inline int hip_ok(hipError_t e) { return e == hipSuccess ? 0 : (int)e; }
 
 size_t g_max_lds = kMaxLds;
 
-int launch_stage_batch(const DeviceBatch& b, uint32_t nseq, uint32_t max_len, uint32_t sigma, uint8_t* d_sym,
-                       uint32_t* d_masks, void* stream) {
+int launch_stage_batch(const DeviceBatch& b, uint32_t nseq, const StageSpan* d_more, uint64_t nmore, uint32_t sigma,
+                       uint8_t* d_sym, uint32_t* d_masks, void* stream) {
   if (nseq == 0) return 0;
-  const uint32_t spans = (8u * ((max_len + 7u) / 8u + 1u) + kStageSpan - 1) / kStageSpan;
-  hipLaunchKernelGGL(stage_batch_kernel, dim3(nseq, spans), dim3(256), 0, (hipStream_t)stream, b.codes, b.dev_off,
-                     b.len, b.sym_off, b.mask_off, sigma, d_sym, d_masks);
+  const uint64_t spans = nseq + nmore;
+  hipLaunchKernelGGL(stage_batch_kernel, dim3(stage_blocks(spans)), dim3(kStageThreads), 0, (hipStream_t)stream,
+                     b.codes, b.dev_off, b.len, b.sym_off, b.mask_off, nseq, d_more, spans, sigma, d_sym, d_masks);
   return hip_ok(hipGetLastError());
 }
 

@@ -221,17 +221,19 @@ static inline uint64_t round_up(uint64_t x, uint64_t a) { return (x + a - 1) / a
 
 namespace {
 // Parts of a batch's device allocation, in bytes, from the residues, the
-// stream bytes and the mask dwords: what is uploaded first (offsets, lengths,
-// codes), then what the GPU makes of it.
+// stream bytes, the mask dwords and the spans past the sequences' first: what
+// is uploaded first (offsets, lengths, spans, codes), then what the GPU makes
+// of it.
 struct BatchLayout {
-  uint64_t off[7], upload, total;
-  BatchLayout(uint64_t residues, uint64_t sb, uint64_t mw, uint32_t n) {
-    const uint64_t sz[7] = {8ull * (n + 1), 8ull * (n + 1), 8ull * (n + 1), 4ull * std::max<uint32_t>(n, 1),
-                            residues + 16, std::max<uint64_t>(sb, 16), mw * 4 + 16};
+  uint64_t off[8], upload, total;
+  BatchLayout(uint64_t residues, uint64_t sb, uint64_t mw, uint64_t nmore, uint32_t n) {
+    const uint64_t nn = n;
+    const uint64_t sz[8] = {8 * (nn + 1), 8 * (nn + 1), 8 * (nn + 1), 4 * std::max<uint64_t>(nn, 1),
+                            sizeof(StageSpan) * nmore, residues + 16, std::max<uint64_t>(sb, 16), mw * 4 + 16};
     total = upload = 0;
-    for (int i = 0; i < 7; ++i) {
+    for (int i = 0; i < 8; ++i) {
       off[i] = total;
-      if (i < 5) upload = total + sz[i];
+      if (i < 6) upload = total + sz[i];
       total += round_up(sz[i], 256);
     }
   }
@@ -239,13 +241,14 @@ struct BatchLayout {
 }  // namespace
 
 uint64_t DeviceBatchOwner::footprint(const uint64_t* seq_off, uint32_t nseq, uint32_t sigma) {
-  uint64_t words = 0, sb = 0;
+  uint64_t words = 0, sb = 0, nmore = 0;
   for (uint32_t i = 0; i < nseq; ++i) {
     const uint64_t L = seq_off[i + 1] - seq_off[i];
     words += (L + 31) / 32;
-    sb += ((L + 7) / 8 + 1) * 16;
+    sb += 2ull * stream_codes((uint32_t)L);
+    nmore += stage_more_spans((uint32_t)L);
   }
-  return BatchLayout(nseq ? seq_off[nseq] - seq_off[0] : 0, sb, words * sigma, nseq).total;
+  return BatchLayout(nseq ? seq_off[nseq] - seq_off[0] : 0, sb, words * sigma, nmore, nseq).total;
 }
 
 int DeviceBatchOwner::create(const uint8_t* hcodes, const uint64_t* seq_off, uint32_t n, uint32_t sig,
@@ -258,6 +261,7 @@ int DeviceBatchOwner::create(const uint8_t* hcodes, const uint64_t* seq_off, uin
   h_mask_off.resize(n + 1);
   h_sym_off.resize(n + 1);
   uint64_t mw = 0, sb = 0;
+  std::vector<StageSpan> more;
   const uint64_t base0 = n ? seq_off[0] : 0, residues = n ? seq_off[n] - base0 : 0;
   max_len = 0;
   for (uint32_t i = 0; i < n; ++i) {
@@ -269,12 +273,13 @@ int DeviceBatchOwner::create(const uint8_t* hcodes, const uint64_t* seq_off, uin
     h_mask_off[i] = mw;
     mw += (uint64_t)((L + 31) / 32) * sigma;
     h_sym_off[i] = sb;  // ceil(L/8) 16-byte chunks plus one spare
-    sb += ((uint64_t)(L + 7) / 8 + 1) * 16;
+    sb += 2ull * stream_codes(L);
+    for (uint32_t x = 1; x <= stage_more_spans(L); ++x) more.push_back(StageSpan{i, x});
   }
   h_dev_off[n] = residues;
   h_mask_off[n] = mw;
   h_sym_off[n] = sb;
-  const BatchLayout lay(residues, sb, mw, n);
+  const BatchLayout lay(residues, sb, mw, more.size(), n);
   if (mem.bytes < lay.total) {
     const int rc = mem.alloc(lay.total);
     if (rc) return rc;
@@ -284,17 +289,19 @@ int DeviceBatchOwner::create(const uint8_t* hcodes, const uint64_t* seq_off, uin
   memcpy(up.data() + lay.off[1], h_mask_off.data(), 8ull * (n + 1));
   memcpy(up.data() + lay.off[2], h_sym_off.data(), 8ull * (n + 1));
   if (n) memcpy(up.data() + lay.off[3], h_len.data(), 4ull * n);
-  if (residues) memcpy(up.data() + lay.off[4], hcodes + base0, residues);
+  if (!more.empty()) memcpy(up.data() + lay.off[4], more.data(), sizeof(StageSpan) * more.size());
+  if (residues) memcpy(up.data() + lay.off[5], hcodes + base0, residues);
   uint8_t* base = mem.as<uint8_t>();
   dev_off = reinterpret_cast<uint64_t*>(base + lay.off[0]);
   mask_off = reinterpret_cast<uint64_t*>(base + lay.off[1]);
   sym_off = reinterpret_cast<uint64_t*>(base + lay.off[2]);
   len = reinterpret_cast<uint32_t*>(base + lay.off[3]);
-  codes = base + lay.off[4];
-  sym = base + lay.off[5];
-  masks = reinterpret_cast<uint32_t*>(base + lay.off[6]);
+  codes = base + lay.off[5];
+  sym = base + lay.off[6];
+  masks = reinterpret_cast<uint32_t*>(base + lay.off[7]);
   FAMSA_HIP(hipMemcpyAsync(base, up.data(), up.size(), hipMemcpyHostToDevice, s));
-  const int e = launch_stage_batch(view(), n, max_len, sigma, sym, masks, s);
+  const int e = launch_stage_batch(view(), n, reinterpret_cast<const StageSpan*>(base + lay.off[4]), more.size(), sigma,
+                                   sym, masks, s);
   if (e) return set_error(FAMSA_LCS_EDEVICE, "stage_batch launch failed: %s", hipGetErrorString((hipError_t)e));
   // the host source is freed on return: wait for the copy, or keep it
   if (wait) FAMSA_HIP(hipStreamSynchronize(s));
