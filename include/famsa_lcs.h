@@ -23,7 +23,11 @@
  *    rejected with FAMSA_LCS_EINVAL even on a machine without a GPU.
  *  - Host pointers are read during the call only; the library copies what it
  *    keeps.  Device and pinned memory the library allocates belongs to the
- *    object that allocated it and is freed by its release/destroy call.
+ *    object that allocated it and is freed by its release/destroy call, but
+ *    for released device blocks of 1 to 256 MB: up to 16 of them, 512 MB in
+ *    all, are kept for later objects until famsa_lcs_trim, an allocation of
+ *    the library that finds no room, or the process's end.  A plan or server
+ *    with an hbm_budget of its own neither takes nor leaves such blocks.
  *  - Sequence i of a batch is codes[seq_off[i] .. seq_off[i+1]); codes are
  *    symbol indices in [0, alphabet_size).  The paper's alphabet has 32
  *    codes (twenty amino acids plus special symbols; Methods, "Progressive
@@ -164,6 +168,11 @@ int famsa_lcs_tiles(famsa_lcs_plan_t* plan, uint64_t first_tile, famsa_lcs_tile_
  * tile buffers: the memory of the first stage of the method, Methods,
  * "Determination of the guide tree").  NULL is a no-op. */
 void famsa_lcs_release(famsa_lcs_plan_t* plan);
+
+/* Give the device blocks kept from released objects back to the driver (for
+ * other users of the device's memory in the process).  Objects that are alive
+ * keep theirs.  EINVAL if device < 0. */
+int famsa_lcs_trim(int device);
 
 /* Thread-local text of the last error ("" if none). */
 const char* famsa_lcs_last_error(void);

@@ -93,6 +93,8 @@ def lib():
         L.famsa_lcs_tiles.restype = ctypes.c_int
         L.famsa_lcs_release.argtypes = [vp]
         L.famsa_lcs_release.restype = None
+        L.famsa_lcs_trim.argtypes = [ctypes.c_int]
+        L.famsa_lcs_trim.restype = ctypes.c_int
         L.famsa_lcs_last_error.argtypes = []
         L.famsa_lcs_last_error.restype = ctypes.c_char_p
         L.famsa_lcs_plan_get_info.argtypes = [vp, ctypes.POINTER(PlanInfo)]
@@ -261,6 +263,11 @@ def profile_align(problems, subst, gap_costs, alphabet_size: Optional[int] = Non
                                     _ptr(score, ctypes.c_int64), _ptr(ops, ctypes.c_uint8),
                                     _ptr(ops_off, ctypes.c_uint64), _ptr(nops, ctypes.c_uint32)))
     return score[:n], [ops[a:a + k].copy() for a, k in zip(ops_off[:n].tolist(), nops.tolist())]
+
+
+def trim(device: int = 0) -> None:
+    """Give the device blocks kept from closed objects back to the driver."""
+    check(lib().famsa_lcs_trim(device))
 
 
 def profile_last_dp_ms() -> float:

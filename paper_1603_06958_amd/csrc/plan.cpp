@@ -593,6 +593,9 @@ int famsa_lcs_plan(const uint8_t* codes, const uint64_t* seq_off, uint32_t nseq,
   if (o.cols_per_item) p->lp.cols_per_item = o.cols_per_item;
   if (o.flags & FAMSA_LCS_LONG_SEGMENTED) p->lp.long_wl = 0;
 
+  for (DevMem* m : {&p->batch.mem, &p->d_work, &p->d_ctl, &p->d_plainwork[0], &p->d_plainwork[1], &p->d_carry[0],
+                    &p->d_carry[1], &p->d_out[0], &p->d_out[1]})
+    m->own = o.hbm_budget != 0;
   // budget: batch + descriptors + 2 step buffers (+ plain scratch)
   size_t freeb = 0, totalb = 0;
   if (hipMemGetInfo(&freeb, &totalb) != hipSuccess) return fail(set_error(FAMSA_LCS_EDEVICE, "hipMemGetInfo failed"));
@@ -678,6 +681,13 @@ int famsa_lcs_tiles(famsa_lcs_plan_t* p, uint64_t first_tile, famsa_lcs_tile_fn 
 }
 
 void famsa_lcs_release(famsa_lcs_plan_t* p) { delete p; }
+
+int famsa_lcs_trim(int device) {
+  clear_error();
+  if (device < 0) return set_error(FAMSA_LCS_EINVAL, "device %d < 0", device);
+  kept_empty(device);
+  return 0;
+}
 
 int famsa_lcs_autotune(famsa_lcs_plan_t* p, const char* cache_path) {
   clear_error();

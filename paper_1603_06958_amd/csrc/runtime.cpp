@@ -31,91 +31,49 @@ void clear_error() { g_err.clear(); }
 const char* last_error_text() { return g_err.c_str(); }
 
 namespace {
-struct Kept {
-  void* p;
-  size_t cap;
-  int device;
-};
-std::mutex g_kept_mu;
-std::vector<Kept> g_kept;  // oldest first
+KeptStore g_kept;
 
-void free_on(int device, void* p) {
+void free_block(const KeptBlock& b) {
   int cur = 0;
-  const bool move = hipGetDevice(&cur) == hipSuccess && cur != device && hipSetDevice(device) == hipSuccess;
-  (void)hipFree(p);
+  const bool move = hipGetDevice(&cur) == hipSuccess && cur != b.device && hipSetDevice(b.device) == hipSuccess;
+  (void)hipFree(b.p);
   if (move) (void)hipSetDevice(cur);
-}
-
-// Takes blocks out of the store until it holds at most `bytes` in `blocks`.
-void trim_kept(size_t bytes, size_t blocks) {
-  size_t held = 0;
-  for (const Kept& k : g_kept) held += k.cap;
-  while (!g_kept.empty() && (held > bytes || g_kept.size() > blocks)) {
-    held -= g_kept.front().cap;
-    free_on(g_kept.front().device, g_kept.front().p);
-    g_kept.erase(g_kept.begin());
-  }
 }
 }  // namespace
 
-size_t kept_bytes(int device) {
-  std::lock_guard<std::mutex> lock(g_kept_mu);
-  size_t held = 0;
-  for (const Kept& k : g_kept) held += k.device == device ? k.cap : 0;
-  return held;
-}
+size_t kept_bytes(int device) { return g_kept.held(device); }
+void kept_empty(int device) { g_kept.empty(device, free_block); }
 
 void DevMem::reset() {
   if (p) {
+    const KeptBlock b{p, bytes, device};
     int cur = 0;
-    const bool same = hipGetDevice(&cur) == hipSuccess && cur == device;
-    if (same && cap >= kKeptLeast && cap <= kKeptBlock && hipDeviceSynchronize() == hipSuccess) {
-      std::lock_guard<std::mutex> lock(g_kept_mu);
-      g_kept.push_back(Kept{p, cap, device});
-      trim_kept(kKeptBytes, kKeptBlocks);
-    } else {
-      free_on(device, p);
-    }
+    if (!own && bytes >= kKeptLeast && bytes <= kKeptBlock && hipGetDevice(&cur) == hipSuccess && cur == device &&
+        hipDeviceSynchronize() == hipSuccess)
+      g_kept.put(b, free_block);
+    else
+      free_block(b);
   }
   p = nullptr;
-  bytes = cap = 0;
+  bytes = 0;
 }
 
 int DevMem::alloc(size_t n) {
   reset();
   if (n == 0) n = 16;
   FAMSA_HIP(hipGetDevice(&device));
-  if (n >= kKeptLeast) {  // the smallest kept block that holds it, if that is not far larger
-    std::lock_guard<std::mutex> lock(g_kept_mu);
-    size_t best = g_kept.size();
-    for (size_t i = 0; i < g_kept.size(); ++i)
-      if (g_kept[i].device == device && g_kept[i].cap >= n && g_kept[i].cap / 2 <= n &&
-          (best == g_kept.size() || g_kept[i].cap < g_kept[best].cap))
-        best = i;
-    if (best < g_kept.size()) {
-      p = g_kept[best].p;
-      cap = g_kept[best].cap;
-      bytes = n;
-      g_kept.erase(g_kept.begin() + (long)best);
-      return 0;
-    }
-  }
-  hipError_t e = hipMalloc(&p, n);
-  if (e == hipErrorOutOfMemory) {
-    (void)hipGetLastError();
-    {
-      std::lock_guard<std::mutex> lock(g_kept_mu);
-      trim_kept(0, 0);
-    }
-    e = hipMalloc(&p, n);
-  }
-  if (e != hipSuccess) {
-    p = nullptr;
-    (void)hipGetLastError();
-    return set_error(e == hipErrorOutOfMemory ? FAMSA_LCS_ENOMEM : FAMSA_LCS_EDEVICE, "hipMalloc(%zu): %s", n,
-                     hipGetErrorString(e));
-  }
-  bytes = cap = n;
+  auto get = [](size_t want, void** q) -> int {
+    const hipError_t e = hipMalloc(q, want);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return (int)e;
+  };
+  KeptBlock b;
+  const int e = g_kept.allocate(device, n, !own, (int)hipErrorOutOfMemory, get, free_block, &b);
+  if (e)
+    return set_error(e == (int)hipErrorOutOfMemory ? FAMSA_LCS_ENOMEM : FAMSA_LCS_EDEVICE, "hipMalloc(%zu): %s", n,
+                     hipGetErrorString((hipError_t)e));
+  p = b.p;
+  bytes = b.bytes;
   return 0;
 }
 

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "../../include/famsa_lcs.h"
+#include "kept_store.h"
 #include "lcs_common.h"
 
 namespace famsa {
@@ -23,22 +24,19 @@ void clear_error();
     if (e_ != hipSuccess) return ::famsa::set_error(FAMSA_LCS_EDEVICE, "%s: %s", #call, hipGetErrorString(e_)); \
   } while (0)
 
-// RAII device / pinned buffers.  Device blocks of 1 MB and more are kept when
-// they are released and handed to later allocations of about their size:
-// getting and giving back such a block takes the driver 0.1 to 0.4 ms, more
-// than many calls' work.  Releasing one waits for the device, as freeing it
-// does, so a block in the store is in use on no stream.  The store holds at
-// most kKeptBytes in kKeptBlocks blocks (the oldest go first) and is emptied
-// before an allocation fails; a plan's or server's budget counts it as free.
-constexpr size_t kKeptBytes = 512u << 20, kKeptBlock = 256u << 20, kKeptLeast = 1u << 20;
-constexpr size_t kKeptBlocks = 16;
+// RAII device / pinned buffers.  Device blocks go to a store when they are
+// released (kept_store.h).  Releasing one waits for the device, as freeing it
+// does, so a block in the store is in use on no stream.  The store is emptied
+// before an allocation fails; a budget taken from the free memory counts it
+// as free.
 size_t kept_bytes(int device);  // held in the store for `device`
+void kept_empty(int device);    // gives those back
 
 struct DevMem {
   void* p = nullptr;
-  size_t bytes = 0;  // as asked for
-  size_t cap = 0;    // the block's size
+  size_t bytes = 0;  // the block's size: what was asked for, or an eighth more at most
   int device = 0;
+  bool own = false;  // takes no kept block and leaves none: for objects whose caller set a budget
   DevMem() = default;
   DevMem(const DevMem&) = delete;
   DevMem& operator=(const DevMem&) = delete;
@@ -48,8 +46,8 @@ struct DevMem {
       reset();
       std::swap(p, o.p);
       std::swap(bytes, o.bytes);
-      std::swap(cap, o.cap);
       device = o.device;
+      own = o.own;
     }
     return *this;
   }

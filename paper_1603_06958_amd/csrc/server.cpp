@@ -133,6 +133,7 @@ int famsa_lcs_server_s::admit() {
       continue;
     }
     j->dev.reset(new DeviceBatchOwner());
+    j->dev->mem.own = opt.hbm_budget != 0;
     if (reuse >= 0) {
       spare_bytes -= spare[reuse].bytes;
       j->dev->mem = std::move(spare[reuse]);
@@ -338,6 +339,7 @@ int famsa_lcs_server_create(const famsa_lcs_options* opt, famsa_lcs_server_t** o
   if (s->fixed >= s->budget) return set_error(FAMSA_LCS_ENOMEM, "budget %llu too small", (unsigned long long)s->budget);
   if ((rc = lib_stream(o.device, 0, &s->cs)) || (rc = lib_stream(o.device, kCopyStream, &s->xs))) return rc;
   for (auto& sl : s->slot) {
+    for (DevMem* m : {&sl.d_out, &sl.d_work, &sl.d_plainwork, &sl.d_carry}) m->own = o.hbm_budget != 0;
     FAMSA_HIP(hipEventCreateWithFlags(&sl.done, hipEventDisableTiming));
     if ((rc = sl.d_out.alloc(s->step_values * 4)) || (rc = sl.h_out.alloc(s->step_values * 4))) return rc;
   }
