@@ -75,34 +75,24 @@ struct NaView {  // device addresses inside one GPU's scratch
 
 __host__ __device__ inline InputCheck* na_check(uint8_t* base) { return reinterpret_cast<InputCheck*>(base + kOffCheck); }
 
-// Columns that the groups from `g` on walk: group h needs the positions after
-// its own first row, [64 h + 1, k).
-__host__ __device__ inline uint32_t na_columns(uint32_t k, uint32_t g) {
-  const uint32_t G = k >= 2 ? (k - 2) / kLanes + 1 : 0;  // groups with a pair: 64 h + 1 < k
-  return g >= G ? 0 : (G - g) * (k - 1) - kLanes * ((G - 1) * G / 2 - (g * g - g) / 2);
-}
-// Columns of group g's items, as the plan path cuts them: 1 / 256 of what is
-// left, 4 to 96 (which keeps 8,192 sequences within the item array).
-__host__ __device__ inline uint32_t na_run(uint32_t k, uint32_t g) {
-  const uint32_t lo = na_columns(k, 0) / 256, want = na_columns(k, g) / 256;
-  const uint32_t least = lo < 4 ? 4 : (lo < 16 ? lo : 16);
-  return want < least ? least : (want > 96 ? 96 : want);
-}
-__host__ __device__ inline uint32_t na_items(uint32_t k, uint32_t g) {
-  const uint32_t n = k - (kLanes * g + 1), c = na_run(k, g);
-  return (n + c - 1) / c;
-}
+struct NaResident {  // workgroups of each class that the GPU holds
+  uint32_t c0, c1, c2;
+};
 
 // The plan, by one workgroup.  Rows sorted longest first by a counting sort
 // (rows of one length in any order: their values do not depend on it); groups
 // of 64 consecutive sorted rows; column position q is sequence colmap[q], and
 // a pair lands in the upper-triangle row of its smaller index.
-__device__ void na_plan(const uint64_t* __restrict__ seq_off, uint32_t k, uint32_t maxlen, uint8_t* __restrict__ base) {
+// SMALL: every class goes in one launch.
+template <bool SMALL>
+__device__ void na_plan(const uint64_t* __restrict__ seq_off, uint32_t k, uint32_t maxlen, NaResident resident,
+                        uint8_t* __restrict__ base) {
   __shared__ uint32_t s_at[1024];  // rows longer than L, then the next place of a row of length L (at 1023 - L)
   __shared__ uint32_t s_wave[16];
   __shared__ uint16_t s_row[kNaMaxSeq], s_len[kNaMaxSeq];
-  __shared__ uint32_t s_first[kNaMaxGroups + 1];
+  __shared__ uint32_t s_first[kNaMaxGroups + 1], s_cols[kNaMaxGroups];
   __shared__ uint32_t s_err, s_cnt[3];
+  __shared__ uint64_t s_span[2];  // the family's first and last offset
   uint32_t* len = reinterpret_cast<uint32_t*>(base + kOffLen);
   uint64_t* sym_off = reinterpret_cast<uint64_t*>(base + kOffSymOff);
   uint64_t* mask_off = reinterpret_cast<uint64_t*>(base + kOffMaskOff);
@@ -125,6 +115,8 @@ __device__ void na_plan(const uint64_t* __restrict__ seq_off, uint32_t k, uint32
     sym_off[i] = (uint64_t)i * kNaSymSlot;
     mask_off[i] = (uint64_t)i * kNaMaskSlot;
     s_len[i] = (uint16_t)L;
+    if (i == 0) s_span[0] = a;
+    if (i == k - 1) s_span[1] = b;
     atomicAdd(&s_at[1023u - L], 1u);  // L <= 896
   }
   __syncthreads();
@@ -158,10 +150,20 @@ __device__ void na_plan(const uint64_t* __restrict__ seq_off, uint32_t k, uint32
     d.pad = 0;
     lanes[q] = d;
   }
-  const uint32_t G = k >= 2 ? (k - 2) / kLanes + 1 : 0;
+  const uint32_t G = na_groups(k);
   if (wave < 2) {  // a lane a group; items numbered by a prefix sum
     const uint32_t g = tid;
-    const uint32_t ni = g < G ? na_items(k, g) : 0u;
+    uint32_t ni = 0, W = 1, cols = 1;
+    int cls = 0;
+    if (g < G) {
+      W = max(1u, (s_len[s_row[kLanes * g]] + 31u) >> 5);  // dwords of the group's longest row
+      const uint32_t Q = (W + 3u) >> 2;
+      cls = Q <= (uint32_t)kClassQMax[0] ? 0 : (Q <= (uint32_t)kClassQMax[1] ? 1 : 2);
+      const uint32_t held = cls == 0 ? resident.c0 : (cls == 1 ? resident.c1 : resident.c2);
+      cols = na_cols(k, g, SMALL ? na_runs_small() : na_runs(k, s_span[1] - s_span[0], held));
+      ni = na_items(k, g, cols);
+      s_cols[g] = cols;
+    }
     uint32_t sum = ni;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
@@ -172,9 +174,6 @@ __device__ void na_plan(const uint64_t* __restrict__ seq_off, uint32_t k, uint32
     s_first[g] = sum - ni;  // within its wave
     if (g < G) {
       const uint32_t P = kLanes * g;
-      const uint32_t W = max(1u, (s_len[s_row[P]] + 31u) >> 5);
-      const uint32_t Q = (W + 3u) >> 2;
-      const int cls = Q <= (uint32_t)kClassQMax[0] ? 0 : (Q <= (uint32_t)kClassQMax[1] ? 1 : 2);
       GroupDesc gd;
       gd.lane_first = P;
       gd.nrows = min((uint32_t)kLanes, k - P);
@@ -192,7 +191,7 @@ __device__ void na_plan(const uint64_t* __restrict__ seq_off, uint32_t k, uint32
   }
   __syncthreads();
   for (uint32_t g = wave; g < G; g += kNaThreads / 64) {
-    const uint32_t f = s_first[g] + (g >= 64 ? s_wave[0] : 0u), ni = na_items(k, g), C = na_run(k, g);
+    const uint32_t f = s_first[g] + (g >= 64 ? s_wave[0] : 0u), C = s_cols[g], ni = na_items(k, g, C);
     for (uint32_t t = lane; t < ni; t += 64) {
       ItemDesc it;
       it.group = g;
@@ -258,12 +257,13 @@ __device__ void na_stage(const uint8_t* __restrict__ codes, const uint64_t* __re
   }
 }
 
+template <bool SMALL>
 __global__ __launch_bounds__(kNaThreads) void na_prep_kernel(const uint8_t* __restrict__ codes,
                                                              const uint64_t* __restrict__ seq_off, uint32_t k,
-                                                             uint32_t sigma, uint32_t maxlen,
+                                                             uint32_t sigma, uint32_t maxlen, NaResident resident,
                                                              uint8_t* __restrict__ base) {
   if (blockIdx.x == 0) {
-    na_plan(seq_off, k, maxlen, base);
+    na_plan<SMALL>(seq_off, k, maxlen, resident, base);
     return;
   }
   // no residue is read before the whole family's offsets are known to be valid: a sequence after an invalid one
@@ -345,10 +345,20 @@ int na_run(const uint8_t* codes, const uint64_t* seq_off, uint32_t nseq, uint32_
   uint8_t* base = d->ptr;
   const int s32 = sig_cap(sigma) == 32 ? 1 : 0;
   const uint32_t maxlen = s32 ? kNaMaxLen32 : kNaMaxLen20;
-  const uint32_t per = kNaThreads / kNaTeam, stage = std::min((nseq + per - 1) / per, kNaStageBlocks);
-  hipLaunchKernelGGL(na_prep_kernel, dim3(1 + stage), dim3(kNaThreads), 0, st, codes, seq_off, nseq, sigma, maxlen, base);
-  FAMSA_HIP(hipGetLastError());
   const uint64_t npairs = (uint64_t)nseq * (nseq ? nseq - 1 : 0) / 2;
+  uint32_t n = na_all_items(nseq, na_runs_small());
+  const bool small = n <= 2u * (uint32_t)d->cus;  // as the plan path's small steps; the widest group is not known here
+  if (!small) n = na_all_items(nseq, na_runs_most());
+  if (n > kNaMaxItems) return set_error(FAMSA_LCS_EINVAL, "%u work items", n);  // never: 7,816 at most
+  const uint32_t per = kNaThreads / kNaTeam, stage = std::min((nseq + per - 1) / per, kNaStageBlocks);
+  const NaResident resident{d->blocks[s32][0], d->blocks[s32][1], d->blocks[s32][2]};
+  auto prep = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(1 + stage), dim3(kNaThreads), 0, st, codes, seq_off, nseq, sigma, maxlen, resident,
+                       base);
+  };
+  if (small) prep(na_prep_kernel<true>);
+  else prep(na_prep_kernel<false>);
+  FAMSA_HIP(hipGetLastError());
   if (npairs) {
     DeviceBatch b{};
     b.sym = base + kOffSym;
@@ -365,12 +375,9 @@ int na_run(const uint8_t* codes, const uint64_t* seq_off, uint32_t nseq, uint32_
     w.rowbase = reinterpret_cast<const uint64_t*>(base + kOffRowbase);
     w.ranges = reinterpret_cast<const StepRange*>(base + kOffRange);
     StepCtl* ctl = reinterpret_cast<StepCtl*>(base + kOffCtl);
-    uint32_t n = 0;  // items: their number does not depend on the lengths
-    for (uint32_t g = 0; g * kLanes + 1 < nseq; ++g) n += na_items(nseq, g);
-    if (n > kNaMaxItems) return set_error(FAMSA_LCS_EINVAL, "%u work items", n);  // never: 8,192 sequences give 5,986
-    if (n <= 2u * (uint32_t)d->cus) {  // as the plan path's small steps; the widest group is not known here
+    if (small) {
       const int e = launch_small(b, w, ctl, out, sigma, na_qcap(s32, 2), std::min(n, (uint32_t)d->cus),
-                                 std::min(16u, na_run(nseq, 0)), na_check(base), status, npairs, st);
+                                 std::min(16u, na_cols(nseq, 0, na_runs_small())), na_check(base), status, npairs, st);
       if (e) return set_error(FAMSA_LCS_EDEVICE, "lcs_small launch failed: %s", hipGetErrorString((hipError_t)e));
       return 0;
     }

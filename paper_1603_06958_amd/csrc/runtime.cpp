@@ -276,6 +276,14 @@ int class_of(uint32_t W, uint32_t sigma) {
   return 3;
 }
 
+// Workgroups of a fast class that a CU holds at once: by the waves its
+// registers allow (eight a SIMD in classes 0 and 1, four in class 2) and by its LDS.
+static uint32_t resident_blocks(int cls, uint32_t sigma, uint32_t q, uint32_t waves) {
+  const uint32_t by_waves = (cls < 2 ? 32u : 16u) / std::max(waves, 1u);
+  const uint32_t by_lds = (uint32_t)(g_max_lds / (fast_lds_bytes(sigma, q) + kLdsReserve));
+  return std::max(1u, std::min(by_waves, by_lds));
+}
+
 uint32_t skew_lanes(uint32_t W, uint32_t sigma, const LaunchParams& lp) {
   if (lp.long_wl == 0) return 0;
   const uint32_t wmax = std::min(lp.long_wl, skew_wl_max(sigma));
@@ -493,17 +501,23 @@ void build_step(WorkLists& wl, const std::vector<StepFamily>& fams, const std::v
   // the group's masks over many columns, but the workgroups that take a
   // class's last items finish up to an item apart, and the next launch waits
   // for them.  So a class is cut from its widest group on into items of
-  // 1 / kSlots of the work that is still left, at most the configured columns
+  // 1 / slots of the work that is still left, at most the configured columns
   // and at least a column for each wave of a large workgroup; a class with
   // fewer columns than that for every workgroup goes down to four (a column a
-  // SIMD).  Measured (LCS kernels of a pass): k = 20,000 of 250 residues in
-  // uniform runs of 256 columns 28.8 ms, of 64 25.4 ms, these 25.3 ms; 24
-  // families of up to 1,500 sequences of 30 to 2,000 residues 4.77 and 4.85
-  // against 4.4 ms; k = 300 of 250 residues, in runs of 16, 0.17 against 0.08
-  // ms.  Smallest runs of 4 or 8 columns everywhere cost 3 to 12% of the
-  // second (a wave without a column waits for its item).
+  // SIMD).  slots: the workgroups that share the class, which are those the
+  // GPU holds at once, but no more than get kSlotWork residues of columns for
+  // each of their waves, and one a CU at least.  With more than one a CU a run
+  // is also at least kLeastWork residues for each wave, as far as every slot
+  // has that much: an item costs its place in the queue (about 20 ns, one after
+  // another), which rows of 30 to 80 residues feel.
+  // Measured (k = 20,000 of 250 residues, LCS kernels): uniform runs of 256
+  // columns 28.8 ms, of 64 25.4 ms, these 22.7 ms (a whole pass); 24 families
+  // of up to 1,500 sequences of 30 to 2,000 residues, whole pass: uniform 2.63,
+  // these 2.38 ms.  Single families, whole pass, in uniform runs of 16 / cut
+  // for one workgroup a CU in every class / these: 2,900 of 100 residues
+  // 197 / 251 / 186 us, 2,000 of 200 277 / 338 / 246, 3,500 of 250 934 / 1,121 /
+  // 844, 700 of 30 87 / 70 / 69, 5,000 of 45 202 / 175 / 181.
   const uint32_t cmax = lp.cols_per_item ? lp.cols_per_item : 128;
-  constexpr uint64_t kSlots = 256;  // workgroups that share a class: a CU each
   StepSig sig;
   auto wlane = [](const GroupDesc& g) -> uint64_t { return g.lpr ? (g.W + g.lpr - 1) / g.lpr : g.W; };  // dwords per lane
   auto colsum = [&](const PendingGroup& pg, uint32_t c0, uint32_t c1) {
@@ -512,7 +526,7 @@ void build_step(WorkLists& wl, const std::vector<StepFamily>& fams, const std::v
   std::vector<uint32_t> by(pend.size());  // widest first; the lists keep the groups' own order
   std::iota(by.begin(), by.end(), 0u);
   std::stable_sort(by.begin(), by.end(), [&](uint32_t a, uint32_t b) { return wlane(pend[a].g) > wlane(pend[b].g); });
-  uint64_t left[4] = {0, 0, 0, 0}, ncols[4] = {0, 0, 0, 0};
+  uint64_t left[4] = {0, 0, 0, 0}, ncols[4] = {0, 0, 0, 0}, residues[4] = {0, 0, 0, 0};
   const uint32_t g0 = (uint32_t)wl.groups.size();
   for (const PendingGroup& pg : pend) {
     wl.groups.push_back(pg.g);
@@ -527,23 +541,57 @@ void build_step(WorkLists& wl, const std::vector<StepFamily>& fams, const std::v
     }
     left[cls] += wlane(pg.g) * colsum(pg, pg.c0, pg.c1);
     ncols[cls] += pg.c1 - pg.c0;
+    residues[cls] += colsum(pg, pg.c0, pg.c1);
   }
-  for (uint32_t x : by) {
-    const PendingGroup& pg = pend[x];
-    const int cls = class_of(pg.g.W, sigma);
-    const uint64_t w = wlane(pg.g);
-    const uint32_t cmin = std::min<uint32_t>(cmax, (uint32_t)std::min<uint64_t>(16, std::max<uint64_t>(4, ncols[cls] / kSlots)));
-    const uint64_t per = std::max<uint64_t>(1, w * colsum(pg, pg.c0, pg.c1) / (pg.c1 - pg.c0));  // a column's cost
-    for (uint32_t c = pg.c0; c < pg.c1;) {
-      const uint64_t want = left[cls] / kSlots / per;
-      uint32_t n = (uint32_t)std::max<uint64_t>(cmin, std::min<uint64_t>(cmax, want));
-      if (n > 16) n -= n % 16;
-      const uint32_t c1 = pg.c1 - c <= n ? pg.c1 : c + n;
-      const uint64_t cost = w * colsum(pg, c, c1);
-      ci[cls].push_back(CostItem{cost + 64, ItemDesc{g0 + x, c, c1, 0}});
-      left[cls] -= std::min(left[cls], cost);
-      c = c1;
+  constexpr uint64_t kCus = 256, kSlotWork = 500, kLeastWork = 200;
+  auto cut = [&](const uint64_t (&slots)[4]) {
+    uint64_t rest[4] = {left[0], left[1], left[2], left[3]};
+    for (auto& v : ci) v.clear();
+    for (uint32_t x : by) {
+      const PendingGroup& pg = pend[x];
+      const int cls = class_of(pg.g.W, sigma);
+      const uint64_t w = wlane(pg.g);
+      const uint64_t share = ncols[cls] / slots[cls];  // columns a slot
+      uint32_t cmin = std::min<uint32_t>(cmax, (uint32_t)std::min<uint64_t>(16, std::max<uint64_t>(4, share)));
+      if (slots[cls] > kCus) {
+        const uint64_t len = std::max<uint64_t>(1, colsum(pg, pg.c0, pg.c1) / (pg.c1 - pg.c0));
+        cmin = std::max(cmin, (uint32_t)std::min<uint64_t>({cmax, kLeastWork * lp.waves[cls] / len, share}));
+      }
+      const uint64_t per = std::max<uint64_t>(1, w * colsum(pg, pg.c0, pg.c1) / (pg.c1 - pg.c0));  // a column's cost
+      for (uint32_t c = pg.c0; c < pg.c1;) {
+        const uint64_t want = rest[cls] / slots[cls] / per;
+        uint32_t n = (uint32_t)std::max<uint64_t>(cmin, std::min<uint64_t>(cmax, want));
+        if (n > 16) n -= n % 16;
+        const uint32_t c1 = pg.c1 - c <= n ? pg.c1 : c + n;
+        const uint64_t cost = w * colsum(pg, c, c1);
+        ci[cls].push_back(CostItem{cost + 64, ItemDesc{g0 + x, c, c1, 0}});
+        rest[cls] -= std::min(rest[cls], cost);
+        c = c1;
+      }
     }
+    return (uint32_t)(ci[0].size() + ci[1].size() + ci[2].size());
+  };
+  // A step with at most two items a CU takes about as long as its longest
+  // column in every class it launches, so its classes share one launch (which
+  // holds one workgroup a CU, for its LDS is the widest group's).
+  const bool several = (sig.q[0] != 0) + (sig.q[1] != 0) + (sig.q[2] != 0) > 1;
+  const uint64_t fast_cols = ncols[0] + ncols[1] + ncols[2];
+  if (several && fast_cols <= 2 * kCus * cmax && cut({kCus, kCus, kCus, kCus}) <= 2 * kCus) {
+    uint32_t widest_run = 4, items = 0;
+    for (int c = 0; c < 3; ++c) {
+      items += (uint32_t)ci[c].size();
+      for (const CostItem& x : ci[c]) widest_run = std::max(widest_run, x.it.c1 - x.it.c0);
+    }
+    sig.small = (uint8_t)std::min<uint32_t>(16, widest_run);
+    wl.max_small_items = std::max(wl.max_small_items, items);
+  } else {
+    uint64_t slots[4] = {kCus, kCus, kCus, kCus};
+    for (int c = 0; c < 3; ++c)
+      if (sig.q[c]) {
+        const uint64_t held = kCus * resident_blocks(c, sigma, sig.q[c], lp.waves[c]);
+        slots[c] = std::max(kCus, std::min(held, residues[c] / (kSlotWork * std::max(lp.waves[c], 1u))));
+      }
+    cut(slots);
   }
   for (int c = 0; c < 4; ++c) {
     std::stable_sort(ci[c].begin(), ci[c].end(), [](const CostItem& a, const CostItem& b) { return a.cost > b.cost; });
@@ -551,19 +599,6 @@ void build_step(WorkLists& wl, const std::vector<StepFamily>& fams, const std::v
     for (const CostItem& x : ci[c]) wl.items.push_back(x.it);
     r.end[c] = (uint32_t)wl.items.size();
     wl.max_items[c] = std::max(wl.max_items[c], r.end[c] - r.begin[c]);
-  }
-  // A step with at most two items a CU takes about as long as its longest
-  // column in every class it launches, so its classes share one launch (which
-  // holds one workgroup a CU, for its LDS is the widest group's).
-  uint32_t fast_items = 0, classes = 0, widest_run = 4;
-  for (int c = 0; c < 3; ++c) {
-    fast_items += r.end[c] - r.begin[c];
-    classes += r.end[c] > r.begin[c];
-    for (const CostItem& x : ci[c]) widest_run = std::max(widest_run, x.it.c1 - x.it.c0);
-  }
-  if (classes > 1 && fast_items <= 2 * kSlots) {
-    sig.small = (uint8_t)std::min<uint32_t>(16, widest_run);
-    wl.max_small_items = std::max(wl.max_small_items, fast_items);
   }
   r.begin[4] = (uint32_t)wl.prows.size();
   wl.prows.insert(wl.prows.end(), pr.begin(), pr.end());
