@@ -179,7 +179,7 @@ const char* famsa_lcs_last_error(void);
 
 typedef struct famsa_lcs_plan_info {
   uint64_t ntiles;         /* tiles delivered by a full famsa_lcs_tiles call */
-  uint64_t nsteps;         /* launch steps (each one kernel launch per length class) */
+  uint64_t nsteps;         /* launch steps (each one kernel launch per length class, or one for several) */
   uint64_t pairs;          /* sum over families of k(k-1)/2 */
   uint64_t cells;          /* sum over pairs of |A||B| */
   uint64_t device_bytes;   /* device memory the plan holds */
@@ -211,7 +211,8 @@ int famsa_lcs_plan_dry_run(const uint8_t* codes, const uint64_t* seq_off, uint32
 typedef struct famsa_lcs_stats {
   double kernel_ms[5];     /* summed duration per kernel: [0] rows of <= 256 residues, [1] <= 384, [2] <= 896
                               (<= 512 with more than 20 symbols), [3] longer rows, in segments,
-                              [4] plain one-pair-per-lane baseline (FAMSA_LCS_PLAIN) */
+                              [4] plain one-pair-per-lane baseline (FAMSA_LCS_PLAIN); a small step whose
+                              first three kinds share one launch counts for the longest of them */
   uint64_t launches[5];
   uint64_t cells[5];       /* algorithmic cells |A||B| assigned to each kernel over the whole plan */
   double step_ms;          /* summed device time of the launch steps (all kernels of a step) */

@@ -713,19 +713,13 @@ int StepExec::enqueue(const StepSig& sig, const DeviceBatch& b, const DeviceWork
     if (e) return set_error(FAMSA_LCS_EDEVICE, "lcs_long launch failed: %s", hipGetErrorString((hipError_t)e));
     if (ev) FAMSA_HIP(hipEventRecord(ev[7], s));
   }
-  if (sig.small) {  // timed as the widest class
-    bool timed = false;
-    for (int c = 2; c >= 0; --c) {
-      if (!sig.q[c]) continue;
-      if (ev) FAMSA_HIP(hipEventRecord(ev[2 * c], s));
-      if (!timed) {
-        timed = true;
-        e = launch_small(b, w, ctl, out, sigma, sig.widest(), std::min((uint32_t)cus, small_items), sig.small, nullptr,
-                         nullptr, 0, s);
-        if (e) return set_error(FAMSA_LCS_EDEVICE, "lcs_small launch failed: %s", hipGetErrorString((hipError_t)e));
-      }
-      if (ev) FAMSA_HIP(hipEventRecord(ev[2 * c + 1], s));
-    }
+  if (sig.small) {
+    const int c = sig.widest_class();
+    if (ev) FAMSA_HIP(hipEventRecord(ev[2 * c], s));
+    e = launch_small(b, w, ctl, out, sigma, sig.widest(), std::min((uint32_t)cus, small_items), sig.small, nullptr,
+                     nullptr, 0, s);
+    if (e) return set_error(FAMSA_LCS_EDEVICE, "lcs_small launch failed: %s", hipGetErrorString((hipError_t)e));
+    if (ev) FAMSA_HIP(hipEventRecord(ev[2 * c + 1], s));
   }
   for (int c = 2; c >= 0 && !sig.small; --c) {
     const uint32_t q = sig.q[c];

@@ -180,7 +180,12 @@ struct StepSig {
     return (uint64_t)q[0] | ((uint64_t)q[1] << 8) | ((uint64_t)q[2] << 16) | ((uint64_t)lng << 24) |
            ((uint64_t)plain << 32) | ((uint64_t)small << 40);
   }
-  bool has(int c) const { return c < 3 ? q[c] != 0 : (c == 3 ? lng != 0 : plain != 0); }
+  int widest_class() const { return q[2] ? 2 : (q[1] ? 1 : 0); }
+  // Whether the step launches class c's kernel (one launch for several classes counts for the widest).
+  bool has(int c) const {
+    if (c >= 3) return c == 3 ? lng != 0 : plain != 0;
+    return q[c] != 0 && (!small || c == widest_class());
+  }
 };
 
 // Host copies of the descriptor arrays for one or more steps.
