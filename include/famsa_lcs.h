@@ -522,8 +522,9 @@ int famsa_gap_costs_scaled(uint32_t k, const double* base, double gl, double gd,
  * Calls on one GPU share its array: two calls whose work overlaps on the
  * device (different streams, or different host threads) race and give wrong
  * results; calls ordered on one stream are safe.
- * Errors (returned, nothing queued): EINVAL (alphabet_size, nseq over the
- * limit, NULL pointer, bad device), EDEVICE (a HIP call failed).
+ * Errors (returned): EINVAL (alphabet_size, nseq over the limit, NULL
+ * pointer, bad device; nothing is queued), EDEVICE (a HIP call failed; no
+ * value of out is defined).
  * ------------------------------------------------------------------------ */
 #define FAMSA_LCS_NOALLOC_MAX_SEQ 8192u
 #define FAMSA_LCS_NOALLOC_MAX_LEN 896u

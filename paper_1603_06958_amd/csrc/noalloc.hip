@@ -359,6 +359,13 @@ int na_run(const uint8_t* codes, const uint64_t* seq_off, uint32_t nseq, uint32_
   if (small) prep(na_prep_kernel<true>);
   else prep(na_prep_kernel<false>);
   FAMSA_HIP(hipGetLastError());
+  // A launch after this one that fails: the call is still ended on the device, so that what it found of its input
+  // is not taken for the next call's.
+  auto failed = [&](const char* kernel, int e) {
+    hipLaunchKernelGGL(na_finish_kernel, dim3(1), dim3(256), 0, st, base, out, (uint64_t)0, (int32_t*)nullptr);
+    (void)hipGetLastError();
+    return set_error(FAMSA_LCS_EDEVICE, "%s launch failed: %s", kernel, hipGetErrorString((hipError_t)e));
+  };
   if (npairs) {
     DeviceBatch b{};
     b.sym = base + kOffSym;
@@ -378,13 +385,12 @@ int na_run(const uint8_t* codes, const uint64_t* seq_off, uint32_t nseq, uint32_
     if (small) {
       const int e = launch_small(b, w, ctl, out, sigma, na_qcap(s32, 2), std::min(n, (uint32_t)d->cus),
                                  std::min(16u, na_cols(nseq, 0, na_runs_small())), na_check(base), status, npairs, st);
-      if (e) return set_error(FAMSA_LCS_EDEVICE, "lcs_small launch failed: %s", hipGetErrorString((hipError_t)e));
-      return 0;
+      return e ? failed("lcs_small", e) : 0;
     }
     for (int c = 2; c >= 0; --c) {  // heaviest class first; a class with no items returns at once
       const int e = launch_fast(c, b, w, ctl, out, sigma, na_qcap(s32, c), std::min(n, d->blocks[s32][c]),
                                 d->waves[s32][c], st);
-      if (e) return set_error(FAMSA_LCS_EDEVICE, "lcs_fast<%d> launch failed: %s", c, hipGetErrorString((hipError_t)e));
+      if (e) return failed("lcs_fast", e);
     }
   }
   hipLaunchKernelGGL(na_finish_kernel, dim3(npairs ? 256 : 1), dim3(256), 0, st, base, out, npairs, status);
