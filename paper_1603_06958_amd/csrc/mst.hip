@@ -399,6 +399,85 @@ __global__ __launch_bounds__(64 * kFiltWaves) void mst_filter(MstDev m, const Ms
   }
 }
 
+// Rows a..b-1 of the tile, whose vertices the forest does not reach yet, are
+// tied to the vertices from `cover` on, which it joins (cover >= b): every row's
+// best pair with one of those (by the similarity in single precision: any pair
+// would do, a good one lets fewer pairs through the pass) goes into the list of
+// survivors at `at`, and the row's vertex takes its partner's place in the
+// hierarchy, as a leaf on it: the partner's labels, and the worse of the
+// partner's bound and the new edge.  (Too low a bound in the partner's lowest
+// rounds, where the path is the new edge alone; that only lets more through.)
+// With cover 0 the best pair may be with any later vertex, so rows that are like each
+// other but not like the forest's find each other (every edge leads to a later
+// vertex, so these edges close no cycle); the hierarchy is then the next update's.
+// A wave a row, eight loads in flight: 1,024 rows of 9,000 columns 20 us.
+constexpr uint32_t kAttachRows = 4;  // of a block
+
+__global__ __launch_bounds__(64 * kAttachRows) void mst_attach(MstDev m, const int32_t* __restrict__ tile, uint32_t r0,
+                                                               uint32_t a, uint32_t b, uint32_t cover, uint32_t at) {
+  const uint32_t lane = threadIdx.x & 63u, i = a + blockIdx.x * kAttachRows + (threadIdx.x >> 6), k = m.k;
+  if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd((unsigned long long*)&m.ps->surv, (unsigned long long)(b - a));
+  if (i >= b) return;
+  const uint32_t li = m.len[i];
+  const int32_t* row = tile + row_off(k, r0, i) - (uint64_t)(i + 1);  // row[j]: the pair (i, j)
+  const uint32_t from = max(cover, i + 1u);
+  float best = -1.0f;
+  uint32_t bj = from;
+  int32_t bL = 0;
+  for (uint32_t j0 = from; j0 < k; j0 += 8 * 64) {
+    int32_t L[8];
+    uint32_t lj[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const uint32_t j = min(j0 + 64u * u + lane, k - 1u);
+      L[u] = row[j];
+      lj[u] = m.len[j];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {  // a repeated last column changes nothing
+      const float d = (float)((int32_t)(li + lj[u]) - 2 * L[u]);
+      const float f = d == 0.0f ? __builtin_inff() : (float)L[u] / (d * d);
+      if (f > best) {
+        best = f;
+        bj = min(j0 + 64u * u + lane, k - 1u);
+        bL = L[u];
+      }
+    }
+  }
+#pragma unroll
+  for (int x = 32; x >= 1; x >>= 1) {
+    const float f = __shfl_xor(best, x, 64);
+    const uint32_t j = (uint32_t)__shfl_xor((int)bj, x, 64);
+    const int32_t L = __shfl_xor(bL, x, 64);
+    if (f > best || (f == best && j < bj)) {
+      best = f;
+      bj = j;
+      bL = L;
+    }
+  }
+  const uint64_t key = sim_key(bL, li, m.len[bj]), id = (uint64_t)i * k + bj;
+  if (lane == 0) {
+    const uint32_t e = m.ctl->nf + at + (i - a);
+    m.eu[e] = i;
+    m.ev[e] = bj;
+    m.ekey[e] = key;
+    m.eL[e] = bL;
+  }
+  if (cover != 0 && lane < kMstSlots) {
+    const uint32_t lab = m.view[bj].label[lane];
+    const bool in = lab >= k;  // a round of the hierarchy (the forest joins bj: every round has relabelled it)
+    uint64_t wk = key, wi = id;
+    if (in && better(wk, wi, m.exact[bj].key[lane], m.exact[bj].id[lane])) {
+      wk = m.exact[bj].key[lane];
+      wi = m.exact[bj].id[lane];
+    }
+    m.view[i].label[lane] = in ? lab : i;
+    m.view[i].bound[lane] = in ? (float)(__longlong_as_double((long long)(wk - 1ull)) * (1.0 - 0x1p-20)) : -1.0f;
+    m.exact[i].key[lane] = wk;
+    m.exact[i].id[lane] = wi;
+  }
+}
+
 // Boruvka round r, in four launches over the whole GPU while there are more
 // components or edges than one workgroup takes.  mst_edges: edges get their
 // ends' labels in this round, those inside a component are dropped, the
@@ -797,7 +876,7 @@ using namespace famsa;
 struct famsa_mst_s {
   uint32_t k = 0;
   int device = 0;
-  uint32_t surv_cap = 0;       // survivors an update holds: at least eight rows' pairs
+  uint32_t surv_cap = 0;       // survivors an update holds: at least one row's pairs
   uint32_t cover = 0xFFFFFFFFu;  // the forest joins all vertices from this one on
   DevMem mem;                  // every array below, in one allocation
   MstDev dev{};
@@ -809,6 +888,7 @@ struct famsa_mst_s {
   hipEvent_t last = nullptr;
   hipEvent_t read = nullptr;  // the last pass over a tile is done
   bool has_last = false;
+  bool kinds = false;    // a block of rows tied to the forest by its own vertices alone let too many pairs through
   uint32_t pending = 0;  // survivors that the forest has not taken in yet
   uint32_t blocks = 0;   // of the passes they are from
   std::mutex mu;         // reading the forest takes them in
@@ -826,6 +906,10 @@ struct famsa_mst_s {
   int filter(const famsa_lcs_tile* t, const Rows& rows, bool take, hipStream_t s, bool* fits);
   int update(uint32_t n, uint64_t most, hipStream_t s);
   int settle();
+  int attach(const famsa_lcs_tile* t, uint32_t a, uint32_t b, uint32_t from, hipStream_t s);
+  int merge_block(const famsa_lcs_tile* t, uint32_t a, uint32_t b, bool more, hipStream_t s);
+  int merge_rows(const famsa_lcs_tile* t, const Rows& rows, bool covered, hipStream_t s);
+  int merge_upwards(const famsa_lcs_tile* t, hipStream_t s);
   int merge_tile(const famsa_lcs_tile* t, hipStream_t s);
 };
 
@@ -908,7 +992,7 @@ int famsa_mst_s::filter(const famsa_lcs_tile* t, const Rows& rows, bool take, hi
   FAMSA_HIP(hipGetLastError());
   if (take) {
     FAMSA_HIP(hipEventRecord(read, s));
-    const int rc = update(kAll, (uint64_t)nrows * (k - 1), s);
+    const int rc = update(kAll, (uint64_t)nrows * (k - 1 - (r0 + rows.t0 * rows.stride)), s);
     if (rc) return rc;
     FAMSA_HIP(hipEventSynchronize(read));
     *fits = *static_cast<volatile uint32_t*>(hflag.p) <= surv_cap;
@@ -944,8 +1028,11 @@ int famsa_mst_s::update(uint32_t n, uint64_t most, hipStream_t s) {
   // many survivors: one workgroup takes 82 us and more over what two rounds
   // leave of 70,000 edges, a round on the whole GPU 30 (k = 12,000 sequences
   // of 60 residues in all: 3.2 ms with no more rounds, 2.9 with two, 2.6 with
-  // four, 2.6 with five); for few components its rounds are the faster ones
-  if (most > 2 * kFinEdges) rounds += k > kFinComps ? 4 : 2;
+  // four, 2.6 with five).  With no more components than it takes from the
+  // start, most edges stay between two of them round after round: k = 4,000 in
+  // one tile, LCS and all, 998 us with two rounds whatever the edges, 936 with
+  // two or four, 905 with three or five
+  if (most > 2 * kFinEdges) rounds += k > kFinComps ? 4 : (most > 4 * kFinEdges ? 5 : 3);
   most += k;  // edges
   const dim3 ge(grid_for(most, kEdgeThreads)), gc(grid_for(k, kEdgeThreads)), b(kEdgeThreads);
   for (uint32_t r = 0; r < rounds; ++r) {
@@ -989,24 +1076,15 @@ int famsa_mst_s::settle() {
 // residues take 4.0 ms with an update each, 3.2 with one every two survivors a
 // vertex, 2.6 every five, 2.5 every eight; k = 30,000 of 250 66.0, 64.9, 64.4
 // and 64.1.
-// Where the forest does not join the tile's vertices yet (the first tile;
-// every tile in descending order), or the survivors of a whole tile do not
-// fit, the rows are taken in passes of growing size spread over the tile,
-// every 8^n-th row first, with an update after each: the first pass always
-// fits, and each pass's forest then drops most pairs of the next (a row seldom
-// beats eight times as many like it).  A pass whose survivors do not fit is
-// halved.
-int famsa_mst_s::merge_tile(const famsa_lcs_tile* t, hipStream_t s) {
-  const uint32_t r0 = t->row_begin, r1 = t->row_end;
-  if (r1 - r0 > 65535u) return set_error(FAMSA_LCS_EINVAL, "tiles of more than 65535 rows are not supported");
-  if (!t->count) {
-    ++tiles;
-    return 0;
-  }
-  if (has_last) FAMSA_HIP(hipStreamWaitEvent(s, last, 0));  // the previous tile's merge, on any stream
-  const uint32_t R = std::min(r1, k - 1) - r0;  // rows with a pair
-  const bool covered = r0 >= cover;
-  const uint32_t first = std::max(8u, surv_cap / k);  // rows whose pairs fit, all of them
+// Where the forest does not join the rows' vertices yet, or the survivors of all
+// rows do not fit, the rows are taken in passes of growing size spread over
+// them, every 8^n-th row first, with an update after each: the first pass fits
+// (one row's pairs always do), and each pass's forest then drops most pairs of
+// the next (a row seldom beats eight times as many like it).  A pass whose
+// survivors do not fit is halved.
+int famsa_mst_s::merge_rows(const famsa_lcs_tile* t, const Rows& all, bool covered, hipStream_t s) {
+  const uint32_t R = all.t1 - all.t0;
+  const uint32_t first = std::max(1u, surv_cap / k);  // rows whose pairs fit, all of them
   const uint32_t wait = (uint32_t)std::min(6ull * k, surv_cap / 3ull);
   std::vector<Rows> todo;  // last first
   auto passes = [&]() {
@@ -1019,7 +1097,10 @@ int famsa_mst_s::merge_tile(const famsa_lcs_tile* t, hipStream_t s) {
     }
     todo.insert(todo.end(), p.rbegin(), p.rend());
   };
-  if (covered || t->count <= surv_cap) todo.push_back(Rows{0, R, 1, 0});
+  uint64_t pairs = 0;
+  for (uint32_t x = all.t0; x < all.t1 && pairs <= surv_cap; ++x) pairs += k - 1 - (t->row_begin + x);
+  const bool spread = all.t0 == 0;  // passes count a tile's rows from its first
+  if (covered || pairs <= surv_cap || !spread) todo.push_back(all);
   else passes();
   while (!todo.empty()) {
     const Rows rows = todo.back();
@@ -1045,13 +1126,107 @@ int famsa_mst_s::merge_tile(const famsa_lcs_tile* t, hipStream_t s) {
       continue;
     }
     if (rows.t1 - rows.t0 <= 1) return set_error(FAMSA_LCS_EDEVICE, "one row's pairs do not fit");
-    if (rows.stride == 1 && rows.skip == 0 && rows.t0 == 0 && rows.t1 == R && R > 8) {
+    if (spread && rows.stride == 1 && rows.skip == 0 && rows.t0 == 0 && rows.t1 == R && R > 8) {
       passes();
     } else {
       todo.push_back(Rows{mid, rows.t1, rows.stride, rows.skip});
       todo.push_back(Rows{rows.t0, mid, rows.stride, rows.skip});
     }
   }
+  return 0;
+}
+
+// Ties rows a..b-1 (family-local) of the tile to the forest (from = cover), or
+// to any later vertex (from = 0).
+int famsa_mst_s::attach(const famsa_lcs_tile* t, uint32_t a, uint32_t b, uint32_t from, hipStream_t s) {
+  int rc = 0;
+  if (pending + (b - a) > surv_cap && (rc = update(pending, pending, s))) return rc;
+  hipLaunchKernelGGL(mst_attach, dim3((b - a + kAttachRows - 1) / kAttachRows), dim3(64 * kAttachRows), 0, s, dev, t->lcs,
+                     t->row_begin, a, b, from, pending);
+  FAMSA_HIP(hipGetLastError());
+  pending += b - a;
+  return 0;
+}
+
+// Rows a..b-1, above the forest's vertices: tied to them, then one pass.  more:
+// rows above these follow at once, so the update does too, behind the pass.
+// Rows of kinds that the forest has none of (families listed clade by clade) let
+// all pairs of their kind through; where these do not fit, such rows are tied to
+// each other as well, and the forest takes that in before the pass.
+int famsa_mst_s::merge_block(const famsa_lcs_tile* t, uint32_t a, uint32_t b, bool more, hipStream_t s) {
+  const Rows rows{a - t->row_begin, b - t->row_begin, 1, 0};
+  // so does it where nothing is left to come and the survivors are few whatever
+  // their number (else the exact number saves the rounds that it does not need)
+  const bool take = more || (a == 0 && !pending && std::min<uint64_t>((uint64_t)(b - a) * (k - 1), surv_cap) <= 2 * kFinEdges);
+  int rc = 0;
+  if (more && pending && (rc = update(pending, pending, s))) return rc;
+  if (!kinds) {
+    if ((rc = attach(t, a, b, cover, s))) return rc;
+    if (take) pending = 0;  // the update behind the pass counts the list itself
+    bool fits = false;
+    if ((rc = filter(t, rows, take, s, &fits))) return rc;
+    if (fits) return 0;
+    kinds = true;
+  }
+  if (pending && (rc = update(pending, pending, s))) return rc;
+  if ((rc = attach(t, a, b, 0, s)) || (rc = update(pending, pending, s))) return rc;
+  return merge_rows(t, rows, true, s);
+}
+
+// A tile above the vertices that the forest joins (tiles in descending order),
+// or at the end of the triangle (a family in one tile): its rows are taken
+// from the last one up, each block of them tied to the forest first and then
+// in one pass against it, as many rows as kUpRatio times the forest's vertices.
+// The first kUpFirst rows of all are taken with all their pairs.  With passes
+// spread over the tile instead, every tile in descending order cost three
+// updates (k = 9,000 of 60 residues in tiles of 1,024 rows, LCS and all:
+// 5.9 ms, now 1.7; dense rounds over every tile 4.6), and a family in one tile
+// four, of many survivors each (k = 4,000: 1.54 ms, now 0.87; dense rounds
+// 0.97).  First rows and ratio, k = 700, 2,000 and 4,000 in one tile: 128 and 7
+// 429, 627, 873 us; 128 and 5 429, 662, 887; 160 and 4 474, 718, 934; 256 and
+// 3 514, 670, 904.
+constexpr uint32_t kUpFirst = 128, kUpRatio = 7;
+
+int famsa_mst_s::merge_upwards(const famsa_lcs_tile* t, hipStream_t s) {
+  const uint32_t r0 = t->row_begin, r1 = std::min(t->row_end, k - 1);
+  int rc = 0;
+  uint32_t b = r1;
+  if (cover < b) {
+    if ((rc = merge_rows(t, Rows{cover - r0, b - r0, 1, 0}, true, s))) return rc;
+    b = cover;
+  }
+  while (b > r0) {
+    uint32_t n;
+    if (cover >= k - 1) {  // no forest: b is k - 1
+      n = std::min(b - r0, kUpFirst);
+      while ((uint64_t)n * (n + 1) / 2 > surv_cap) n /= 2;  // (one pair always fits)
+      if ((rc = merge_rows(t, Rows{b - n - r0, b - r0, 1, 0}, false, s))) return rc;
+    } else {
+      const uint64_t most = std::min<uint64_t>((uint64_t)std::max(k - cover, 64u) * kUpRatio, surv_cap / 2);
+      n = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>({b - r0, most, 0xF0000000u / k}));  // survivors in 32 bits
+      if ((rc = merge_block(t, b - n, b, n < b - r0, s))) return rc;
+    }
+    b -= n;
+    cover = b;
+  }
+  return 0;
+}
+
+int famsa_mst_s::merge_tile(const famsa_lcs_tile* t, hipStream_t s) {
+  const uint32_t r0 = t->row_begin, r1 = t->row_end;
+  if (r1 - r0 > 65535u) return set_error(FAMSA_LCS_EINVAL, "tiles of more than 65535 rows are not supported");
+  if (!t->count) {
+    ++tiles;
+    return 0;
+  }
+  if (has_last) FAMSA_HIP(hipStreamWaitEvent(s, last, 0));  // the previous tile's merge, on any stream
+  const uint32_t R = std::min(r1, k - 1) - r0;  // rows with a pair
+  int rc;
+  const bool joined = r0 >= cover, none = cover >= k - 1;  // the forest joins every vertex of the tile, or nothing yet
+  const bool above = !joined && std::min(r1, k - 1) >= std::min(cover, k - 1);  // or all from the tile's end on
+  if (above && !(none && t->count <= surv_cap)) rc = merge_upwards(t, s);
+  else rc = merge_rows(t, Rows{0, R, 1, 0}, joined, s);
+  if (rc) return rc;
   cover = std::min(cover, r0);
   ++tiles;
   return 0;
