@@ -503,8 +503,11 @@ void build_step(WorkLists& wl, const std::vector<StepFamily>& fams, const std::v
   // for them.  So a class is cut from its widest group on into items of
   // 1 / slots of the work that is still left, at most the configured columns
   // and at least a column for each wave of a large workgroup; a class with
-  // fewer columns than that for every workgroup goes down to four (a column a
-  // SIMD).  slots: the workgroups that share the class, which are those the
+  // fewer columns than that for every slot goes down to four (a column a
+  // SIMD), but not to more items than slots: a few items over mean a second
+  // round where a CU holds one workgroup (300 sequences of 2,000 residues and
+  // 32 symbols: 1,059 us in 300 items, 640 in 178; 500 of 1,000 segmented 714
+  // and 620).  slots: the workgroups that share the class, which are those the
   // GPU holds at once, but no more than get kSlotWork residues of columns for
   // each of their waves, and one a CU at least.  With more than one a CU a run
   // is also at least kLeastWork residues for each wave, as far as every slot
@@ -547,12 +550,23 @@ void build_step(WorkLists& wl, const std::vector<StepFamily>& fams, const std::v
   auto cut = [&](const uint64_t (&slots)[4]) {
     uint64_t rest[4] = {left[0], left[1], left[2], left[3]};
     for (auto& v : ci) v.clear();
+    // the shortest runs of a class: sixteen columns, or as few (four at least) as leave no more items than slots
+    uint32_t least[4];
+    for (int c = 0; c < 4; ++c) {
+      least[c] = (uint32_t)std::min<uint64_t>(16, std::max<uint64_t>(4, ncols[c] / slots[c]));
+      for (; least[c] < 16; ++least[c]) {
+        uint64_t items = 0;
+        for (const PendingGroup& pg : pend)
+          if (class_of(pg.g.W, sigma) == c) items += (pg.c1 - pg.c0 + least[c] - 1) / least[c];
+        if (items <= slots[c]) break;
+      }
+    }
     for (uint32_t x : by) {
       const PendingGroup& pg = pend[x];
       const int cls = class_of(pg.g.W, sigma);
       const uint64_t w = wlane(pg.g);
       const uint64_t share = ncols[cls] / slots[cls];  // columns a slot
-      uint32_t cmin = std::min<uint32_t>(cmax, (uint32_t)std::min<uint64_t>(16, std::max<uint64_t>(4, share)));
+      uint32_t cmin = std::min(cmax, least[cls]);
       if (slots[cls] > kCus) {
         const uint64_t len = std::max<uint64_t>(1, colsum(pg, pg.c0, pg.c1) / (pg.c1 - pg.c0));
         cmin = std::max(cmin, (uint32_t)std::min<uint64_t>({cmax, kLeastWork * lp.waves[cls] / len, share}));

@@ -92,3 +92,32 @@ def test_values_either_side(k, lo, hi, sigma):
     B.family_noalloc(codes.data_ptr(), off.data_ptr(), k, out.data_ptr(), status.data_ptr(), alphabet_size=sigma)
     torch.cuda.synchronize()
     assert int(status.item()) == 0 and np.array_equal(out.cpu().numpy(), got[B.PLAIN])
+
+
+@pytest.mark.parametrize("k,lo,hi,sigma,flags", [
+    (500, 1000, 1000, 20, B.LONG_SEGMENTED), (120, 900, 3000, 20, B.LONG_SEGMENTED), (300, 600, 900, 32, B.LONG_SEGMENTED),
+    (40, 5000, 5000, 20, B.LONG_SEGMENTED), (700, 1000, 1000, 20, B.LONG_SEGMENTED), (300, 2000, 2000, 32, 0),
+    (200, 6000, 6000, 20, 0), (100, 15000, 15000, 32, 0), (20, 15000, 15000, 32, 0), (500, 700, 700, 20, 0)])
+def test_no_second_round_for_a_few_items(k, lo, hi, sigma, flags):
+    """One workgroup a CU: a class whose columns fit in as many runs of sixteen has no more items than that, and the
+    shortest such runs; one that is larger has none shorter than sixteen, but at the end of a group."""
+    d, info = workdump.dry_run(inputs.random_family(k, lo, hi, seed=k, alphabet=sigma), alphabet_size=sigma, flags=flags)
+    workdump.check_coverage(d)
+    widest = 28 if sigma <= 20 else 16
+    cols, runs = {}, {}
+    for it in d["items"]:
+        g = int(it["group"])
+        if d["groups"][g]["W"] > widest or lo == 700:
+            cols[g] = cols.get(g, 0) + int(it["c1"] - it["c0"])
+            runs.setdefault(g, []).append(int(it["c1"] - it["c0"]))
+
+    def items(n):
+        return sum(-(-c // n) for c in cols.values())
+
+    n_items = sum(len(r) for r in runs.values())
+    if items(16) <= CUS:
+        assert n_items <= CUS
+        least = next(n for n in range(4, 17) if items(n) <= CUS)
+        assert n_items == items(least)
+    else:
+        assert all(min(r[:-1], default=16) >= 16 for r in runs.values())
