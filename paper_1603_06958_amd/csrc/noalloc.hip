@@ -115,10 +115,8 @@ __device__ void na_plan(const uint64_t* __restrict__ seq_off, uint32_t k, uint32
     sym_off[i] = (uint64_t)i * kNaSymSlot;
     mask_off[i] = (uint64_t)i * kNaMaskSlot;
     s_len[i] = (uint16_t)L;
-    if constexpr (!SMALL) {
-      if (i == 0) s_span[0] = a;
-      if (i == k - 1) s_span[1] = b;
-    }
+    if (i == 0) s_span[0] = a;
+    if (i == k - 1) s_span[1] = b;
     atomicAdd(&s_at[1023u - L], 1u);  // L <= 896
   }
   __syncthreads();
@@ -155,19 +153,14 @@ __device__ void na_plan(const uint64_t* __restrict__ seq_off, uint32_t k, uint32
   const uint32_t G = na_groups(k);
   if (wave < 2) {  // a lane a group; items numbered by a prefix sum
     const uint32_t g = tid;
-    auto dwords = [&]() { return max(1u, (s_len[s_row[kLanes * g]] + 31u) >> 5); };  // of the group's longest row
-    auto class_of = [](uint32_t W) {
-      const uint32_t Q = (W + 3u) >> 2;
-      return Q <= (uint32_t)kClassQMax[0] ? 0 : (Q <= (uint32_t)kClassQMax[1] ? 1 : 2);
-    };
-    uint32_t ni = 0;
+    uint32_t ni = 0, W = 1, cols = 1;
+    int cls = 0;
     if (g < G) {
-      NaRuns r = na_runs_small();
-      if constexpr (!SMALL) {
-        const int cls = class_of(dwords());
-        r = na_runs(k, s_span[1] - s_span[0], cls == 0 ? resident.c0 : (cls == 1 ? resident.c1 : resident.c2));
-      }
-      const uint32_t cols = na_cols(k, g, r);
+      W = max(1u, (s_len[s_row[kLanes * g]] + 31u) >> 5);  // dwords of the group's longest row
+      const uint32_t Q = (W + 3u) >> 2;
+      cls = Q <= (uint32_t)kClassQMax[0] ? 0 : (Q <= (uint32_t)kClassQMax[1] ? 1 : 2);
+      const uint32_t held = cls == 0 ? resident.c0 : (cls == 1 ? resident.c1 : resident.c2);
+      cols = na_cols(k, g, SMALL ? na_runs_small() : na_runs(k, s_span[1] - s_span[0], held));
       ni = na_items(k, g, cols);
       s_cols[g] = cols;
     }
@@ -180,7 +173,7 @@ __device__ void na_plan(const uint64_t* __restrict__ seq_off, uint32_t k, uint32
     if (lane == 63) s_wave[wave] = sum;
     s_first[g] = sum - ni;  // within its wave
     if (g < G) {
-      const uint32_t P = kLanes * g, W = dwords();
+      const uint32_t P = kLanes * g;
       GroupDesc gd;
       gd.lane_first = P;
       gd.nrows = min((uint32_t)kLanes, k - P);
@@ -193,7 +186,7 @@ __device__ void na_plan(const uint64_t* __restrict__ seq_off, uint32_t k, uint32
       gd.lpr = 0;
       gd.pad[0] = gd.pad[1] = gd.pad[2] = 0;
       groups[g] = gd;
-      atomicAdd(&s_cnt[class_of(W)], ni);  // classes do not increase with g: rows are sorted longest first
+      atomicAdd(&s_cnt[cls], ni);  // classes do not increase with g: rows are sorted longest first
     }
   }
   __syncthreads();
