@@ -266,9 +266,10 @@ void famsa_slink_destroy(famsa_slink_t* s);
  * maximum spanning forest of the forest plus the tile's pairs (one pass over
  * the tile keeps the pairs better than the worst edge on the forest's path
  * between their ends; Boruvka rounds on the GPU take these in, those of
- * several tiles at a time, the last ones when the forest is read).  Device memory is O(k),
- * about 1.2 KB a sequence, in one allocation made by famsa_mst_create; tiles
- * hold at most 65535 rows and may come in any order.  Similarities are
+ * several tiles at a time, the last ones when the forest is read).  Device
+ * memory is O(k), 1.2 to 2.2 KB a sequence (129 MB for 100,000), in one
+ * allocation made by famsa_mst_create; tiles hold at most 65535 rows and may
+ * come in any order, ascending or descending being the fastest.  Similarities are
  * ordered exactly; equal similarities are ordered by the pair (u, v), u < v,
  * so the tree is unique.
  * ------------------------------------------------------------------------ */
@@ -361,7 +362,8 @@ int famsa_gapped_create(const uint8_t* codes, const uint64_t* seq_off, uint32_t 
 /* Insert gap runs into sequences first..first+count-1: run r puts len[r] gap
  * columns before column col[r].  Columns are those before this call, sorted
  * ascending, 1 <= col[r] <= width + 1 of every sequence touched (width + 1
- * appends).  One GPU thread per sequence; O(nruns log n) each. */
+ * appends).  1, 4, 16 or 64 lanes a sequence by the number of runs; O(nruns
+ * log n) work each. */
 int famsa_gapped_insert(famsa_gapped_t* g, uint32_t first, uint32_t count, const uint32_t* col, const uint32_t* len,
                         uint32_t nruns);
 /* width[i] = the alignment columns of sequence i (the guard's excluded). */
@@ -414,7 +416,9 @@ void famsa_lcs_server_destroy(famsa_lcs_server_t* srv);
  * the rows per wave, or the segmented kernel) on the plan's first launch
  * step and store the winner in a text cache, one line per GPU architecture
  * and alphabet size ("arch/sigmaN waves0 waves1 waves2 cols long_dwords
- * waves3"; path: cache_path, else FAMSA_LCS_TUNE_CACHE, else none).
+ * waves3", cols being the most columns an item holds; path: cache_path, else
+ * FAMSA_LCS_TUNE_CACHE, else none).  A line holds until it is tuned anew: one
+ * that an earlier version of the library wrote gives up some speed.
  * Results never change.
  * ------------------------------------------------------------------------ */
 int famsa_lcs_autotune(famsa_lcs_plan_t* plan, const char* cache_path);

@@ -12,7 +12,7 @@
 //
 // It is exact: every kernel below returns the DP value bit for bit.
 //
-// Three kernels:
+// The kernels:
 //  * stage_batch   -- column streams and PM[c][w] of every sequence.
 //  * lcs_fast<cls> -- one wavefront handles 64 rows (one per lane) against a
 //    single column sequence, so the column symbol is wave-uniform; each lane
@@ -23,6 +23,9 @@
 //    v_and_b32 (U), v_addc_co_u32 (carry chain through the dwords) and
 //    v_bitop3_b32 (the three-input S | (V & ~M), a gfx950 instruction).
 //    Persistent workgroups pull work items from an atomic queue.
+//  * lcs_small     -- the same for every length class in one launch (small
+//    steps and the allocation-free call).
+//  * lcs_long      -- longer rows, spread over lanes or in segments.
 //  * lcs_plain     -- the baseline: one pair per lane, 64-bit words, masks
 //    read from global memory, no LDS and no queue.
 #include <hip/hip_runtime.h>
@@ -41,10 +44,10 @@ namespace famsa {
 // A batch's column streams and match masks from its codes: four waves take 64
 // residues each of a span of a sequence, in rounds of 256.  Spans 0 .. nseq - 1
 // are the sequences' first ones, the others are listed in `more`.  A wave's 64
-// residues are two mask words
-// of every code, and one ballot a code makes both.  The host built the streams
-// (twice the codes' bytes) and padded copies of the codes before, in seven
-// uploads; a thread a word then compared its 32 residues with every code.
+// residues are two mask words of every code, and one ballot a code makes both.
+// The host built the streams (twice the codes' bytes) and padded copies of the
+// codes before, in seven uploads; a thread a word then compared its 32 residues
+// with every code.
 __device__ __forceinline__ void stage_span(const uint8_t* __restrict__ codes, const uint64_t* __restrict__ dev_off,
                                            const uint32_t* __restrict__ len, const uint64_t* __restrict__ sym_off,
                                            const uint64_t* __restrict__ mask_off, uint32_t s, uint32_t span,

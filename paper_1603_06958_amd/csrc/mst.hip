@@ -10,7 +10,8 @@
 // cycle property).  In steps:
 //   1. a pair (i, j) of the tile can enter the forest only if it is better
 //      than the worst edge on F's path between i and j; one pass over the
-//      tile (mst_filter) keeps the pairs that are, the survivors;
+//      tile (mst_filter) keeps the pairs that are, the survivors (rows that F
+//      does not reach yet are tied to it first, mst_attach);
 //   2. an update, Boruvka on F plus the survivors of one or several tiles,
 //      gives the new forest: every component takes the best edge that leaves
 //      it, components hook along these edges and are renumbered, edges inside
@@ -27,8 +28,8 @@
 // edges a vertex.  Per 1,024-row tile of 30,000 columns the pass takes 12-50 us
 // (later tiles are narrower) and an update, once in several tiles, 150-250 us,
 // most of it launches, against 560 us a tile for dense rounds; k = 12,000
-// sequences of 60 residues to their guide tree 9.1 -> 3.7 ms, k = 30,000 of
-// 250 88.9 -> 66.3 ms (the LCS kernels are 60 of them).
+// sequences of 60 residues to their guide tree 9.3 -> 3.8 ms, k = 30,000 of
+// 250 91.0 -> 67.7 ms (the LCS kernels are 60 of them).
 //
 // Similarity (Methods, "Pairwise similarities calculation") is
 // LCS / indel^2 with indel = |A| + |B| - 2 LCS, +infinity when indel = 0.
@@ -913,7 +914,9 @@ struct famsa_mst_s {
   int merge_tile(const famsa_lcs_tile* t, hipStream_t s);
 };
 
-// One allocation: about 1.2 KB a vertex, most of it room for survivors.
+// One allocation, most of it room for survivors: 1.2 KB a vertex and 0.96 KB
+// more for the first 8,192 (2.2 KB a vertex for small families, 129 MB for
+// 100,000); past a million vertices 0.43 KB a vertex and 0.5 GB.
 int famsa_mst_s::layout() {
   const uint64_t n = std::max<uint32_t>(k, 1);
   const uint64_t pairs = n * (n - 1) / 2;
@@ -929,7 +932,8 @@ int famsa_mst_s::layout() {
   const uint64_t o_len = part(4 * n), o_ctl = part(sizeof(MstCtl)), o_eu = part(4 * E), o_ev = part(4 * E),
                  o_ek = part(8 * E), o_eL = part(4 * E), o_nu = part(4 * n), o_nv = part(4 * n), o_nk = part(8 * n),
                  o_nL = part(4 * n), o_lk = part(16 * E), o_l = part(24 * E), o_ck = part(32 * n),
-                 o_ci = part(32 * n), o_pa = part(16 * n), o_ni = part(16 * n), o_ps = part(2 * sizeof(MstPass)), o_vw = part(sizeof(MstView) * n), o_ex = part(sizeof(MstExact) * n);
+                 o_ci = part(32 * n), o_pa = part(16 * n), o_ni = part(16 * n), o_ps = part(2 * sizeof(MstPass)),
+                 o_vw = part(sizeof(MstView) * n), o_ex = part(sizeof(MstExact) * n);
   int rc = mem.alloc(off);
   if (rc) return rc;
   if ((rc = hflag.alloc(64))) return rc;

@@ -20,7 +20,7 @@
 // Results are the plan path's bit for bit (same kernels, same recurrence).
 // A call of 48 sequences takes 38 us (90 us when the sort was bitonic, staging
 // waited for the plan, and every class had a launch of a full grid), one of
-// 8,192 sequences of 300 residues 5.75 ms (7.08 ms; the LCS kernel is 5.7).
+// 8,192 sequences of 300 residues 6.0 ms (7.2 ms; the LCS kernel is 5.9).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

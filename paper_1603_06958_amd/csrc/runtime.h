@@ -286,7 +286,7 @@ int class_of(uint32_t W, uint32_t sigma);
 struct StepExec {
   uint32_t sigma = 20;
   uint32_t qmax[3] = {0, 0, 0};        // plan-wide, per fast class
-  uint32_t waves[4] = {4, 8, 16, 16};
+  uint32_t waves[4] = {8, 16, 16, 16};
   uint32_t bpc[3][8] = {};             // resident workgroups per CU for fast class c at q quads
   uint32_t blocks[4] = {0, 0, 0, 0};   // [3]: long-row kernel grid
   uint32_t items[4] = {0, 0, 0, 0};    // most items of a class in a step: no more workgroups are launched
