@@ -371,13 +371,14 @@ int famsa_gapped_state(famsa_gapped_t* g, uint32_t s, uint32_t* no_gaps, uint32_
   if (ptree) *ptree = g->h_ptree[s];
   FAMSA_HIP(hipSetDevice(g->device));
   FAMSA_HIP(hipStreamSynchronize(g->s));
+  int rc = 0;
   if (no_gaps)
-    FAMSA_HIP(hipMemcpy(no_gaps, g->gaps.as<uint32_t>() + g->h_pos_off[s], (size_t)g->h_npos[s] * 4,
-                        hipMemcpyDeviceToHost));
-  if (dps)
-    FAMSA_HIP(hipMemcpy(dps, g->dps.as<uint32_t>() + g->h_tree_off[s], (size_t)g->h_ptree[s] * 4,
-                        hipMemcpyDeviceToHost));
-  return 0;
+    rc = copy_now(g->device, no_gaps, g->gaps.as<uint32_t>() + g->h_pos_off[s], (size_t)g->h_npos[s] * 4,
+                  hipMemcpyDeviceToHost);
+  if (!rc && dps)
+    rc = copy_now(g->device, dps, g->dps.as<uint32_t>() + g->h_tree_off[s], (size_t)g->h_ptree[s] * 4,
+                  hipMemcpyDeviceToHost);
+  return rc;
 }
 
 void famsa_gapped_destroy(famsa_gapped_t* g) {

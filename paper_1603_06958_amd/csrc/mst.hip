@@ -881,6 +881,7 @@ struct famsa_mst_s {
   uint32_t cover = 0xFFFFFFFFu;  // the forest joins all vertices from this one on
   DevMem mem;                  // every array below, in one allocation
   MstDev dev{};
+  size_t read_bytes = 0;  // ctl, the last update's forest and the lengths, from mem's start
   PinMem hflag;
   uint64_t tiles = 0;
   // Tiles arrive on whatever stream their producer used (a plan alternates
@@ -929,9 +930,12 @@ int famsa_mst_s::layout() {
     off += (bytes + 255) & ~255ull;
     return at;
   };
-  const uint64_t o_len = part(4 * n), o_ctl = part(sizeof(MstCtl)), o_eu = part(4 * E), o_ev = part(4 * E),
-                 o_ek = part(8 * E), o_eL = part(4 * E), o_nu = part(4 * n), o_nv = part(4 * n), o_nk = part(8 * n),
-                 o_nL = part(4 * n), o_lk = part(16 * E), o_l = part(24 * E), o_ck = part(32 * n),
+  // first what a reader copies, in one piece
+  const uint64_t o_ctl = part(sizeof(MstCtl)), o_nu = part(4 * n), o_nv = part(4 * n), o_nL = part(4 * n),
+                 o_len = part(4 * n);
+  read_bytes = off;
+  const uint64_t o_eu = part(4 * E), o_ev = part(4 * E), o_ek = part(8 * E), o_eL = part(4 * E), o_nk = part(8 * n),
+                 o_lk = part(16 * E), o_l = part(24 * E), o_ck = part(32 * n),
                  o_ci = part(32 * n), o_pa = part(16 * n), o_ni = part(16 * n), o_ps = part(2 * sizeof(MstPass)),
                  o_vw = part(sizeof(MstView) * n), o_ex = part(sizeof(MstExact) * n);
   int rc = mem.alloc(off);
@@ -1313,17 +1317,13 @@ int famsa_mst_result(const famsa_mst_t* m, uint32_t* u, uint32_t* v, int64_t* lc
   std::lock_guard<std::mutex> lock(f->mu);
   int rc = f->settle();
   if (rc) return rc;
-  MstCtl c;
-  FAMSA_HIP(hipMemcpy(&c, m->dev.ctl, sizeof c, hipMemcpyDeviceToHost));
-  const uint32_t n = c.nf;
-  std::vector<uint32_t> hu(n), hv(n), hl(m->k);
-  std::vector<int32_t> hL(n);
-  if (n) {
-    FAMSA_HIP(hipMemcpy(hu.data(), m->dev.eu, n * 4, hipMemcpyDeviceToHost));
-    FAMSA_HIP(hipMemcpy(hv.data(), m->dev.ev, n * 4, hipMemcpyDeviceToHost));
-    FAMSA_HIP(hipMemcpy(hL.data(), m->dev.eL, n * 4, hipMemcpyDeviceToHost));
-  }
-  if (m->k) FAMSA_HIP(hipMemcpy(hl.data(), m->dev.len, (size_t)m->k * 4, hipMemcpyDeviceToHost));
+  std::vector<uint8_t> h(m->read_bytes);
+  if ((rc = copy_now(m->device, h.data(), m->mem.p, h.size(), hipMemcpyDeviceToHost))) return rc;
+  auto at = [&](const void* d) { return h.data() + (static_cast<const uint8_t*>(d) - m->mem.as<uint8_t>()); };
+  const uint32_t n = reinterpret_cast<const MstCtl*>(at(m->dev.ctl))->nf;
+  const uint32_t *hu = reinterpret_cast<const uint32_t*>(at(m->dev.nu)), *hv = reinterpret_cast<const uint32_t*>(at(m->dev.nv));
+  const uint32_t* hl = reinterpret_cast<const uint32_t*>(at(m->dev.len));
+  const int32_t* hL = reinterpret_cast<const int32_t*>(at(m->dev.nL));
   for (uint32_t e = 0; e < n; ++e) {
     if (u) u[e] = hu[e];
     if (v) v[e] = hv[e];
@@ -1357,7 +1357,7 @@ int famsa_mst_get_stats(const famsa_mst_t* m, uint64_t* tiles, uint64_t* rounds)
   int rc = f->settle();
   if (rc) return rc;
   MstCtl c;
-  FAMSA_HIP(hipMemcpy(&c, m->dev.ctl, sizeof c, hipMemcpyDeviceToHost));
+  if ((rc = copy_now(m->device, &c, m->dev.ctl, sizeof c, hipMemcpyDeviceToHost))) return rc;
   if (tiles) *tiles = m->tiles;
   if (rounds) *rounds = c.rounds;
   return 0;

@@ -154,7 +154,7 @@ extern "C" int famsa_valu_peak(int device, uint32_t variant, uint32_t blocks_per
   if (!err && hipEventRecord(e1, s) != hipSuccess) err = 5;
   if (!err && hipEventSynchronize(e1) != hipSuccess) err = 6;
   if (!err && hipEventElapsedTime(&ms, e0, e1) != hipSuccess) err = 7;
-  if (!err && hipMemcpy(h.data(), clocks.p, h.size() * 8, hipMemcpyDeviceToHost) != hipSuccess) err = 8;
+  if (!err && copy_now(device, h.data(), clocks.p, h.size() * 8, hipMemcpyDeviceToHost)) err = 8;
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   (void)hipStreamSynchronize(s);

@@ -456,7 +456,8 @@ int famsa_lcs_plan_s::run(uint64_t first_tile, famsa_lcs_tile_fn fn, void* user)
     hc[s % nslots].stride = (uint32_t)nslots;
     if (nslots == 1) break;
   }
-  FAMSA_HIP(hipMemcpy(d_ctl.p, hc, sizeof hc, hipMemcpyHostToDevice));
+  const int crc = copy_now(opt.device, d_ctl.p, hc, sizeof hc, hipMemcpyHostToDevice);
+  if (crc) return crc;
   if (opt.user_stream) {
     FAMSA_HIP(hipEventRecord(ev_user, opt.user_stream));
     for (int i = 0; i < 2; ++i) FAMSA_HIP(hipStreamWaitEvent(cs[i], ev_user, 0));

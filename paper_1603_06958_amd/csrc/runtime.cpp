@@ -647,6 +647,15 @@ int lib_stream(int device, int i, hipStream_t* out) {
   return 0;
 }
 
+int copy_now(int device, void* dst, const void* src, size_t bytes, hipMemcpyKind kind) {
+  hipStream_t s = nullptr;
+  const int rc = lib_stream(device, kWaitStream, &s);
+  if (rc) return rc;
+  FAMSA_HIP(hipMemcpyAsync(dst, src, bytes, kind, s));
+  FAMSA_HIP(hipStreamSynchronize(s));
+  return 0;
+}
+
 int gpu_info(int device, GpuInfo* gi) {
   hipDeviceProp_t prop;
   FAMSA_HIP(hipGetDeviceProperties(&prop, device));

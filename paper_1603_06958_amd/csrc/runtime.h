@@ -268,9 +268,14 @@ int gpu_info(int device, GpuInfo* gi);
 // streams beyond those share a queue, running one after the other; streams
 // made per plan would therefore lose their overlap as plans come and go.
 // Every plan and server on a device shares these three.
-constexpr int kLibStreams = 3;
+constexpr int kLibStreams = 4;
 constexpr int kCopyStream = 2;
+constexpr int kWaitStream = 3;  // copy_now's
 int lib_stream(int device, int i, hipStream_t* out);
+// A copy that the host waits for, between host memory and `device`.  Not
+// hipMemcpy: that goes over the null stream, which fails, and spoils the
+// capture, while another thread's plan captures its graphs.
+int copy_now(int device, void* dst, const void* src, size_t bytes, hipMemcpyKind kind);
 
 // Maximum spanning forest of an edge set (guide_tree.cpp).
 int spanning_forest(uint32_t k, const uint32_t* u, const uint32_t* v, const int64_t* num, const int64_t* den,
