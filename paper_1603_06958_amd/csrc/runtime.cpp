@@ -570,6 +570,7 @@ void build_step(WorkLists& wl, const std::vector<StepFamily>& fams, const std::v
       if (slots[cls] > kCus) {
         const uint64_t len = std::max<uint64_t>(1, colsum(pg, pg.c0, pg.c1) / (pg.c1 - pg.c0));
         cmin = std::max(cmin, (uint32_t)std::min<uint64_t>({cmax, kLeastWork * lp.waves[cls] / len, share}));
+        if (cmin > 16) cmin = std::min(cmax, (cmin + 15) / 16 * 16);
       }
       const uint64_t per = std::max<uint64_t>(1, w * colsum(pg, pg.c0, pg.c1) / (pg.c1 - pg.c0));  // a column's cost
       for (uint32_t c = pg.c0; c < pg.c1;) {
