@@ -226,11 +226,10 @@ __device__ void na_plan(const uint64_t* __restrict__ seq_off, uint32_t k, uint32
 // takes 64 residues, and one ballot a code is two mask words.  A thread a word
 // compared its 32 residues with every code: 40 us for 8,192 sequences of 300.
 // A code outside the alphabet is marked and staged as code 0, so that the LCS
-// kernels stay within their tables whatever the input.  The caller has found
-// every offset of the family valid.
-__device__ void na_stage(const uint8_t* __restrict__ codes, const uint64_t* __restrict__ seq_off, uint32_t s,
-                         uint32_t sigma, uint8_t* __restrict__ base) {
-  const uint64_t a = seq_off[s], b = seq_off[s + 1];
+// kernels stay within their tables whatever the input.  [a, b): the sequence in
+// `codes`; the caller has found every offset of the family valid.
+__device__ void na_stage(const uint8_t* __restrict__ codes, uint64_t a, uint64_t b, uint32_t s, uint32_t sigma,
+                         uint8_t* __restrict__ base) {
   const uint32_t L = (uint32_t)(b - a), W = (L + 31u) >> 5, lane = threadIdx.x & 63u;
   const uint32_t w0 = (threadIdx.x & (kNaTeam - 1u)) >> 6;
   const uint8_t* src = codes + a;
@@ -266,12 +265,20 @@ __global__ __launch_bounds__(kNaThreads) void na_prep_kernel(const uint8_t* __re
     na_plan<SMALL>(seq_off, k, maxlen, resident, base);
     return;
   }
+  constexpr uint32_t per = kNaThreads / kNaTeam;
+  uint32_t s = (blockIdx.x - 1) * per + threadIdx.x / kNaTeam;
+  uint64_t a = seq_off[min(s, k)], b = seq_off[min(s + 1, k)];  // the first sequence's, with the check's loads
   // no residue is read before the whole family's offsets are known to be valid: a sequence after an invalid one
   // may lie outside the caller's codes
   if (!__syncthreads_and(na_share_valid(seq_off, k, maxlen, threadIdx.x, kNaThreads))) return;
-  constexpr uint32_t per = kNaThreads / kNaTeam;
-  for (uint32_t s = (blockIdx.x - 1) * per + threadIdx.x / kNaTeam; s < k; s += (gridDim.x - 1) * per)
-    na_stage(codes, seq_off, s, sigma, base);
+  while (s < k) {
+    na_stage(codes, a, b, s, sigma, base);
+    s += (gridDim.x - 1) * per;
+    if (s < k) {
+      a = seq_off[s];
+      b = seq_off[s + 1];
+    }
+  }
 }
 
 __global__ __launch_bounds__(256) void na_finish_kernel(uint8_t* __restrict__ base, int32_t* __restrict__ out,
