@@ -49,7 +49,7 @@ void DevMem::reset() {
     const KeptBlock b{p, bytes, device};
     int cur = 0;
     if (!own && bytes >= kKeptLeast && bytes <= kKeptBlock && hipGetDevice(&cur) == hipSuccess && cur == device &&
-        hipDeviceSynchronize() == hipSuccess)
+        lib_streams_wait(device) == 0)
       g_kept.put(b, free_block);
     else
       free_block(b);
@@ -625,14 +625,37 @@ void build_step(WorkLists& wl, const std::vector<StepFamily>& fams, const std::v
   wl.sigs.push_back(sig);
 }
 
+namespace {
+struct StreamPool {
+  std::mutex mu;
+  std::map<int, std::array<hipStream_t, kLibStreams>> of;  // by device; null: not made yet
+};
+
+StreamPool& stream_pool() {
+  static StreamPool* p = new StreamPool;  // never destroyed: blocks may be released while the process ends
+  return *p;
+}
+}  // namespace
+
+int lib_streams_wait(int device) {
+  std::array<hipStream_t, kLibStreams> s{};
+  {
+    StreamPool& pool = stream_pool();
+    std::lock_guard<std::mutex> lock(pool.mu);
+    const auto it = pool.of.find(device);
+    if (it != pool.of.end()) s = it->second;
+  }
+  int rc = 0;
+  for (hipStream_t x : s)
+    if (x && hipStreamSynchronize(x) != hipSuccess) rc = FAMSA_LCS_EDEVICE;
+  return rc;
+}
+
 int lib_stream(int device, int i, hipStream_t* out) {
-  static std::mutex mu;
-  static std::map<int, std::array<hipStream_t, kLibStreams>> pool;
   if (i < 0 || i >= kLibStreams) return set_error(FAMSA_LCS_EINVAL, "stream index %d", i);
-  std::lock_guard<std::mutex> lock(mu);
-  auto it = pool.find(device);
-  if (it == pool.end()) it = pool.emplace(device, std::array<hipStream_t, kLibStreams>{}).first;
-  hipStream_t& st = it->second[i];
+  StreamPool& pool = stream_pool();
+  std::lock_guard<std::mutex> lock(pool.mu);
+  hipStream_t& st = pool.of[device][i];
   if (!st) {
     int cur = 0;
     FAMSA_HIP(hipGetDevice(&cur));

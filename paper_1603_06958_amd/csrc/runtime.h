@@ -25,10 +25,11 @@ void clear_error();
   } while (0)
 
 // RAII device / pinned buffers.  Device blocks go to a store when they are
-// released (kept_store.h).  Releasing one waits for the device, as freeing it
-// does, so a block in the store is in use on no stream.  The store is emptied
-// before an allocation fails; a budget taken from the free memory counts it
-// as free.
+// released (kept_store.h).  Releasing one waits for the library's streams, and
+// its owner has waited for any other stream that used it, so a block in the
+// store is in use on no stream.  (hipDeviceSynchronize would wait for all, but
+// it spoils the graph captures of other threads.)  The store is emptied before
+// an allocation fails; a budget taken from the free memory counts it as free.
 size_t kept_bytes(int device);  // held in the store for `device`
 void kept_empty(int device);    // gives those back
 
@@ -262,16 +263,18 @@ struct GpuInfo {
 };
 int gpu_info(int device, GpuInfo* gi);
 
-// The streams the library runs on, per device: two compute streams and one
-// copy stream, made on first use and kept until the process ends.  HIP backs
-// a process's streams with a few hardware queues (four by default) and
-// streams beyond those share a queue, running one after the other; streams
-// made per plan would therefore lose their overlap as plans come and go.
-// Every plan and server on a device shares these three.
+// The streams the library runs on, per device: two compute streams, one copy
+// stream and one for copy_now, made on first use and kept until the process
+// ends.  HIP backs a process's streams with a few hardware queues (four by
+// default) and streams beyond those share a queue, running one after the
+// other; streams made per plan would therefore lose their overlap as plans
+// come and go.  Every plan and server on a device shares these four.
 constexpr int kLibStreams = 4;
 constexpr int kCopyStream = 2;
 constexpr int kWaitStream = 3;  // copy_now's
 int lib_stream(int device, int i, hipStream_t* out);
+// All that is queued on them, on `device`, is done: 0, or FAMSA_LCS_EDEVICE.
+int lib_streams_wait(int device);
 // A copy that the host waits for, between host memory and `device`.  Not
 // hipMemcpy: that goes over the null stream, which fails, and spoils the
 // capture, while another thread's plan captures its graphs.
