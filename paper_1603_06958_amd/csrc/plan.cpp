@@ -602,7 +602,7 @@ int famsa_lcs_plan(const uint8_t* codes, const uint64_t* seq_off, uint32_t nseq,
   if (hipMemGetInfo(&freeb, &totalb) != hipSuccess) return fail(set_error(FAMSA_LCS_EDEVICE, "hipMemGetInfo failed"));
   freeb += kept_bytes(o.device);
   const uint64_t budget = o.hbm_budget ? o.hbm_budget : (uint64_t)(freeb * 0.9);
-  const uint64_t fixed = DeviceBatchOwner::footprint(seq_off, nseq, o.sigma);
+  const uint64_t fixed = DeviceBatchOwner::footprint(seq_off, nseq, o.sigma, p->plain());
   if (fixed > budget) return fail(set_error(FAMSA_LCS_ENOMEM, "batch needs %llu bytes, budget is %llu",
                                             (unsigned long long)fixed, (unsigned long long)budget));
   if (!o.hbm_budget || fixed + 2 * o.step_values * 4 > budget)
@@ -610,7 +610,7 @@ int famsa_lcs_plan(const uint8_t* codes, const uint64_t* seq_off, uint32_t nseq,
 
   if ((rc = p->host_phase(seq_off, nseq))) return fail(rc);
   if ((rc = p->setup_device())) return fail(rc);
-  if ((rc = p->batch.create(codes, seq_off, nseq, o.sigma, p->cs[0]))) return fail(rc);
+  if ((rc = p->batch.create(codes, seq_off, nseq, o.sigma, p->cs[0], true, p->plain()))) return fail(rc);
   p->batch.values = (o.flags & FAMSA_LCS_OUT_INDEL) ? FAMSA_LCS_VALUES_INDEL
                     : (o.flags & FAMSA_LCS_OUT_SIM) ? FAMSA_LCS_VALUES_SIM
                                                     : FAMSA_LCS_VALUES_LCS;

@@ -178,16 +178,16 @@ DeviceBatch DeviceBatchOwner::view() const {
 static inline uint64_t round_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 
 namespace {
-// Parts of a batch's device allocation, in bytes, from the residues, the
+// Parts of a batch's device allocation, in bytes, from the bytes of codes, the
 // stream bytes, the mask dwords and the spans past the sequences' first: what
 // is uploaded first (offsets, lengths, spans, codes), then what the GPU makes
 // of it.
 struct BatchLayout {
   uint64_t off[8], upload, total;
-  BatchLayout(uint64_t residues, uint64_t sb, uint64_t mw, uint64_t nmore, uint32_t n) {
+  BatchLayout(uint64_t cb, uint64_t sb, uint64_t mw, uint64_t nmore, uint32_t n) {
     const uint64_t nn = n;
     const uint64_t sz[8] = {8 * (nn + 1), 8 * (nn + 1), 8 * (nn + 1), 4 * std::max<uint64_t>(nn, 1),
-                            sizeof(StageSpan) * nmore, residues + 16, std::max<uint64_t>(sb, 16), mw * 4 + 16};
+                            sizeof(StageSpan) * nmore, cb + 16, std::max<uint64_t>(sb, 16), mw * 4 + 16};
     total = upload = 0;
     for (int i = 0; i < 8; ++i) {
       off[i] = total;
@@ -198,19 +198,20 @@ struct BatchLayout {
 };
 }  // namespace
 
-uint64_t DeviceBatchOwner::footprint(const uint64_t* seq_off, uint32_t nseq, uint32_t sigma) {
-  uint64_t words = 0, sb = 0, nmore = 0;
+uint64_t DeviceBatchOwner::footprint(const uint64_t* seq_off, uint32_t nseq, uint32_t sigma, bool spaced) {
+  uint64_t cb = 0, words = 0, sb = 0, nmore = 0;
   for (uint32_t i = 0; i < nseq; ++i) {
     const uint64_t L = seq_off[i + 1] - seq_off[i];
+    cb += code_bytes((uint32_t)L, spaced);
     words += (L + 31) / 32;
     sb += 2ull * stream_codes((uint32_t)L);
     nmore += stage_more_spans((uint32_t)L);
   }
-  return BatchLayout(nseq ? seq_off[nseq] - seq_off[0] : 0, sb, words * sigma, nmore, nseq).total;
+  return BatchLayout(cb, sb, words * sigma, nmore, nseq).total;
 }
 
 int DeviceBatchOwner::create(const uint8_t* hcodes, const uint64_t* seq_off, uint32_t n, uint32_t sig,
-                             hipStream_t s, bool wait) {
+                             hipStream_t s, bool wait, bool spaced) {
   nseq = n;
   sigma = sig;
   h_len.resize(n);
@@ -218,26 +219,26 @@ int DeviceBatchOwner::create(const uint8_t* hcodes, const uint64_t* seq_off, uin
   h_dev_off.resize(n + 1);
   h_mask_off.resize(n + 1);
   h_sym_off.resize(n + 1);
-  uint64_t mw = 0, sb = 0;
+  uint64_t cb = 0, mw = 0, sb = 0;
   std::vector<StageSpan> more;
-  const uint64_t base0 = n ? seq_off[0] : 0, residues = n ? seq_off[n] - base0 : 0;
   max_len = 0;
   for (uint32_t i = 0; i < n; ++i) {
     const uint32_t L = (uint32_t)(seq_off[i + 1] - seq_off[i]);
     h_len[i] = L;
     h_lenprefix[i + 1] = h_lenprefix[i] + L;
     max_len = std::max(max_len, L);
-    h_dev_off[i] = seq_off[i] - base0;
+    h_dev_off[i] = cb;
+    cb += code_bytes(L, spaced);
     h_mask_off[i] = mw;
     mw += (uint64_t)((L + 31) / 32) * sigma;
     h_sym_off[i] = sb;  // ceil(L/8) 16-byte chunks plus one spare
     sb += 2ull * stream_codes(L);
     for (uint32_t x = 1; x <= stage_more_spans(L); ++x) more.push_back(StageSpan{i, x});
   }
-  h_dev_off[n] = residues;
+  h_dev_off[n] = cb;
   h_mask_off[n] = mw;
   h_sym_off[n] = sb;
-  const BatchLayout lay(residues, sb, mw, more.size(), n);
+  const BatchLayout lay(cb, sb, mw, more.size(), n);
   if (mem.bytes < lay.total) {
     const int rc = mem.alloc(lay.total);
     if (rc) return rc;
@@ -248,7 +249,12 @@ int DeviceBatchOwner::create(const uint8_t* hcodes, const uint64_t* seq_off, uin
   memcpy(up.data() + lay.off[2], h_sym_off.data(), 8ull * (n + 1));
   if (n) memcpy(up.data() + lay.off[3], h_len.data(), 4ull * n);
   if (!more.empty()) memcpy(up.data() + lay.off[4], more.data(), sizeof(StageSpan) * more.size());
-  if (residues) memcpy(up.data() + lay.off[5], hcodes + base0, residues);
+  if (spaced) {
+    for (uint32_t i = 0; i < n; ++i)
+      if (h_len[i]) memcpy(up.data() + lay.off[5] + h_dev_off[i], hcodes + seq_off[i], h_len[i]);
+  } else if (cb) {
+    memcpy(up.data() + lay.off[5], hcodes + seq_off[0], cb);
+  }
   uint8_t* base = mem.as<uint8_t>();
   dev_off = reinterpret_cast<uint64_t*>(base + lay.off[0]);
   mask_off = reinterpret_cast<uint64_t*>(base + lay.off[1]);

@@ -114,7 +114,7 @@ int validate_batch(const uint8_t* codes, const uint64_t* seq_off, uint32_t nseq,
 // handed to the next job instead of freed.
 struct DeviceBatchOwner {
   DevMem mem;
-  uint8_t* codes = nullptr;      // sequences back to back
+  uint8_t* codes = nullptr;      // sequences back to back, or each at 32 bytes (spaced: for the plain kernel)
   uint64_t* dev_off = nullptr;
   uint32_t* len = nullptr;
   uint64_t* mask_off = nullptr;
@@ -137,9 +137,9 @@ struct DeviceBatchOwner {
   // does not synchronise: the host sources stay in this object, and work
   // ordered on `s` after the call sees the batch.
   int create(const uint8_t* codes, const uint64_t* seq_off, uint32_t nseq, uint32_t sigma, hipStream_t s,
-             bool wait = true);
+             bool wait = true, bool spaced = false);
   // Device bytes create() needs for this batch.
-  static uint64_t footprint(const uint64_t* seq_off, uint32_t nseq, uint32_t sigma);
+  static uint64_t footprint(const uint64_t* seq_off, uint32_t nseq, uint32_t sigma, bool spaced = false);
 };
 
 // A row tile to compute inside a launch step.

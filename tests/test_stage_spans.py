@@ -61,3 +61,32 @@ def test_more_sequences_than_a_launch_holds():
             p.run(lambda t: got.append(B.tile_array(t).copy()) or 1)
         p.run(lambda t: got.append(B.tile_array(t).copy()), first_tile=n1 + 1)  # the last family's
     assert len(got) == 2 and np.array_equal(got[0], want) and np.array_equal(got[1], want)
+
+
+SPACING = r"""
+#include <cstdio>
+#include "staging.h"
+using namespace famsa;
+int main() {
+  for (unsigned len = 0; len <= 65535; ++len) {
+    const unsigned long long apart = code_bytes(len, true), packed = code_bytes(len, false);
+    if (packed != len || apart % 32 || apart < len || apart >= len + 32ull) printf("length %u: %llu, %llu\n", len, apart, packed);
+  }
+}
+"""
+
+
+def test_a_plain_plans_codes_lie_at_32_bytes(tmp_path):
+    assert hostcode.run(tmp_path, SPACING) == ""
+
+
+@pytest.mark.gpu
+def test_codes_that_begin_past_the_callers_first():
+    rng = np.random.default_rng(5)
+    lens = [0, 1, 31, 32, 33, 64, 0, 95, 96, 97, 261]
+    b = inputs.from_sequences([rng.integers(0, 20, n).astype(np.uint8) for n in lens])
+    codes, off = np.concatenate([np.full(77, 19, np.uint8), b.codes]), b.seq_off + np.uint64(77)
+    want = oracle.tile_expected(b.codes, b.seq_off, 0, len(lens), 0, len(lens))
+    for flags in (0, B.PLAIN):
+        with B.Plan(codes, off, flags=flags) as p:
+            assert np.array_equal(p.collect()[(0, 0, len(lens))], want)
