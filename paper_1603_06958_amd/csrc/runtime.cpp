@@ -681,8 +681,7 @@ int copy_now(int device, void* dst, const void* src, size_t bytes, hipMemcpyKind
   hipStream_t s = nullptr;
   const int rc = lib_stream(device, kWaitStream, &s);
   if (rc) return rc;
-  FAMSA_HIP(hipMemcpyAsync(dst, src, bytes, kind, s));
-  FAMSA_HIP(hipStreamSynchronize(s));
+  FAMSA_HIP(hipMemcpyWithStream(dst, src, bytes, kind, s));
   return 0;
 }
 
